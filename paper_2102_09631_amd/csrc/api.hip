@@ -85,10 +85,13 @@ CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dt
     o += align_up((size_t)r * h_in * 4, 256);
     p.off_Yt = o;
     o += align_up((size_t)r * h_out * 4, 256);
-    p.off_gram = o;
-    o += align_up(qr_part_bytes(h_out, r), 256);
-    p.off_rinv = o;
-    o += 2 * DAD_MAX_RANK * DAD_MAX_RANK * 8;
+    // The orthonormalisation's partials and factors take the place of V where they fit: V is not read again before the
+    // next thin_nn writes it.
+    const size_t gram = align_up(qr_part_bytes(h_out, r), 256), rinv = 2 * DAD_MAX_RANK * DAD_MAX_RANK * 8;
+    const bool in_v = gram + rinv <= (size_t)N * r * 4;
+    p.off_gram = in_v ? p.off_V : o;
+    p.off_rinv = p.off_gram + gram;
+    if (!in_v) o += gram + rinv;
     const size_t rp = r <= 32 ? 32 : 64;
     p.off_Gb = o;
     if (p.dma) o += align_up(rp * (size_t)h_out * 2, 256);
