@@ -110,8 +110,6 @@ RebuildPlan plan_rebuild(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt) {
               : p.f32 ? rebuild_f32_split(K, h_in, h_out)
                       : split_rows(K, ceil_div(h_in, 64) * ceil_div(h_out, 64), 2048, 512, 16);
     p.total = p.split.splits > 1 ? (size_t)p.split.splits * h_in * h_out * 4 : 0;
-    // full gradients (K = N) ask for a workspace whether or not this shape's plan splits K
-    if (p.f32 && p.total == 0 && K >= 512) p.total = 256;
     return p;
 }
 

@@ -137,12 +137,23 @@ def test_grouped_rebuild_rejects_bad_arguments_on_host(lib):
     assert lib.dad_reconstruct_grad_grouped(2, bad, 0, None, 0, None) == dad.DAD_ERR_SHAPE
     bad = (D * 2)(D(p, p, p + 4, 4, 8, 8), D(p, p, p, 8, 16, 24))
     assert lib.dad_reconstruct_grad_grouped(2, bad, 0, None, 0, None) == dad.DAD_ERR_ALIGN
-    big = (D * 2)(D(p, p, p, 1024, 1024, 1024), D(p, p, p, 1024, 1024, 1024))
+    big = (D * 2)(D(p, p, p, 2000, 96, 80), D(p, p, p, 2000, 96, 80))  # a split contraction: at least two slabs of G each
     need = lib.dad_reconstruct_grouped_workspace_bytes(2, big, dad.DAD_F32)
-    assert need >= 2 * lib.dad_reconstruct_workspace_bytes(1024, 1024, 1024, dad.DAD_F32) > 0
+    one = lib.dad_reconstruct_workspace_bytes(2000, 96, 80, dad.DAD_F32)
+    assert need >= 2 * one and one >= 2 * 96 * 80 * 4
     assert lib.dad_reconstruct_grad_grouped(2, big, 0, None, 0, None) == dad.DAD_ERR_NULL
     assert lib.dad_reconstruct_grad_grouped(2, big, 0, p, need - 1, None) == dad.DAD_ERR_WORKSPACE
     assert lib.dad_reconstruct_grouped_workspace_bytes(2, good, dad.DAD_F32) == 0
+
+
+# a product asks for its slabs and for nothing else
+@pytest.mark.parametrize("dt", [dad.DAD_F32, dad.DAD_BF16])
+def test_reconstruct_workspace_is_whole_slabs(lib, dt):
+    for K in (1, 4, 64, 300, 512, 1000, 1024, 4096, 20000):
+        for h_in, h_out in ((3, 70), (96, 80), (784, 1024), (1024, 1024), (256, 512), (2048, 2048)):
+            need = lib.dad_reconstruct_workspace_bytes(K, h_in, h_out, dt)
+            slabs, rest = divmod(need, h_in * h_out * 4)
+            assert rest == 0 and slabs != 1
 
 
 def test_grouped_compress_rejects_bad_arguments_on_host(lib):
