@@ -80,6 +80,17 @@ def test_backprop_edges(gpu, dtype, N, h, hn, act):
     assert O.rel_fro(got, O.backprop_delta(Dn, Wn, Z, act)) <= (1e-5 if dtype == "f32" else 2.0 ** -8)
 
 
+# more rows than 65535 tiles of 64
+@pytest.mark.parametrize("dtype,h,hn", [("f32", 4, 5), ("bf16", 9, 3), ("f32", 2, 1)])
+def test_backprop_many_rows(gpu, dtype, h, hn):
+    N = 64 * 65535 + 70
+    rng = np.random.default_rng([6, h, hn])
+    Dn, Wn, Z = (grid(rng.standard_normal(s), dtype) for s in ((N, hn), (h, hn), (N, h)))
+    got = dad.backprop_delta(dev(Dn, dtype, gpu), dev(Wn, dtype, gpu), dev(Z, dtype, gpu), "relu").float().cpu().numpy()
+    for part in (slice(0, 200), slice(N // 2, N // 2 + 200), slice(N - 200, N)):
+        assert O.rel_fro(got[part], O.backprop_delta(Dn[part], Wn, Z[part], "relu")) <= (1e-5 if dtype == "f32" else 2.0 ** -8)
+
+
 # reductions with fp32 intermediates: every count of 16-row rank blocks less one, whole and plus one; fewer rows
 # than a block; rows and widths that end inside a block; widths around one 16-byte load; row chunks of thin_tn; several
 # row tiles per wave of thin_nn (N >= 8192 and N >= 32768); 64-column blocks in pairs; slabs summed before and by the
