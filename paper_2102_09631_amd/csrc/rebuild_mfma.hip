@@ -230,8 +230,11 @@ constexpr int DMA_LOADS = 4;  // 16-byte loads per thread per stage, for both ti
 // SRC is `const bf16_t*` (operands in one allocation each) or RowBlocks (the sites' blocks in
 // place, the same row split for both operands, every block a multiple of 256 rows): a K chunk may
 // span blocks, and the operand pointers jump at a block's end.
+// TAIL: K is not a multiple of BK.  The rows of the last stage beyond K repeat row K - 1 and are zeroed in LDS before they are
+// multiplied.  Whole K has an instance without that code: in the one loop of both it cost every product 4 to 7 %
+// (65536 x 1024 x 4096: 484 -> 504 us, zero factors 350 -> 368 us; 242 -> 250 VGPRs, 32 -> 52 SGPRs).
 // One workgroup's tile: `lid` is its logical index among the tiles_m * tiles_n * splits of this product.
-template <int T, int WM, int WN, typename SRC>
+template <int T, int WM, int WN, typename SRC, bool TAIL>
 __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, float* __restrict__ out, int64_t K, int h_in,
                                                  int h_out, int64_t chunk, int tiles_m, int tiles_n, int lid) {
     constexpr int WAVES = WM * WN;
@@ -242,6 +245,7 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
     constexpr int CPR = ROWB / 16;                         // 16-byte chunks per row
     constexpr int RPI = 64 / CPR;                          // tile rows covered by one load of a wave
     static_assert(rb::BK == 2 * RPI * WAVES, "two loads per wave and operand cover a stage");
+    static_assert(!TAIL || std::is_pointer<SRC>::value, "row blocks are whole stages");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -259,10 +263,8 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
     const int p0 = pm * T, q0 = qn * T;
     const int64_t kbeg = (int64_t)split * chunk;
     const int64_t kend = (kbeg + chunk < K) ? kbeg + chunk : K;
-    const int nk = (int)((kend - kbeg + rb::BK - 1) / rb::BK);
-    // rows of the last stage beyond K (only the last chunk of a K that is not a multiple of BK): their
-    // loads repeat row K - 1, and the stage's LDS rows are zeroed before they are multiplied
-    const int tail = (int)((int64_t)nk * rb::BK - (kend - kbeg));
+    const int nk = (int)((kend - kbeg + (TAIL ? rb::BK - 1 : 0)) / rb::BK);
+    const int tail = TAIL ? (int)((int64_t)nk * rb::BK - (kend - kbeg)) : 0;  // rows of the last stage beyond K
 
     // this lane's two rows per operand tile: row = 2*RPI*wave + RPI*i + lane/CPR, LDS chunk position lane%CPR
     RowCursor cur_l, cur_r;
@@ -294,7 +296,9 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
                     gr[i] += jr;
                 }
             }
-        } else {
+            row_next += rb::BK;
+        }
+        if constexpr (TAIL) {
             if (row_next + rb::BK > kend) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
@@ -305,8 +309,8 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
                     }
                 }
             }
+            row_next += rb::BK;
         }
-        row_next += rb::BK;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             dma16(gl[i], base + RPI * i * ROWB);
@@ -371,12 +375,14 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
         __syncthreads();  // everyone's part of tile kt is in LDS, and tile kt-1's slot is free
         if (kt + rb::DMA_STAGES - 1 < nk) issue((STAGE + rb::DMA_STAGES - 1) % rb::DMA_STAGES);
         const char* tl = smem + STAGE * STAGEB;
-        if (tail && kt == nk - 1) {
-            for (int e = t; e < tail * CPR; e += 64 * WAVES)
+        if constexpr (TAIL) {
+            if (tail && kt == nk - 1) {
+                for (int e = t; e < tail * CPR; e += 64 * WAVES)
 #pragma unroll
-                for (int op = 0; op < 2; ++op)
-                    *reinterpret_cast<u32x4*>(smem + STAGE * STAGEB + op * TILEB + (rb::BK - tail) * ROWB + e * 16) = u32x4{0, 0, 0, 0};
-            __syncthreads();
+                    for (int op = 0; op < 2; ++op)
+                        *reinterpret_cast<u32x4*>(smem + STAGE * STAGEB + op * TILEB + (rb::BK - tail) * ROWB + e * 16) = u32x4{0, 0, 0, 0};
+                __syncthreads();
+            }
         }
         constexpr int NR = 2 * (FA + FB), NM = FA * FB;  // LDS reads and MFMAs per K-step
         __builtin_amdgcn_sched_barrier(0);
@@ -413,12 +419,12 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
         }
 }
 
-template <int T, int WM, int WN, typename SRC>
+template <int T, int WM, int WN, typename SRC, bool TAIL>
 __global__ __launch_bounds__(64 * WM * WN) void k_rebuild_bf16_dma(const SRC L, const SRC R,
                                                                   float* __restrict__ out, int64_t K, int h_in,
                                                                   int h_out, int64_t chunk, int tiles_m,
                                                                   int tiles_n, int total) {
-    rebuild_tile_dma<T, WM, WN, SRC>(L, R, out, K, h_in, h_out, chunk, tiles_m, tiles_n, rb_logical_id(total));
+    rebuild_tile_dma<T, WM, WN, SRC, TAIL>(L, R, out, K, h_in, h_out, chunk, tiles_m, tiles_n, rb_logical_id(total));
 }
 
 // Several products in one launch (the full gradients of the layers of a block): gradients with few
@@ -438,7 +444,7 @@ struct RebuildJobs {
     RebuildJob j[rb::MAX_JOBS];
 };
 
-template <int T, int WM, int WN>
+template <int T, int WM, int WN, bool TAIL>
 __global__ __launch_bounds__(64 * WM * WN) void k_rebuild_bf16_dma_jobs(RebuildJobs tb, int total) {
     const int lid = rb_logical_id(total);
     int ji = 0;
@@ -447,8 +453,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_rebuild_bf16_dma_jobs(RebuildJ
     const RebuildJob& jb = tb.j[ji];
     const bf16_t* L = jb.L;
     const bf16_t* R = jb.R;
-    rebuild_tile_dma<T, WM, WN, const bf16_t*>(L, R, jb.out, jb.K, jb.h_in, jb.h_out, jb.chunk, jb.tiles_m, jb.tiles_n,
-                                               lid - tb.first_block[ji]);
+    rebuild_tile_dma<T, WM, WN, const bf16_t*, TAIL>(L, R, jb.out, jb.K, jb.h_in, jb.h_out, jb.chunk, jb.tiles_m, jb.tiles_n,
+                                                     lid - tb.first_block[ji]);
 }
 
 
@@ -531,12 +537,17 @@ static dad_status launch_rebuild_dma(const void* L, const void* R, const RowBloc
     const int tm = (int)(h_in / T), tn = (int)(h_out / T);
     const int total = tm * tn * sp.splits;
     ProfScope prof(KID_REBUILD_BF16_DMA, s);
+    const dim3 grid((unsigned)total), block(64 * WM * WN);
+    const bf16_t *l = static_cast<const bf16_t*>(L), *r = static_cast<const bf16_t*>(R);
     if (lb)
-        hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, RowBlocks>), dim3((unsigned)total), dim3(64 * WM * WN), lds, s,
-                           *lb, *rbk, dst, K, (int)h_in, (int)h_out, sp.chunk, tm, tn, total);
+        hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, false>), grid, block, lds, s, *lb, *rbk, dst, K, (int)h_in,
+                           (int)h_out, sp.chunk, tm, tn, total);
+    else if (K % rb::BK == 0)
+        hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, false>), grid, block, lds, s, l, r, dst, K, (int)h_in,
+                           (int)h_out, sp.chunk, tm, tn, total);
     else
-        hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*>), dim3((unsigned)total), dim3(64 * WM * WN), lds,
-                           s, (const bf16_t*)L, (const bf16_t*)R, dst, K, (int)h_in, (int)h_out, sp.chunk, tm, tn, total);
+        hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, true>), grid, block, lds, s, l, r, dst, K, (int)h_in,
+                           (int)h_out, sp.chunk, tm, tn, total);
     DAD_LAUNCH_CHECK();
     return DAD_OK;
 }
@@ -615,6 +626,7 @@ dad_status launch_rebuild_group(int n, const void* const* L, const void* const* 
         const int cnt = n - first < rb::MAX_JOBS ? n - first : rb::MAX_JOBS;
         RebuildJobs tb;
         int64_t blocks = 0;
+        bool ragged = false;
         for (int i = 0; i < rb::MAX_JOBS; ++i) {
             if (i >= cnt) {
                 tb.first_block[i] = 0x7fffffff;
@@ -627,6 +639,7 @@ dad_status launch_rebuild_group(int n, const void* const* L, const void* const* 
             jb.R = static_cast<const bf16_t*>(R[k]);
             jb.out = sp[k].splits == 1 ? G[k] : slabs[k];
             jb.K = K[k];
+            ragged |= K[k] % rb::BK != 0;
             jb.chunk = sp[k].chunk;
             jb.h_in = (int)h_in[k];
             jb.h_out = (int)h_out[k];
@@ -638,7 +651,10 @@ dad_status launch_rebuild_group(int n, const void* const* L, const void* const* 
         }
         {
             ProfScope prof(KID_REBUILD_BF16_DMA, s);
-            hipLaunchKernelGGL((k_rebuild_bf16_dma_jobs<256, 2, 4>), dim3((unsigned)blocks), dim3(512), lds, s, tb, (int)blocks);
+            if (ragged)
+                hipLaunchKernelGGL((k_rebuild_bf16_dma_jobs<256, 2, 4, true>), dim3((unsigned)blocks), dim3(512), lds, s, tb, (int)blocks);
+            else
+                hipLaunchKernelGGL((k_rebuild_bf16_dma_jobs<256, 2, 4, false>), dim3((unsigned)blocks), dim3(512), lds, s, tb, (int)blocks);
         }
         DAD_LAUNCH_CHECK();
     }
@@ -650,13 +666,21 @@ dad_status launch_rebuild_group(int n, const void* const* L, const void* const* 
     return DAD_OK;
 }
 
-dad_status rebuild_prepare_device() {
-    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma_jobs<256, 2, 4>), rb::DMA_STAGES * 2 * rb::BK * 256 * 2));
-    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<256, 2, 4, const bf16_t*>), rb::DMA_STAGES * 2 * rb::BK * 256 * 2));
-    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<128, 2, 2, const bf16_t*>), rb::DMA_STAGES * 2 * rb::BK * 128 * 2));
-    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<256, 2, 4, RowBlocks>), rb::DMA_STAGES * 2 * rb::BK * 256 * 2));
-    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<128, 2, 2, RowBlocks>), rb::DMA_STAGES * 2 * rb::BK * 128 * 2));
+template <int T, int WM, int WN>
+static dad_status prepare_dma() {
+    constexpr int lds = rb::DMA_STAGES * 2 * rb::BK * T * 2;
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, false>), lds));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, false>), lds));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, true>), lds));
     return DAD_OK;
+}
+
+dad_status rebuild_prepare_device() {
+    constexpr int lds = rb::DMA_STAGES * 2 * rb::BK * 256 * 2;
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma_jobs<256, 2, 4, false>), lds));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma_jobs<256, 2, 4, true>), lds));
+    const dad_status rc = prepare_dma<256, 2, 4>();
+    return rc != DAD_OK ? rc : prepare_dma<128, 2, 2>();
 }
 
 }  // namespace dad

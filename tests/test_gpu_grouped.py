@@ -49,6 +49,14 @@ def test_grouped_rebuild_with_split_contraction_and_many_jobs(gpu):
         _check_against_oracle(b, L, R, 1e-5)
 
 
+def test_grouped_rebuild_bf16_whole_and_ragged_rows(gpu):
+    """Runs of whole 256-tiles that share a launch: all of whole K stages, and with a ragged K among them."""
+    whole, ragged = _pair(2048, 256, 512, 21, gpu, torch.bfloat16), _pair(2077, 512, 256, 22, gpu, torch.bfloat16)
+    for pairs in ([whole, whole], [whole, ragged, whole], [ragged, ragged]):
+        for (L, R), G in zip(pairs, dad.reconstruct_grad_grouped(pairs)):
+            _check_against_oracle(G, L, R, 1e-5)
+
+
 def test_grouped_rebuild_bf16_jobs(gpu):
     pairs = [_pair(4096, 512, 768, 7, gpu, torch.bfloat16), _pair(1000, 256, 264, 8, gpu, torch.bfloat16)]
     single = [dad.reconstruct_grad(L, R) for L, R in pairs]
