@@ -233,6 +233,9 @@ constexpr int DMA_LOADS = 4;  // 16-byte loads per thread per stage, for both ti
 // TAIL: K is not a multiple of BK.  The rows of the last stage beyond K repeat row K - 1 and are zeroed in LDS before they are
 // multiplied.  Whole K has an instance without that code: in the one loop of both it cost every product 4 to 7 %
 // (65536 x 1024 x 4096: 484 -> 504 us, zero factors 350 -> 368 us; 242 -> 250 VGPRs, 32 -> 52 SGPRs).
+// With 128-tiles such a K also adds every 256 rows to a second accumulator, as k_rebuild_bf16 does and for its reason
+// (3077 x 1152 x 2176, error against fp64: 2.7e-7 with one running sum over a chunk, 0.97e-7 folded, fp32 FMA kernel before
+// 1.4e-7; 20011 x 1152 x 2176: 121 -> 129 us, FMA kernel 1470 us); 256-tiles have no registers for it.
 // One workgroup's tile: `lid` is its logical index among the tiles_m * tiles_n * splits of this product.
 template <int T, int WM, int WN, typename SRC, bool TAIL>
 __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, float* __restrict__ out, int64_t K, int h_in,
@@ -331,6 +334,23 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
+    constexpr bool FOLD = TAIL && T == 128;
+    f32x16 sum[FOLD ? FA : 1][FOLD ? FB : 1];
+    auto fold = [&](bool first) {
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int a = 0; a < FA; ++a)
+#pragma unroll
+                for (int b = 0; b < FB; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        sum[a][b][v] = first ? acc[a][b][v] : sum[a][b][v] + acc[a][b][v];
+                        acc[a][b][v] = 0.f;
+                    }
+        }
+    };
+    fold(true);
+
 #pragma unroll
     for (int s = 0; s < rb::DMA_STAGES - 1; ++s)
         if (s < nk) issue(s);
@@ -400,8 +420,10 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
         if (kt + 1 < nk) step(kt + 1, std::integral_constant<int, 1>{});
         if (kt + 2 < nk) step(kt + 2, std::integral_constant<int, 2>{});
         if (kt + 3 < nk) step(kt + 3, std::integral_constant<int, 3>{});
+        if (FOLD && (kt & rb::DMA_STAGES)) fold(false);
     }
     if (nk > 0) mma(fa1, fb1);
+    fold(false);
 
     // D[q][p] layout: lane holds p = lane % 32 and q = 8*g + 4*(lane/32) + 0..3 for g = 0..3: 16-byte stores
     float* o = out + (int64_t)split * h_in * h_out;
@@ -413,7 +435,8 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
             const int qb = q0 + wn * (FB * 32) + b * 32 + ((lane >> 5) << 2);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                f32x4 v4 = {acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
+                const f32x16& x = FOLD ? sum[FOLD ? a : 0][FOLD ? b : 0] : acc[a][b];
+                f32x4 v4 = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
                 *reinterpret_cast<f32x4*>(o + (int64_t)p * h_out + qb + 8 * g) = v4;
             }
         }

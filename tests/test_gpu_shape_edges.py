@@ -37,11 +37,13 @@ def test_rebuild_bf16_edges(gpu, K, h_in, h_out):
 
 # long sums: 256 rows are summed by the matrix instructions (16 roundings of about 3.4e-8 at a third of the height, 8e-8
 # together), then added to the rest (K / 256 roundings, 7e-8 at K = 3072); one running sum is at 2.5e-7
-@pytest.mark.parametrize("K", [256, 257, 512, 3072])
-def test_rebuild_bf16_long_sums(gpu, K):
+# (the direct-to-LDS kernel on 128-tiles: 2176 columns, K that is not a multiple of 32)
+@pytest.mark.parametrize("K,h_out", [(256, 2101), (257, 2101), (512, 2101), (3072, 2101), (287, 2176), (513, 2176), (1025, 2176),
+                                     (3077, 2176)])
+def test_rebuild_bf16_long_sums(gpu, K, h_out):
     rng = np.random.default_rng([31, K])
     A = grid(np.maximum(rng.standard_normal((K, 1152)), 0.0), "bf16")
-    D = grid(rng.standard_normal((K, 2101)), "bf16")
+    D = grid(rng.standard_normal((K, h_out)), "bf16")
     G = dad.reconstruct_grad(dev(A, "bf16", gpu), dev(D, "bf16", gpu))
     assert O.rel_fro(G.cpu().numpy(), O.full_grad(A, D)) <= 1.5e-7
 
