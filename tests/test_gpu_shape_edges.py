@@ -118,6 +118,19 @@ def test_reduction_edges(gpu, dtype, N, h_in, h_out, r):
     assert torch.equal(Pt, Pt2) and torch.equal(Gt, Gt2)
 
 
+# wide fp32 rows: thin_nn adds sums of 64 columns (16 matrix instructions) and of its waves.  An application is four
+# contractions of about 1.2e-7 each, 3e-7 for the pair's product; one running sum over a wave's share of a row is at 6.5e-7
+@pytest.mark.parametrize("N,h_in,h_out,r", [(186, 4096, 4096, 35), (64, 4096, 4096, 16), (128, 6000, 5000, 4), (187, 4093, 4090, 35)])
+def test_reduction_f32_long_sums(gpu, N, h_in, h_out, r):
+    rng = np.random.default_rng([33, N, h_in, h_out, r])
+    A = rng.standard_normal((N, h_in)).astype(np.float32)
+    D = (0.01 * rng.standard_normal((N, h_out))).astype(np.float32)
+    G0 = rng.standard_normal((r, h_out)).astype(np.float32)
+    Pt, Gt = dad.compress_rank(*(torch.from_numpy(x).to(gpu) for x in (A, D)), r, 2, torch.from_numpy(G0).to(gpu), check=True)
+    ref = O.rank_r_grad(*O.block_spi(A, D, G0, 2))
+    assert O.rel_fro(Pt.cpu().numpy().astype(np.float64).T @ Gt.cpu().numpy(), ref) <= 4.5e-7
+
+
 # orthonormalisation of a given iterate (A = Delta = I, one application: Y = G0^T): condition numbers on either side of
 # the bound for a second round, up to columns that differ only in their last fp32 bits; one and several workgroups
 @pytest.mark.parametrize("h,r", [(40, 7), (64, 16), (300, 32), (700, 33), (700, 64), (2700, 64), (4200, 20)])
