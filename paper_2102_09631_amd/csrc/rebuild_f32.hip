@@ -85,11 +85,25 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
             y[set][s] = *reinterpret_cast<const f32x4_b4*>(r + (uint32_t)rc * (uint32_t)h_out + qc);
         }
     };
-    f32x4 acc[4][4];
+    // The matrix instructions sum FOLD rounds of three steps (192 K rows), which are then added to the rest: one running
+    // sum over a wave's share of K rounds at full height with every instruction (2048 x 2304 x 756, error against fp64:
+    // 5.7e-7 with one sum, 2.5e-7 so, the LDS-staged kernel before 4.7e-7; 4096 x 2048 x 2048: 274 -> 283 us, 384 rows 278 us
+    // but 2560 x 403 x 977 then at 2.3e-7, before 2.1e-7).
+    constexpr int FOLD = 4;
+    f32x4 acc[4][4], sum[4][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 4; ++b) acc[a][b] = sum[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto fold = [&]() {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                sum[a][b] += acc[a][b];
+                acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
     auto compute = [&](auto set_c, int b) {
         constexpr int set = decltype(set_c)::value;
         const int64_t left = kend - kbeg - (int64_t)b * rf::BK;
@@ -115,7 +129,12 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
         auto at_most = [&](int b) { return b < nb ? b : nb - 1; };
         load(s0, kp);
         load(s1, at_most(kp + ks));
+        int round = 0;
         for (int b = kp; b < nb; b += 3 * ks) {
+            if (++round > FOLD) {
+                fold();
+                round = 1;
+            }
             load(s2, at_most(b + 2 * ks));
             __builtin_amdgcn_sched_barrier(0);
             compute(s0, b);
@@ -131,7 +150,9 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
         }
     }
 
-    // acc[a][e][v]: row p0 + 16 q + 4 v + a, column q0 + 4 c + e.  A lane's row of a tile that was moved back:
+    fold();
+
+    // sum[a][e][v]: row p0 + 16 q + 4 v + a, column q0 + 4 c + e.  A lane's row of a tile that was moved back:
     // its operand columns are pc .. pc + 3, i.e. rows indexed by the lane that holds them.
     float* o = jb.out + (int64_t)split * h_in * h_out;
     auto store = [&](int a, int v, f32x4 g) {
@@ -144,14 +165,14 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) store(a, v, f32x4{acc[a][0][v], acc[a][1][v], acc[a][2][v], acc[a][3][v]});
+            for (int v = 0; v < 4; ++v) store(a, v, f32x4{sum[a][0][v], sum[a][1][v], sum[a][2][v], sum[a][3][v]});
         return;
     }
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         if (a) __syncthreads();
 #pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][v][lane] = f32x4{acc[a][0][v], acc[a][1][v], acc[a][2][v], acc[a][3][v]};
+        for (int v = 0; v < 4; ++v) red[wave][v][lane] = f32x4{sum[a][0][v], sum[a][1][v], sum[a][2][v], sum[a][3][v]};
         __syncthreads();
         for (int v = kp; v < 4; v += ks) {
             f32x4 g = red[tile * ks][v][lane];

@@ -152,6 +152,16 @@ def test_orthonormalisation_of_ill_conditioned_iterates(gpu, h, r, log_cond):
 
 # fp32 gradients: K around a 16-row step and around what two, four and eight waves per tile need, tiles less one, whole
 # and plus one column, one and several tiles per workgroup, slabs (long K, few tiles), widths below one 16-byte load
+# long fp32 sums: rounds of 192 rows (48 instructions of four products, 1.4e-7) added to the rest (K / 192 roundings); one
+# running sum over a wave's share of K is at 5.7e-7
+@pytest.mark.parametrize("K,h_in,h_out", [(2048, 2304, 756), (4096, 1024, 1024), (8191, 500, 700), (191, 300, 300), (577, 2100, 1030)])
+def test_rebuild_f32_long_sums(gpu, K, h_in, h_out):
+    rng = np.random.default_rng([34, K, h_in, h_out])
+    A, D = rng.standard_normal((K, h_in)).astype(np.float32), rng.standard_normal((K, h_out)).astype(np.float32)
+    G = dad.reconstruct_grad(dev(A, "f32", gpu), dev(D, "f32", gpu))
+    assert O.rel_fro(G.cpu().numpy(), O.full_grad(A, D)) <= 3.7e-7
+
+
 @pytest.mark.parametrize("K,h_in,h_out", [(1, 4, 5), (5, 3, 70), (15, 64, 63), (16, 65, 64), (17, 130, 66), (33, 300, 1030),
                                           (255, 640, 641), (257, 1030, 1025), (1000, 2100, 2060), (3000, 129, 10), (9001, 70, 65)])
 def test_rebuild_f32_edges(gpu, K, h_in, h_out):
