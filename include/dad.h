@@ -169,18 +169,20 @@ dad_status dad_compress_rank_noalloc(const void* A, const void* D, int64_t N, in
 
 /*
  * dad_compress_rank_grouped - dad_compress_rank for n layers in one call (Algorithm 1 reduces every
- * layer's pair in the same step).  Layer i gets exactly the launches of dad_compress_rank on its own
- * region of the workspace, so its Pt, Gt are bit-identical to a single call's; up to `lanes` layers
- * are in flight at once (layer i on lane i mod lanes), so that the short, latency-bound launches of
- * one layer's orthonormalisation run while another layer streams its factors.  A run of consecutive
- * stacked layers of equal N that the bf16 direct-to-LDS kernels serve (N a multiple of 256, widths
- * multiples of 128, r in {16, 32, 64}) is executed as a batch of up to 32: every launch does the
- * same step of all its layers, so the run costs the launches of one layer.  Batched are layers of
- * equal widths with at most 256 MiB of factors each (typically the S site reductions of one layer
- * in Algorithm 1, each site's block passed as a layer), and layers of unequal widths, all multiples
- * of 256, with at most 64 MiB each (the layers of a small block).  A batch takes one lane and as
- * many workspace regions as it has layers (the size query accounts for that); its results are still
- * bit-identical to single calls.
+ * layer's pair in the same step).  Every layer's Pt, Gt are bit-identical to a single call's; up to
+ * `lanes` layers (or batches, below) are in flight at once, each in its own region of the workspace, so
+ * that the short, latency-bound launches of one layer run beside another's.  How, depends on the layer:
+ *   - fp32 layers and bf16 layers outside the whole-tile sizes below share merged launches on `stream`, as
+ *     many at a time as they have regions (lanes = 1: one after the other);
+ *   - a run of consecutive stacked layers of equal N that the bf16 direct-to-LDS kernels serve (N a
+ *     multiple of 256, widths multiples of 128, r in {16, 32, 64}) is executed as a batch of up to 32: every
+ *     launch does the same step of all its layers, so the run costs the launches of one layer.  Batched
+ *     are layers of equal widths with at most 256 MiB of factors each (typically the S site reductions of
+ *     one layer in Algorithm 1, each site's block passed as a layer), and layers of unequal widths, all
+ *     multiples of 256, with at most 64 MiB each (the layers of a small block).  A batch takes one lane and
+ *     as many workspace regions as it has layers (the size query accounts for that);
+ *   - the other layers are dealt to the lanes in turn.
+ * A group of both kinds shares the lanes between the merged launches and the others by their numbers.
  *   descs     HOST array of n layers, 1 <= n <= DAD_MAX_GROUP; every pointer is a device pointer with
  *             the meaning and alignment of dad_compress_rank's.  A layer with S > 0 gives its factors
  *             as the S site blocks of dad_stack_factors (A_sites, D_sites, rows: HOST arrays read

@@ -1,4 +1,6 @@
 """Grouped entry points against the single-layer calls (bit for bit) and against the oracle."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -344,3 +346,76 @@ def test_a_whole_step_replays_from_one_hip_graph(gpu):
         torch.cuda.synchronize()
     ref = O.full_grad(stacked[2][0].float().cpu().numpy(), stacked[2][1].float().cpu().numpy())
     assert O.rel_fro(full.G[2].cpu().numpy(), ref) <= 1e-5
+
+
+# ---------------------------------------------------------------- groups of both kinds: whole tiles and any shape
+
+def _longest_chain(graph):
+    """(nodes on the longest dependent chain, nodes) of a captured graph."""
+    lib = C.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+    raw, n = C.c_void_p(graph.raw_cuda_graph()), C.c_size_t(0)
+    assert lib.hipGraphGetNodes(raw, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert lib.hipGraphGetNodes(raw, nodes, C.byref(n)) == 0
+    m = C.c_size_t(0)
+    assert lib.hipGraphGetEdges(raw, None, None, C.byref(m)) == 0
+    src, dst = (C.c_void_p * m.value)(), (C.c_void_p * m.value)()
+    assert lib.hipGraphGetEdges(raw, src, dst, C.byref(m)) == 0
+    after = {v: [] for v in nodes}
+    before = {v: 0 for v in nodes}
+    for a, b in zip(src, dst):
+        after[a].append(b)
+        before[b] += 1
+    depth, ready = {v: 1 for v in nodes}, [v for v in nodes if before[v] == 0]
+    while ready:
+        v = ready.pop()
+        for w in after[v]:
+            depth[w] = max(depth[w], depth[v] + 1)
+            before[w] -= 1
+            if before[w] == 0:
+                ready.append(w)
+    return max(depth.values()), n.value
+
+
+MIXED = [(1024, 256, 384), (1000, 200, 384), (2048, 384, 256), (1000, 384, 200), (1024, 512, 384), (300, 130, 70)]
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 4, 8])
+def test_mixed_group_equals_single_calls_and_replays(gpu, lanes):
+    dad.init()
+    layers = [_layer(n, a, b, 16, 700 + i, gpu, torch.bfloat16) for i, (n, a, b) in enumerate(MIXED)]
+    single = [dad.compress_rank(A, D, 16, 2, G0, check=True) for A, D, G0 in layers]
+    grp = dad.CompressGroup(layers, 16, 2, lanes=lanes)
+    broken = dad.CompressGroup([(A, torch.zeros_like(D) if i == 3 else D, G0) for i, (A, D, G0) in enumerate(layers)], 16, 2,
+                               lanes=lanes, workspace=grp.workspace)
+    broken.run()
+    assert dad.poll_numeric_status(grp.workspace) == dad.DAD_ERR_NUMERIC
+    grp.run(check=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        grp.run()
+    for rep in range(4):
+        for p, g in zip(grp.Pt, grp.Gt):
+            p.fill_(float("nan"))
+            g.fill_(float("nan"))
+        if rep:
+            graph.replay()
+        else:
+            grp.run(check=True)
+        torch.cuda.synchronize()
+        for (p1, g1), p2, g2 in zip(single, grp.Pt, grp.Gt):
+            assert torch.equal(p1, p2) and torch.equal(g1, g2), rep
+
+
+def test_mixed_group_runs_its_layers_side_by_side(gpu):
+    """Whole-tile and odd-width layers in turn, four lanes: the longest chain of dependent launches is that of the
+    layers of one lane, not of all of them."""
+    dad.init()
+    layers = [_layer(n, a, b, 16, 720 + i, gpu, torch.bfloat16) for i, (n, a, b) in enumerate(MIXED)]
+    grp = dad.CompressGroup(layers, 16, 2, lanes=4)
+    grp.run(check=True)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        grp.run()
+    chain, nodes = _longest_chain(graph)
+    assert chain <= 0.6 * nodes, (chain, nodes)
