@@ -270,7 +270,10 @@ dad_status dad_compress_rank_gram(const void* A, const void* D, int64_t N, int64
                                   int r, int n_iter, const float* G0, float* Pt, float* Gt, void* workspace,
                                   size_t ws_bytes, void* stream);
 
-/* Bytes of device workspace dad_compress_rank_sequential needs (0 on invalid sizes). */
+/* Bytes of device workspace dad_compress_rank_sequential and dad_compress_rank_adaptive need (0 on invalid sizes): a few
+ * vectors of N, h_in and h_out floats and, where some number of components is faster on M = A^T D, M itself (4 h_in h_out bytes)
+ * and the slabs dad_reconstruct_grad takes for it.  The query does not know r or the number of applications: a call that
+ * stays on the factors leaves M's part unused. */
 size_t dad_compress_sequential_workspace_bytes(int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt);
 
 /*
@@ -325,7 +328,8 @@ dad_status dad_compress_rank_adaptive(const void* A, const void* D, int64_t N, i
                                       float* sGt, float* sigma, int* effective_rank, int* iterations,
                                       void* workspace, size_t ws_bytes, void* stream);
 
-/* Bytes of device workspace dad_reconstruct_grad needs (may be 0 for small K; 0 on invalid sizes). */
+/* Bytes of device workspace dad_reconstruct_grad needs: 0, or one slab of 4 h_in h_out bytes per chunk of K, between 2 and 64,
+ * where splitting K pays (few output tiles, long K); 0 on invalid sizes. */
 size_t dad_reconstruct_workspace_bytes(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt);
 
 /*

@@ -117,7 +117,7 @@ DensePlan plan_dense(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt
     DensePlan p;
     p.m = plan_compress(h_in, h_out, h_out, r, DAD_F32);
     p.rb = plan_rebuild(N, h_in, h_out, dt);
-    p.off_M = align_up(p.m.total, 256);
+    p.off_M = align_up(p.m.off_Yt + (size_t)r * h_out * 4, 256);  // nothing is orthonormalised: the layout ends with its Yt
     p.off_slabs = p.off_M + align_up((size_t)h_in * h_out * 4, 256);
     p.total = p.off_slabs + align_up(p.rb.total, 256);
     return p;

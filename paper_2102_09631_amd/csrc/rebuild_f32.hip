@@ -192,15 +192,21 @@ static int64_t rf_cost(int64_t groups, int64_t steps, int ks, int64_t splits) {
 }
 
 // Waves of a tile and slabs of one product, by its own sizes alone: a product of a group gives the bits of a single call.
+// Slabs of more than 64 MB have to gain 2 %: for the last percent a tall product would ask for hundreds of megabytes
+// (97792 x 2432 x 874: 196 MB for 23 slabs, 51 MB for 6, 3.53 and 3.65 ms).
 static SplitPlan rf_plan(int64_t K, int64_t h_in, int64_t h_out, int* waves) {
     const int64_t steps = ceil_div(K, rf::BK);
-    int64_t best = INT64_MAX, splits = 1;
+    struct { int64_t cost = INT64_MAX, splits = 1; int ks = 1; } best[2];  // slabs of up to 64 MB, and of more
     for (int ks = 1; ks <= rf::NW; ks *= 2)
         for (int64_t w = 1; w <= 64 && (w == 1 || w * ks * 8 <= steps); ++w) {
             const int64_t slabs = w == 1 ? 0 : 5 + (2 * w + 1) * h_in * h_out / 1000000;  // 4 bytes at 4 TB/s
             const int64_t cost = rf_cost(rf_groups(h_in, h_out, ks), steps, ks, w) + slabs;
-            if (cost < best) best = cost, splits = w, *waves = ks;
+            auto& b = best[w > 1 && w * h_in * h_out * 4 > (int64_t)64 << 20];
+            if (cost < b.cost) b.cost = cost, b.splits = w, b.ks = ks;
         }
+    const auto& b = best[best[1].cost < INT64_MAX && best[1].cost * 50 < best[0].cost * 49];
+    const int64_t splits = b.splits;
+    *waves = b.ks;
     SplitPlan sp;
     sp.chunk = splits == 1 ? K : (int64_t)align_up((size_t)ceil_div(K, splits), rf::BK);
     sp.splits = (int)ceil_div(K, sp.chunk);

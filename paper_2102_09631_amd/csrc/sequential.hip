@@ -229,11 +229,12 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
 // The recurrence is a chain of short launches, and a product with M = A^T Delta is one of them where a product with
 // the factors is two and a slab sum: M is made first wherever dense_wins says so.  768 x 768, N = 4096, bf16, 8
 // components: 624 us on the factors, 444 us on M (of which M 20 us).
-// The workspace begins with the layout of the route taken: the products on the factors (c), or on the gradient (d).
+// The workspace holds the layout of the route taken, products on the factors (c) or on the gradient (d), and behind
+// it the running vector (h_out fp32).
 struct SeqPlan {
     CompressPlan c;
     DensePlan d;
-    size_t off_panel;  // the running vector, h_out fp32
+    size_t off_panel;
     size_t total;
     bool dense;        // some number of components is faster on the gradient: the workspace holds it
 };
@@ -244,12 +245,13 @@ constexpr int64_t SEQ_MANY_PRODUCTS = 64 * 5;
 
 static SeqPlan plan_sequential(int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt) {
     SeqPlan p;
+    const size_t vec = align_up((size_t)h_out * 4, 256);
     p.c = plan_compress(N, h_in, h_out, 1, dt);
     p.d = plan_dense(N, h_in, h_out, 1, dt);
     p.dense = dense_wins(N, h_in, h_out, dt, SEQ_MANY_PRODUCTS);
-    const size_t body = p.dense && p.d.total > p.c.total ? p.d.total : p.c.total;
-    p.off_panel = align_up(body, 256);
-    p.total = p.off_panel + align_up((size_t)h_out * 4, 256);
+    const size_t factors = p.c.off_Yt + vec;  // nothing is orthonormalised: the layout ends with its Yt
+    p.off_panel = p.dense && p.d.total > factors ? p.d.total : factors;
+    p.total = p.off_panel + vec;
     return p;
 }
 

@@ -156,6 +156,20 @@ def test_reconstruct_workspace_is_whole_slabs(lib, dt):
             assert rest == 0 and slabs != 1
 
 
+# more slabs than the time of a product needs are not asked for
+@pytest.mark.parametrize("K,h_in,h_out,slabs", [(97792, 2432, 874, 8), (90119, 7296, 5504, 0), (75465, 6400, 7552, 0), (30000, 784, 1024, 7)])
+def test_fp32_products_ask_for_few_slabs(lib, K, h_in, h_out, slabs):
+    assert lib.dad_reconstruct_workspace_bytes(K, h_in, h_out, dad.DAD_F32) <= slabs * h_in * h_out * 4
+
+
+# the recurrence: the gradient, at most a few slabs of it, and vectors
+@pytest.mark.parametrize("N,h_in,h_out,dt,slabs", [(37191, 4864, 4992, 0, 0), (73540, 8064, 7424, 0, 0), (67940, 3584, 7680, 0, 0),
+                                                   (4096, 768, 768, 1, 4), (2000, 512, 300, 0, 8)])
+def test_sequential_workspace_is_the_gradient_and_vectors(lib, N, h_in, h_out, dt, slabs):
+    need = lib.dad_compress_sequential_workspace_bytes(N, h_in, h_out, dt)
+    assert need <= (1 + slabs) * h_in * h_out * 4 + 4 * (2 * N + 40 * (h_in + h_out)) + (1 << 20)
+
+
 def test_grouped_compress_rejects_bad_arguments_on_host(lib):
     p = 0x1000
     D = dad.CompressDesc
