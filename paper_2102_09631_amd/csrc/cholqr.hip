@@ -283,8 +283,8 @@ template <int JT, bool FINAL, int CAP>
 __global__ __launch_bounds__(FINAL ? QrDims<JT>::NT : 256) void k_qr_apply(JobTable<QrJob, CAP> tb, int r) {
     const QrJob& jb = tb.j[blockIdx.y];
     const int64_t h = jb.h;
-    const int nblocks = FINAL ? qr_blocks<JT>(h) : (int)((h + 63) / 64);
-    if ((int)blockIdx.x >= nblocks) return;
+    constexpr int COLS = FINAL ? QrDims<JT>::COLS : 64;  // of a workgroup
+    if ((int64_t)blockIdx.x * COLS >= h) return;
     const float* Yt = jb.Ysum ? jb.Ysum : jb.Y;
     float* Gt = jb.Gt;
     bf16_t* gt_bf16 = jb.gt_bf16;
@@ -317,6 +317,16 @@ __global__ __launch_bounds__(FINAL ? QrDims<JT>::NT : 256) void k_qr_apply(JobTa
         __shared__ QrShared<JT> sh;
         __shared__ int last_s;
         const bool again = range[0] > 0.0 && !(range[1] <= QR_ONE_ROUND_BOUND);  // uniform over the grid
+        if (!again) {
+            const int64_t c0 = (int64_t)blockIdx.x * COLS + wave * 16;
+            f64x4 g[JT];
+            apply_columns<JT>(ri, Yt, h, r, c0, g);
+            write(g, c0 + li, gt_bf16 != nullptr);
+            return;
+        }
+        // the second round: few workgroups, as one of them adds their Gram partials
+        const int nblocks = qr_blocks<JT>(h);
+        if ((int)blockIdx.x >= nblocks) return;
         f64x4 acc[QrDims<JT>::NBK];
 #pragma unroll
         for (int b = 0; b < QrDims<JT>::NBK; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
@@ -326,8 +336,7 @@ __global__ __launch_bounds__(FINAL ? QrDims<JT>::NT : 256) void k_qr_apply(JobTa
             if (cu >= h) break;
             f64x4 g[JT];
             apply_columns<JT>(ri, Yt, h, r, cu + wave * 16, g);
-            write(g, c, gt_bf16 != nullptr && !again);
-            if (!again) continue;
+            write(g, c, false);
             if (u) __syncthreads();
 #pragma unroll
             for (int b = 0; b < JT; ++b)
@@ -342,7 +351,6 @@ __global__ __launch_bounds__(FINAL ? QrDims<JT>::NT : 256) void k_qr_apply(JobTa
             for (int a = 0; a < JT; ++a) y[a] = *reinterpret_cast<const f32x4*>(&sh.tile[16 * a + li][wave * 16 + 4 * q]);
             gram_add<JT>(acc, y);
         }
-        if (!again) return;
         __syncthreads();
         __threadfence();  // the first result leaves before the ticket
         if (!gram_finish<JT>(sh, acc, jb.part, nblocks, jb.hdr + 16, &last_s)) return;
@@ -379,7 +387,7 @@ static dad_status qr(const QrJob* jobs, int count, int r, bool final, hipStream_
         if (jobs[i].h > h) h = jobs[i].h;
     }
     constexpr int NT = QrDims<JT>::NT;
-    const dim3 grid((unsigned)nb, (unsigned)count);
+    const dim3 grid((unsigned)nb, (unsigned)count), cols((unsigned)ceil_div(h, QrDims<JT>::COLS), (unsigned)count);
     {
         ProfScope prof(KID_GRAM, s);
         launch_jobs<QR_JOBS>(jobs, count, [&](auto tb, auto cap) {
@@ -390,7 +398,7 @@ static dad_status qr(const QrJob* jobs, int count, int r, bool final, hipStream_
     if (final) {
         ProfScope prof(KID_APPLY, s);
         launch_jobs<QR_JOBS>(jobs, count, [&](auto tb, auto cap) {
-            hipLaunchKernelGGL((k_qr_apply<JT, true, decltype(cap)::value>), grid, dim3(NT), 0, s, tb, r);
+            hipLaunchKernelGGL((k_qr_apply<JT, true, decltype(cap)::value>), cols, dim3(NT), 0, s, tb, r);
         });
     } else {
         ProfScope prof(KID_APPLY2, s);
