@@ -94,13 +94,20 @@ def test_backprop_many_rows(gpu, dtype, h, hn):
 
 
 # reductions with fp32 intermediates: every count of 16-row rank blocks less one, whole and plus one; fewer rows
-# than a block; rows and widths that end inside a block; widths around one 16-byte load; row chunks of thin_tn; several
-# row tiles per wave of thin_nn (N >= 8192 and N >= 32768); 64-column blocks in pairs; slabs summed before and by the
-# orthonormalisation
+# than a block; rows and widths that end inside a block; widths around one 16-byte load; row chunks of thin_tn; two
+# row tiles per wave of thin_nn (N > 8160), rows of their own for its waves (N > 16352) and two tiles of them (N > 24544), each at
+# every count of rank blocks; workgroups that share a row of thin_nn (few rows, wide); 64-column blocks in pairs (fp32 and bf16
+# factors of more than 32 MB), with eight waves and with four; slabs summed before and by the orthonormalisation
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,h_in,h_out,r", [(4, 9, 8, 1), (100, 7, 70, 1), (61, 65, 68, 15), (70, 64, 67, 16), (300, 70, 75, 17), (301, 130, 200, 32),
                                             (400, 140, 139, 33), (512, 200, 300, 48), (513, 300, 200, 49), (520, 260, 270, 64),
-                                            (9000, 90, 131, 8), (33000, 40, 52, 5), (6000, 1500, 1400, 20)])
+                                            (9000, 90, 131, 8), (33000, 40, 52, 5), (6000, 1500, 1400, 20),
+                                            (8161, 40, 70, 17), (10000, 100, 65, 40), (12000, 70, 140, 64), (16352, 65, 64, 49),
+                                            (16353, 40, 100, 5), (16400, 129, 70, 20), (17000, 64, 61, 33), (24544, 140, 72, 64),
+                                            (24545, 72, 130, 16), (40001, 100, 40, 17), (50000, 48, 64, 48), (65600, 66, 140, 64),
+                                            (131100, 40, 33, 20), (131100, 65, 130, 40), (9001, 2050, 1900, 7), (9001, 2050, 1900, 40),
+                                            (9001, 1900, 2050, 64), (40, 3000, 5000, 33), (100, 6001, 5003, 64), (260, 4099, 2055, 20),
+                                            (1000, 5120, 1280, 49), (31, 9000, 3000, 16)])
 def test_reduction_edges(gpu, dtype, N, h_in, h_out, r):
     rng = np.random.default_rng([3, N, h_in, h_out, r])
     A = grid(np.maximum(rng.standard_normal((N, h_in)), 0.0), dtype)
