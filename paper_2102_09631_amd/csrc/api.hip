@@ -59,8 +59,8 @@ CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dt
     };
     p.tn_in = tn_split(h_in);
     p.tn_out = tn_split(h_out);
-    p.nn_in = gen_thin_nn_split(N, h_in);
-    p.nn_out = gen_thin_nn_split(N, h_out);
+    p.nn_in = p.direct ? SplitPlan{direct_nn_splits(N, h_in, r, dt), 0} : gen_thin_nn_split(N, h_in);
+    p.nn_out = p.direct ? SplitPlan{direct_nn_splits(N, h_out, r, dt), 0} : gen_thin_nn_split(N, h_out);
     size_t o = 0;
     p.off_flag = o;
     o += 256;
@@ -74,9 +74,10 @@ CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dt
     p.off_part = o;
     size_t part_max = part_in > part_out ? part_in : part_out;
     if (part_floor > part_max) part_max = part_floor;  // a batch of jobs of several widths shares one layout
-    if (!p.dma && !p.direct) {  // column-split slabs of the guarded thin_nn share the region
-        const size_t nn_in = p.nn_in.splits > 1 ? (size_t)p.nn_in.splits * N * r * 4 : 0;
-        const size_t nn_out = p.nn_out.splits > 1 ? (size_t)p.nn_out.splits * N * r * 4 : 0;
+    if (!p.dma) {  // column-split slabs of thin_nn share the region
+        const size_t rows = (size_t)(p.direct ? direct_npad(N) : N);
+        const size_t nn_in = p.nn_in.splits > 1 ? (size_t)p.nn_in.splits * rows * r * 4 : 0;
+        const size_t nn_out = p.nn_out.splits > 1 ? (size_t)p.nn_out.splits * rows * r * 4 : 0;
         if (nn_in > part_max) part_max = nn_in;
         if (nn_out > part_max) part_max = nn_out;
     }
@@ -231,7 +232,7 @@ static dad_status direct_compress(const CompressJob* jobs, int n, dad_dtype dt, 
         for (int i = 0; i < n; ++i) {
             const CompressJob& j = jobs[i];
             t[i] = NnJob{delta ? j.D : j.A, !delta ? j.at<float>(j.p->off_Ut) : first ? j.G0 : j.Gt, j.at<float>(j.p->off_V),
-                         first ? j.hdr() : nullptr, j.N, (int)(delta ? j.h_out : j.h_in)};
+                         j.at<float>(j.p->off_part), first ? j.hdr() : nullptr, j.N, (int)(delta ? j.h_out : j.h_in)};
         }
         int* const c = first ? clear : nullptr;
         first = false;

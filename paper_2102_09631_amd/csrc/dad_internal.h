@@ -244,7 +244,7 @@ struct CompressPlan {
     size_t total;
     SplitPlan tn_in;      // split of  A^T V   (width h_in)
     SplitPlan tn_out;     // split of  Delta^T W (width h_out)
-    SplitPlan nn_in;      // column split of  A U  (guarded kernel only; chunk = columns)
+    SplitPlan nn_in;      // column split of  A U  (chunk = columns, guarded kernel only)
     SplitPlan nn_out;     // column split of  Delta G
 };
 
@@ -323,10 +323,11 @@ struct alignas(64) NnJob {  // Vt (r x Npad) <- (X Pt^T)^T
     const void* X;
     const float* Pt;
     float* Vt;
+    float* slabs;   // direct_nn_splits(...) * r * Npad floats where that is more than one
     int* zero_hdr;  // a 256-byte workspace header the launch clears on the side, or null
     int64_t N;
     int h;
-    int ks, wg;  // set by direct_nn: waves that share a row, workgroups
+    int ks, cs, wg;  // set by direct_nn: waves and workgroups that share a row, workgroups
 };
 struct alignas(64) TnJob {  // out (r x h), or `splits` slabs of it, <- Vt X
     const void* X;
@@ -339,6 +340,7 @@ dad_status direct_nn(const NnJob* jobs, int count, int r, dad_dtype dt, hipStrea
                      int* clear = nullptr);
 dad_status direct_tn(const TnJob* jobs, int count, int r, dad_dtype dt, hipStream_t s, const int* skip = nullptr);
 int64_t direct_npad(int64_t N);
+int direct_nn_splits(int64_t N, int64_t h, int r, dad_dtype dt);  // workgroups that share a row
 bool direct_ok(int64_t h_in, int64_t h_out, dad_dtype dt);
 SplitPlan direct_tn_split(int64_t N, int64_t h, int r, dad_dtype dt);
 
