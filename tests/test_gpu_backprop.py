@@ -37,11 +37,12 @@ def to_dev(x, dtype, dev):
     ("f32", 37, 50, 23, "tanh"),          # everything ragged
     ("f32", 1, 9, 5, "sigmoid"),          # one sample
     ("f32", 130, 64, 200, "relu"),
-    ("bf16", 77, 136, 72, "relu"),        # guarded kernel, bf16
+    # 64- and 128-tiles: the kernel for any shape takes small whole-tile products too (they are too few for 256-tiles)
+    ("bf16", 77, 136, 72, "relu"),
     ("bf16", 33, 65, 31, "identity"),     # odd widths
-    ("bf16", 256, 256, 32, "relu"),       # tile-aligned but h_next not a multiple of 64: guarded kernel
-    ("bf16", 256, 256, 64, "relu"),       # one MFMA tile, one stage
-    ("bf16", 512, 768, 192, "tanh"),      # 2 x 3 tiles, 3 stages
+    ("bf16", 256, 256, 32, "relu"),       # half a stage
+    ("bf16", 256, 256, 64, "relu"),       # one stage
+    ("bf16", 512, 768, 192, "tanh"),      # 3 stages
     ("bf16", 768, 512, 1024, "sigmoid"),  # 16 stages
     ("bf16", 256, 1024, 320, "identity"), # 5 stages (odd count)
     ("bf16", 512, 256, 3072, "relu"),     # long contraction
@@ -57,6 +58,48 @@ def test_backprop_delta_matches_oracle(gpu, dtype, N, h, hn, act):
     assert err <= TOL[dtype]
     if act == "relu":      # the mask is exact: no value leaks where Z <= 0
         assert np.all(got[Z <= 0] == 0)
+
+
+# 256-tiles: enough of them to fill the chip in whole rounds, one stage, an odd and an even count of a few, and many; every
+# activation.  Every row is checked: against fp64 on the device, where 4096 x 4096 x 1024 takes milliseconds
+@pytest.mark.parametrize("act", ["identity", "relu", "tanh", "sigmoid"])
+@pytest.mark.parametrize("N,h,hn", [(4096, 4096, 64), (4096, 4096, 128), (8192, 4096, 192), (4096, 4096, 320), (4096, 4096, 1024)])
+def test_backprop_delta_on_256_tiles(gpu, N, h, hn, act):
+    gen = torch.Generator(device=gpu)
+    gen.manual_seed(N + hn)
+    Dn = (torch.randn(N, hn, generator=gen, device=gpu) * 1e-2).to(torch.bfloat16)
+    Wn = (torch.randn(h, hn, generator=gen, device=gpu) / hn ** 0.5).to(torch.bfloat16)
+    Z = torch.randn(N, h, generator=gen, device=gpu).to(torch.bfloat16)
+    dad.profile_enable(True)
+    dad.profile_reset()
+    try:
+        got = dad.backprop_delta(Dn, Wn, Z, act).double()
+        assert list(dad.profile_read()) == ["k_backprop_bf16"]
+    finally:
+        dad.profile_enable(False)
+    z = Z.double()
+    dphi = {"identity": torch.ones_like, "relu": lambda x: (x > 0).double(), "tanh": lambda x: 1 - torch.tanh(x) ** 2,
+            "sigmoid": lambda x: torch.sigmoid(x) * (1 - torch.sigmoid(x))}[act](z)
+    ref = (Dn.double() @ Wn.double().T) * dphi
+    # one rounding to bf16 (2^-9 of each value at most, 2^-8 allowed) of a sum of hn products in fp32
+    assert torch.all((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-6 * ref.abs().max())
+
+
+# what the hardware's exponential and reciprocal leave of a result rounded to bf16: with an exact contraction all but
+# 3.4e-5 of the values are the correctly rounded ones, as with the library's functions and a division (3.4e-5)
+@pytest.mark.parametrize("act", ["tanh", "sigmoid"])
+@pytest.mark.parametrize("N,h", [(2001, 1000), (4096, 4096)])
+def test_backprop_delta_rounds_correctly(gpu, N, h, act):
+    gen = torch.Generator(device=gpu)
+    gen.manual_seed(7)
+    Z = (3 * torch.randn(N, h, generator=gen, device=gpu)).to(torch.bfloat16)
+    Dn, Wn = torch.zeros(N, 64, device=gpu, dtype=torch.bfloat16), torch.zeros(h, 64, device=gpu, dtype=torch.bfloat16)
+    Dn[:, 0] = torch.randn(N, generator=gen, device=gpu).to(torch.bfloat16)
+    Wn[:, 0] = 1
+    z = Z.double()
+    dphi = 1 / torch.cosh(z) ** 2 if act == "tanh" else torch.sigmoid(z) * torch.sigmoid(-z)
+    off = dad.backprop_delta(Dn, Wn, Z, act) != (Dn[:, :1].double() * dphi).to(torch.bfloat16)
+    assert off.double().mean().item() <= 6e-5
 
 
 def test_backprop_delta_writes_sites_in_place_in_the_stacked_buffer(gpu):
