@@ -232,7 +232,9 @@ constexpr int DMA_LOADS = 4;  // 16-byte loads per thread per stage, for both ti
 // span blocks, and the operand pointers jump at a block's end.
 // TAIL: K is not a multiple of BK.  The rows of the last stage beyond K repeat row K - 1 and are zeroed in LDS before they are
 // multiplied.  Whole K has an instance without that code: in the one loop of both it cost every product 4 to 7 %
-// (65536 x 1024 x 4096: 484 -> 504 us, zero factors 350 -> 368 us; 242 -> 250 VGPRs, 32 -> 52 SGPRs).
+// (65536 x 1024 x 4096: 484 -> 504 us, zero factors 350 -> 368 us; 242 -> 250 VGPRs, 32 -> 52 SGPRs).  Row blocks are whole
+// stages, but their one instance has the zeroing (never entered): the compiler's schedule with it is the better one there
+// (16 blocks of 16384 x 1280 x 5120: 2926 us with it, 2972 to 3008 without; smaller products equal).
 // With 128-tiles such a K also adds every 256 rows to a second accumulator, as k_rebuild_bf16 does and for its reason
 // (3077 x 1152 x 2176, error against fp64: 2.7e-7 with one running sum over a chunk, 0.97e-7 folded, fp32 FMA kernel before
 // 1.4e-7; 20011 x 1152 x 2176: 121 -> 129 us, FMA kernel 1470 us); 256-tiles have no registers for it.
@@ -248,7 +250,7 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
     constexpr int CPR = ROWB / 16;                         // 16-byte chunks per row
     constexpr int RPI = 64 / CPR;                          // tile rows covered by one load of a wave
     static_assert(rb::BK == 2 * RPI * WAVES, "two loads per wave and operand cover a stage");
-    static_assert(!TAIL || std::is_pointer<SRC>::value, "row blocks are whole stages");
+    constexpr bool RAGGED = TAIL && std::is_pointer<SRC>::value;  // K may end inside a stage
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -301,7 +303,7 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
             }
             row_next += rb::BK;
         }
-        if constexpr (TAIL) {
+        if constexpr (RAGGED) {
             if (row_next + rb::BK > kend) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
@@ -334,7 +336,7 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-    constexpr bool FOLD = TAIL && T == 128;
+    constexpr bool FOLD = RAGGED && T == 128;
     f32x16 sum[FOLD ? FA : 1][FOLD ? FB : 1];
     auto fold = [&](bool first) {
         if constexpr (FOLD) {
@@ -563,7 +565,7 @@ static dad_status launch_rebuild_dma(const void* L, const void* R, const RowBloc
     const dim3 grid((unsigned)total), block(64 * WM * WN);
     const bf16_t *l = static_cast<const bf16_t*>(L), *r = static_cast<const bf16_t*>(R);
     if (lb)
-        hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, false>), grid, block, lds, s, *lb, *rbk, dst, K, (int)h_in,
+        hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, true>), grid, block, lds, s, *lb, *rbk, dst, K, (int)h_in,
                            (int)h_out, sp.chunk, tm, tn, total);
     else if (K % rb::BK == 0)
         hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, false>), grid, block, lds, s, l, r, dst, K, (int)h_in,
@@ -692,7 +694,7 @@ dad_status launch_rebuild_group(int n, const void* const* L, const void* const* 
 template <int T, int WM, int WN>
 static dad_status prepare_dma() {
     constexpr int lds = rb::DMA_STAGES * 2 * rb::BK * T * 2;
-    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, false>), lds));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, true>), lds));
     DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, false>), lds));
     DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, true>), lds));
     return DAD_OK;
