@@ -83,7 +83,7 @@ def kernel_model(name, N, h_in, h_out, r, es, which, bf16=True):
     `which` says which factor the launch streams ("in" = A, "out" = Delta).
     """
     h = h_in if which == "in" else h_out
-    if name in ("k_thin_nn_bf16", "k_thin_tn_bf16", "k_thin_nn_direct", "k_thin_tn_direct", "k_thin_nn", "k_thin_tn"):
+    if name in ("k_thin_nn_bf16", "k_thin_tn_bf16", "k_thin_nn_direct", "k_thin_nn_tall", "k_thin_tn_direct", "k_thin_nn", "k_thin_tn"):
         return "hbm", float(N) * h * es
     if name in ("k_rebuild_bf16", "k_rebuild_bf16_dma"):
         return "mfma", 2.0 * N * h_in * h_out
@@ -263,7 +263,7 @@ def two_level(args, w, dad, W, torch, np, dev):
     for name in kern:
         tot = 0.0
         for _, hi, ho in layers:
-            if name in ("k_thin_nn_bf16", "k_thin_nn_direct", "k_thin_nn"):
+            if name in ("k_thin_nn_bf16", "k_thin_nn_direct", "k_thin_nn_tall", "k_thin_nn"):
                 parts = [(ho, n_iter + 1), (hi, n_iter)]
             elif name in ("k_thin_tn_bf16", "k_thin_tn_direct", "k_thin_tn"):
                 parts = [(hi, n_iter + 1), (ho, n_iter)]
@@ -822,7 +822,7 @@ def one_level(args, w, steps, warmup, dad, W, torch, np, dev, cpu_budget_s, yard
     for name in kern:
         tot, bound = 0.0, None
         for _, hi, ho in layers:
-            if name in ("k_thin_nn_bf16", "k_thin_nn_direct", "k_thin_nn"):
+            if name in ("k_thin_nn_bf16", "k_thin_nn_direct", "k_thin_nn_tall", "k_thin_nn"):
                 parts = [("out", n_iter + 1), ("in", n_iter)]
             elif name in ("k_thin_tn_bf16", "k_thin_tn_direct", "k_thin_tn"):
                 parts = [("in", n_iter + 1), ("out", n_iter)]

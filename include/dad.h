@@ -129,13 +129,11 @@ size_t dad_compress_workspace_bytes(int64_t N, int64_t h_in, int64_t h_out, int 
  *   Gt        device out, r x h_out fp32: rows orthonormal
  *   workspace device, ws_bytes >= dad_compress_workspace_bytes(...)
  * Outputs have the factor layout (one row per component), so S such pairs can
- * be stacked and compressed again (Algorithm 1).  For dt = DAD_BF16 on shapes
- * the MFMA kernels serve (N >= 256, widths multiples of 128, r a multiple of
- * 8) the two N x r intermediates travel as bf16 between contractions: Delta G
- * rounded once, A U as two bf16 terms (value and rounding remainder, 16
- * significand bits: activations with a non-zero mean make one rounding of it
- * too coarse); with N a multiple of 256 the h x r panels enter the next
- * contraction rounded to bf16 as well.  On other shapes and for fp32 factors
+ * be stacked and compressed again (Algorithm 1).  For dt = DAD_BF16 on shapes of whole tiles (N a
+ * multiple of 256, widths multiples of 128, r in {16, 32, 64}) the two N x r intermediates travel as
+ * bf16 between contractions: Delta G rounded once, A U as two bf16 terms (value and rounding remainder,
+ * 16 significand bits: activations with a non-zero mean make one rounding of it too coarse), and the h x r
+ * panels enter the next contraction rounded to bf16 as well.  On other shapes and for fp32 factors
  * the intermediates are fp32.  The panels themselves, the outputs and
  * everything r x r stay fp32 (Gram matrix and r x r factorisation in fp64).
  * If the iterate loses rank (r > rank(M)) the outputs are unspecified and
@@ -353,7 +351,7 @@ dad_status dad_reconstruct_grad(const void* L, const void* R, int64_t K, int64_t
  *             when that is 0)
  * fp32 jobs (the rank-r pairs, K = r) share launches, up to 32 jobs per launch: one layer's rank-r
  * gradient is a few MB and launch bound on its own; their results are bit-identical to n separate
- * dad_reconstruct_grad calls.  Runs of consecutive bf16 jobs with K a multiple of 32 and widths
+ * dad_reconstruct_grad calls.  Runs of consecutive bf16 jobs with K >= 256 and widths
  * multiples of 256 (the full gradients of a block's layers) share launches too, up to 16 per launch,
  * with ONE number of K chunks chosen for the run as a whole: gradients with few output tiles then
  * fill the chip together instead of each splitting K finely.  Such a job is summed in another chunk

@@ -106,6 +106,8 @@ __device__ __forceinline__ bool gram_finish(QrShared<JT>& sh, const f64x4 (&acc)
         double* mine = part + (int64_t)blockIdx.x * NBK * 256;
         // The partials are exchanged with agent-scope accesses, which go past the caches that are not shared
         // by the XCDs: no cache has to be written back before the ticket or invalidated after it (1-2 us each).
+        // The accesses are relaxed, which orders nothing by the language; on this chip a store that s_waitcnt has seen
+        // arrive is visible to every later access of this scope, and the loads are issued after the ticket's value is known.
         if (grp == 0)
 #pragma unroll
             for (int b = 0; b < NBK; ++b) __hip_atomic_store(mine + b * 256 + t, sum[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -145,15 +147,15 @@ __device__ __forceinline__ bool gram_finish(QrShared<JT>& sh, const f64x4 (&acc)
     }
     __syncthreads();
     if (grp == 0) {
-    int blk = 0;
+        int blk = 0;
 #pragma unroll
-    for (int a = 0; a < JT; ++a)
+        for (int a = 0; a < JT; ++a)
 #pragma unroll
-        for (int b = a; b < JT; ++b, ++blk) {
-            const int i = 16 * a + 4 * wave + (lane >> 4), j = 16 * b + (lane & 15);
-            sh.f.S[i][j] = sum[blk];
-            if (a != b) sh.f.S[j][i] = sum[blk];
-        }
+            for (int b = a; b < JT; ++b, ++blk) {
+                const int i = 16 * a + 4 * wave + (lane >> 4), j = 16 * b + (lane & 15);
+                sh.f.S[i][j] = sum[blk];
+                if (a != b) sh.f.S[j][i] = sum[blk];
+            }
     }
     __syncthreads();
     return true;

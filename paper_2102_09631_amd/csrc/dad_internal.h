@@ -200,7 +200,7 @@ enum KernelId {
     KID_STACK = 0, KID_THIN_NN_BF16, KID_THIN_TN_BF16, KID_REDUCE, KID_GRAM, KID_APPLY, KID_APPLY2, KID_REBUILD_BF16,
     KID_THIN_NN, KID_THIN_TN, KID_REBUILD, KID_PANEL_INIT, KID_REBUILD_BF16_DMA, KID_BACKPROP_BF16, KID_BACKPROP,
     KID_GRAM_TILES, KID_GRAM_GATHER, KID_NS_STEP, KID_NS_PROJECT, KID_REBUILD_F32, KID_REDUCE_WIDE, KID_SEQ_VECTOR,
-    KID_DIRECT_NN, KID_DIRECT_TN,
+    KID_DIRECT_NN, KID_DIRECT_TN, KID_DIRECT_NN_TALL,
     KID_COUNT
 };
 
@@ -235,8 +235,8 @@ struct CompressPlan {
     size_t off_part;      // split partials, fp32
     size_t off_Ut;        // r x h_in fp32
     size_t off_Yt;        // r x h_out fp32
-    size_t off_gram;      // gram partials, fp64
-    size_t off_rinv;      // two DAD_MAX_RANK^2 fp64 inverse factors
+    size_t off_gram;      // gram partials, fp64; in the place of V where they fit
+    size_t off_rinv;      // two DAD_MAX_RANK^2 fp64 inverse factors, behind them
     size_t off_Gb;        // bf16 copy of the current right block, RP x h_out (direct-to-LDS path only)
     size_t off_Ub;        // bf16 copy of U, RP x h_in
     bool dma;             // whole-tile bf16 kernels that load straight into LDS (panels and N x r in bf16)
@@ -254,9 +254,9 @@ CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dt
 struct RebuildPlan {
     SplitPlan split;
     size_t total;  // bytes of partials (0 when splits == 1)
-    bool fast;     // bf16 MFMA kernels
-    bool f32;      // fp32 MFMA kernel (every fp32 shape)
-    int tile;      // output tile edge of the bf16 MFMA kernel (256 or 128)
+    bool fast;     // bf16 MFMA kernels (all but operands shorter than one 16-byte load)
+    bool f32;      // fp32 MFMA kernel (widths of at least 4; else the guarded kernel)
+    int tile;      // output tile edge of the direct-to-LDS bf16 kernel (256 or 128); 0: the register-staged kernel
 };
 
 RebuildPlan plan_rebuild(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt);

@@ -157,7 +157,7 @@ def test_orthonormalisation_of_ill_conditioned_iterates(gpu, h, r, log_cond):
     assert O.rel_fro(g.T @ g, Qf @ Qf.T) <= 1e-6 + 4 * np.finfo(np.float32).eps * 10.0 ** log_cond
 
 
-# fp32 gradients: K around a 16-row step and around what two, four and eight waves per tile need, tiles less one, whole
+# fp32 gradients: K around a 16-row step and around what two and four waves per tile need, tiles less one, whole
 # and plus one column, one and several tiles per workgroup, slabs (long K, few tiles), widths below one 16-byte load
 # long fp32 sums: rounds of 192 rows (48 instructions of four products, 1.4e-7) added to the rest (K / 192 roundings); one
 # running sum over a wave's share of K is at 5.7e-7
