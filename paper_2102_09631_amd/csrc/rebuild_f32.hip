@@ -45,8 +45,11 @@ struct alignas(64) RebuildF32Job {
 __host__ __device__ inline int rf_block_m(int ks) { return ks == 1 ? 2 : 1; }
 __host__ __device__ inline int rf_block_n(int ks) { return rf::NW / ks / rf_block_m(ks); }
 
-template <int CAP>
-__global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<RebuildF32Job, CAP> tb) {
+// SHORT: less than eight steps (K = r, mostly).  What counts is that the loads, products and stores of several waves of a SIMD
+// overlap, so the instance keeps two steps and no second accumulator: 163 registers, three waves to a SIMD.  32 products of
+// 1024 x 1024 to 1024 x 4096, K = 32, in one launch: 160 us in the instance for a long K, 129 us so (LDS-staged kernel before 113).
+template <int CAP, bool SHORT>
+__global__ __launch_bounds__(64 * rf::NW, SHORT ? 3 : 1) void k_rebuild_f32_mfma(JobTable<RebuildF32Job, CAP> tb) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     f32x4 (*red)[4][64] = reinterpret_cast<f32x4 (*)[4][64]>(smem);
     const RebuildF32Job& jb = tb.j[blockIdx.y];
@@ -71,7 +74,8 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
     const int nb = (int)((kend - kbeg + rf::BK - 1) / rf::BK);
     const bool idle = p0 >= h_in || q0 >= h_out;  // a tile of the block outside the matrix
 
-    f32x4 x[3][4], y[3][4];
+    constexpr int SETS = SHORT ? 2 : 3;
+    f32x4 x[SETS][4], y[SETS][4];
     auto load = [&](auto set_c, int b) {
         constexpr int set = decltype(set_c)::value;
         const int64_t k0 = kbeg + (int64_t)b * rf::BK;
@@ -90,19 +94,24 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
     // 5.7e-7 with one sum, 2.5e-7 so, the LDS-staged kernel before 4.7e-7; 4096 x 2048 x 2048: 274 -> 283 us, 384 rows 278 us
     // but 2560 x 403 x 977 then at 2.3e-7, before 2.1e-7).
     constexpr int FOLD = 4;
-    f32x4 acc[4][4], sum[4][4];
+    f32x4 acc[4][4], more[SHORT ? 1 : 4][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = sum[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 4; ++b) {
+            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (!SHORT) more[a][b] = acc[a][b];
+        }
     auto fold = [&]() {
+        if constexpr (!SHORT) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+            for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                sum[a][b] += acc[a][b];
-                acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+                for (int b = 0; b < 4; ++b) {
+                    more[a][b] += acc[a][b];
+                    acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
     };
     auto compute = [&](auto set_c, int b) {
         constexpr int set = decltype(set_c)::value;
@@ -124,8 +133,22 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
     // leave the next step in flight
     const std::integral_constant<int, 0> s0;
     const std::integral_constant<int, 1> s1;
-    const std::integral_constant<int, 2> s2;
-    if (!idle && kp < nb) {
+    const std::integral_constant<int, SETS - 1> s2;
+    if (SHORT) {
+        if (!idle && kp < nb) {
+            load(s0, kp);
+            for (int b = kp; b < nb; b += 2 * ks) {
+                if (b + ks < nb) load(s1, b + ks);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(s0, b);
+                __builtin_amdgcn_sched_barrier(0);
+                if (b + 2 * ks < nb) load(s0, b + 2 * ks);
+                __builtin_amdgcn_sched_barrier(0);
+                if (b + ks < nb) compute(s1, b + ks);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else if (!idle && kp < nb) {
         auto at_most = [&](int b) { return b < nb ? b : nb - 1; };
         load(s0, kp);
         load(s1, at_most(kp + ks));
@@ -151,6 +174,10 @@ __global__ __launch_bounds__(64 * rf::NW) void k_rebuild_f32_mfma(JobTable<Rebui
     }
 
     fold();
+    f32x4 (&sum)[4][4] = [&]() -> f32x4 (&)[4][4] {
+        if constexpr (SHORT) return acc;
+        else return more;
+    }();
 
     // sum[a][e][v]: row p0 + 16 q + 4 v + a, column q0 + 4 c + e.  A lane's row of a tile that was moved back:
     // its operand columns are pc .. pc + 3, i.e. rows indexed by the lane that holds them.
@@ -258,9 +285,12 @@ dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R,
         if (nj) {
             ProfScope prof(KID_REBUILD_F32, s);
             // a short contraction is all first loads and stores: those overlap between workgroups of a compute unit
-            const int lds = longest >= 8 ? CU_LDS : rf::NW * 4 * 64 * 16;
+            const dim3 grid((unsigned)most, (unsigned)nj), block(64 * rf::NW);
             const auto launch = [&](auto tb, auto cap) {
-                hipLaunchKernelGGL(k_rebuild_f32_mfma<decltype(cap)::value>, dim3((unsigned)most, (unsigned)nj), dim3(64 * rf::NW), lds, s, tb);
+                if (longest >= 8)
+                    hipLaunchKernelGGL((k_rebuild_f32_mfma<decltype(cap)::value, false>), grid, block, CU_LDS, s, tb);
+                else
+                    hipLaunchKernelGGL((k_rebuild_f32_mfma<decltype(cap)::value, true>), grid, block, rf::NW * 4 * 64 * 16, s, tb);
             };
             if (nj <= 4)
                 launch_jobs<4>(jobs, nj, launch);
@@ -277,9 +307,9 @@ dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R,
 }
 
 dad_status rebuild_f32_prepare_device() {
-    DAD_HIP_TRY(set_max_lds(k_rebuild_f32_mfma<1>, CU_LDS));
-    DAD_HIP_TRY(set_max_lds(k_rebuild_f32_mfma<4>, CU_LDS));
-    DAD_HIP_TRY(set_max_lds(k_rebuild_f32_mfma<rf::MAX_JOBS>, CU_LDS));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<1, false>), CU_LDS));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<4, false>), CU_LDS));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<rf::MAX_JOBS, false>), CU_LDS));
     return DAD_OK;
 }
 

@@ -51,6 +51,20 @@ def test_grouped_rebuild_with_split_contraction_and_many_jobs(gpu):
         _check_against_oracle(b, L, R, 1e-5)
 
 
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65, 96, 112, 113, 127, 128, 129])
+def test_grouped_rank_rebuild_short_and_long(gpu, K):
+    """Around every step of 16 rows up to where the kernel for short sums ends: alone, beside another short one, and
+    beside a long one (whose launch both then take)."""
+    short, other, long = _pair(K, 200, 333, 40 + K, gpu), _pair(5, 70, 64, 41, gpu), _pair(500, 96, 80, 42, gpu)
+    alone = dad.reconstruct_grad(*short)
+    _check_against_oracle(alone, *short, 1e-6)
+    for pairs in ([short, other], [long, short]):
+        for (L, R), G in zip(pairs, dad.reconstruct_grad_grouped(pairs)):
+            _check_against_oracle(G, L, R, 1e-6)
+            if L is short[0]:
+                assert torch.equal(G, alone)
+
+
 def test_grouped_rebuild_bf16_whole_and_ragged_rows(gpu):
     """Runs of whole 256-tiles that share a launch: all of whole K stages, and with a ragged K among them."""
     whole, ragged = _pair(2048, 256, 512, 21, gpu, torch.bfloat16), _pair(2077, 512, 256, 22, gpu, torch.bfloat16)
