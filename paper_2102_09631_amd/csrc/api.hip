@@ -52,20 +52,30 @@ CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dt
     CompressPlan p;
     p.dma = thin_dma_ok(N, h_in, h_out, r, dt);
     p.direct = !p.dma && direct_ok(h_in, h_out, dt);
+    const size_t bytes_V = align_up((size_t)(p.direct ? direct_npad(N) : N) * r * 4, 256);  // fp32, or two bf16 planes
+    const size_t bytes_U = align_up((size_t)r * h_in * 4, 256), bytes_Y = align_up((size_t)r * h_out * 4, 256);
+    // The orthonormalisation's partials and factors take the place of V where they fit: V is not read again before the
+    // next thin_nn writes it.
+    const size_t gram = align_up(qr_part_bytes(h_out, r), 256), rinv = 2 * DAD_MAX_RANK * DAD_MAX_RANK * 8;
+    const bool in_v = gram + rinv <= (size_t)N * r * 4;
+    // A reduction that fits the static scratch without slabs takes no more of them than fit with it (the direct kernels' row
+    // splits are free): dad_compress_rank_noalloc, whose bits are those of the call with a workspace, then refuses none.
+    const size_t fixed = 256 + bytes_V + bytes_U + bytes_Y + (in_v ? 0 : gram + rinv);
+    const size_t slabs = fixed <= DAD_STATIC_SCRATCH_BYTES ? (DAD_STATIC_SCRATCH_BYTES - fixed) / 256 * 256 : SIZE_MAX;
     auto tn_split = [&](int64_t h) {
         if (p.dma) return thin_tn_split(N, h, r);
-        if (p.direct) return direct_tn_split(N, h, r, dt);
+        if (p.direct) return direct_tn_split(N, h, r, dt, slabs);
         return split_rows(N, ceil_div(h, 64), 1024, 32, 32);
     };
     p.tn_in = tn_split(h_in);
     p.tn_out = tn_split(h_out);
-    p.nn_in = p.direct ? SplitPlan{direct_nn_splits(N, h_in, r, dt), 0} : gen_thin_nn_split(N, h_in);
-    p.nn_out = p.direct ? SplitPlan{direct_nn_splits(N, h_out, r, dt), 0} : gen_thin_nn_split(N, h_out);
+    p.nn_in = p.direct ? SplitPlan{direct_nn_splits(N, h_in, r, dt, slabs), 0} : gen_thin_nn_split(N, h_in);
+    p.nn_out = p.direct ? SplitPlan{direct_nn_splits(N, h_out, r, dt, slabs), 0} : gen_thin_nn_split(N, h_out);
     size_t o = 0;
     p.off_flag = o;
     o += 256;
     p.off_V = o;
-    o += align_up((size_t)(p.direct ? direct_npad(N) : N) * r * 4, 256);  // fp32, or two bf16 planes
+    o += bytes_V;
     size_t part_in = (size_t)p.tn_in.splits * r * h_in * 4, part_out = (size_t)p.tn_out.splits * r * h_out * 4;
     if (p.direct) {  // one chunk is written straight to its destination
         if (p.tn_in.splits == 1) part_in = 0;
@@ -83,13 +93,9 @@ CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dt
     }
     o += align_up(part_max, 256);
     p.off_Ut = o;
-    o += align_up((size_t)r * h_in * 4, 256);
+    o += bytes_U;
     p.off_Yt = o;
-    o += align_up((size_t)r * h_out * 4, 256);
-    // The orthonormalisation's partials and factors take the place of V where they fit: V is not read again before the
-    // next thin_nn writes it.
-    const size_t gram = align_up(qr_part_bytes(h_out, r), 256), rinv = 2 * DAD_MAX_RANK * DAD_MAX_RANK * 8;
-    const bool in_v = gram + rinv <= (size_t)N * r * 4;
+    o += bytes_Y;
     p.off_gram = in_v ? p.off_V : o;
     p.off_rinv = p.off_gram + gram;
     if (!in_v) o += gram + rinv;
@@ -232,7 +238,7 @@ static dad_status direct_compress(const CompressJob* jobs, int n, dad_dtype dt, 
         for (int i = 0; i < n; ++i) {
             const CompressJob& j = jobs[i];
             t[i] = NnJob{delta ? j.D : j.A, !delta ? j.at<float>(j.p->off_Ut) : first ? j.G0 : j.Gt, j.at<float>(j.p->off_V),
-                         j.at<float>(j.p->off_part), first ? j.hdr() : nullptr, j.N, (int)(delta ? j.h_out : j.h_in)};
+                         j.at<float>(j.p->off_part), first ? j.hdr() : nullptr, j.N, (int)(delta ? j.h_out : j.h_in), (delta ? j.p->nn_out : j.p->nn_in).splits};
         }
         int* const c = first ? clear : nullptr;
         first = false;

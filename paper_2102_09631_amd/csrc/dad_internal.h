@@ -323,11 +323,12 @@ struct alignas(64) NnJob {  // Vt (r x Npad) <- (X Pt^T)^T
     const void* X;
     const float* Pt;
     float* Vt;
-    float* slabs;   // direct_nn_splits(...) * r * Npad floats where that is more than one
+    float* slabs;   // cs * r * Npad floats, cs > 1
     int* zero_hdr;  // a 256-byte workspace header the launch clears on the side, or null
     int64_t N;
     int h;
-    int ks, cs, wg;  // set by direct_nn: waves and workgroups that share a row, workgroups
+    int cs;      // workgroups that share a row (direct_nn_splits)
+    int ks, wg;  // set by direct_nn: waves of a workgroup that share a row, workgroups
 };
 struct alignas(64) TnJob {  // out (r x h), or `splits` slabs of it, <- Vt X
     const void* X;
@@ -340,9 +341,10 @@ dad_status direct_nn(const NnJob* jobs, int count, int r, dad_dtype dt, hipStrea
                      int* clear = nullptr);
 dad_status direct_tn(const TnJob* jobs, int count, int r, dad_dtype dt, hipStream_t s, const int* skip = nullptr);
 int64_t direct_npad(int64_t N);
-int direct_nn_splits(int64_t N, int64_t h, int r, dad_dtype dt);  // workgroups that share a row
+// slab_bytes (here and below): most bytes of slabs; one chunk leaves none.
+int direct_nn_splits(int64_t N, int64_t h, int r, dad_dtype dt, size_t slab_bytes);
 bool direct_ok(int64_t h_in, int64_t h_out, dad_dtype dt);
-SplitPlan direct_tn_split(int64_t N, int64_t h, int r, dad_dtype dt);
+SplitPlan direct_tn_split(int64_t N, int64_t h, int r, dad_dtype dt, size_t slab_bytes);
 
 dad_status launch_rebuild(const void* L, const void* R, int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt,
                           float* G, float* partials, const RebuildPlan& plan, hipStream_t s);

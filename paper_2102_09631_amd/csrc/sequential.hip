@@ -299,7 +299,7 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
     const dad_dtype xt = dense ? DAD_F32 : dt;
     auto nn = [&](const void* X, const float* P, int64_t h, SplitPlan sp, const int* skip) {
         if (!c.direct) return gen_thin_nn(X, P, V, part, sp, rows, h, 1, xt, nullptr, s, skip);
-        const NnJob j = {X, P, static_cast<float*>(V), part, nullptr, rows, (int)h};
+        const NnJob j = {X, P, static_cast<float*>(V), part, nullptr, rows, (int)h, sp.splits};
         return direct_nn(&j, 1, 1, xt, s, skip);
     };
     auto tn = [&](const void* X, float* out, int64_t h, SplitPlan sp, const int* skip) {

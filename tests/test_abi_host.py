@@ -95,7 +95,9 @@ def test_noalloc_rejects_bad_arguments_and_oversize_on_host(lib):
 # V alone is 19 to 30 MB of the 32 MB: the row splits of thin_tn and the orthonormalisation have to do with the rest
 @pytest.mark.parametrize("N,h_in,h_out,r,dt", [(78438, 6016, 128, 64, 1), (89728, 4992, 128, 64, 1), (162560, 37, 6144, 32, 0),
                                                (161792, 128, 5504, 33, 0), (232409, 128, 7680, 24, 1), (107732, 640, 7040, 48, 1),
-                                               (83112, 5760, 3712, 64, 1), (149508, 768, 7552, 33, 0)])
+                                               (83112, 5760, 3712, 64, 1), (149508, 768, 7552, 33, 0),
+                                               (99796, 256, 1536, 64, 1), (122719, 128, 128, 64, 0), (230322, 159, 484, 33, 0),
+                                               (104128, 7680, 384, 64, 1), (77071, 26240, 512, 64, 1)])
 def test_static_scratch_holds_tall_reductions(lib, N, h_in, h_out, r, dt):
     assert 0 < lib.dad_compress_workspace_bytes(N, h_in, h_out, r, dt) <= dad.DAD_STATIC_SCRATCH_BYTES
 
