@@ -48,7 +48,9 @@ __host__ __device__ inline int rf_block_n(int ks) { return rf::NW / ks / rf_bloc
 // SHORT: less than eight steps (K = r, mostly).  What counts is that the loads, products and stores of several waves of a SIMD
 // overlap, so the instance keeps two steps and no second accumulator: 163 registers, three waves to a SIMD.  32 products of
 // 1024 x 1024 to 1024 x 4096, K = 32, in one launch: 160 us in the instance for a long K, 129 us so (LDS-staged kernel before 113).
-template <int CAP, bool SHORT>
+// NT: non-temporal stores, for a launch whose results are larger than the Infinity Cache holds: 103 us there.  Smaller ones
+// are left in the caches for whoever reads the gradients next.
+template <int CAP, bool SHORT, bool NT>
 __global__ __launch_bounds__(64 * rf::NW, SHORT ? 3 : 1) void k_rebuild_f32_mfma(JobTable<RebuildF32Job, CAP> tb) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     f32x4 (*red)[4][64] = reinterpret_cast<f32x4 (*)[4][64]>(smem);
@@ -185,7 +187,11 @@ __global__ __launch_bounds__(64 * rf::NW, SHORT ? 3 : 1) void k_rebuild_f32_mfma
     auto store = [&](int a, int v, f32x4 g) {
         const int i = 4 * q + v;  // row index of the matrix instruction: the lane i of the operand
         const int p = (p0 + 4 * i < h_in - 4 ? p0 + 4 * i : h_in - 4) + a;
-        *reinterpret_cast<f32x4_b4*>(o + (int64_t)p * h_out + qc) = g;
+        f32x4_b4* const at = reinterpret_cast<f32x4_b4*>(o + (int64_t)p * h_out + qc);
+        if (NT)
+            __builtin_nontemporal_store(g, at);
+        else
+            *at = g;
     };
     if (ks == 1) {
         if (idle) return;
@@ -259,6 +265,7 @@ dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R,
         SumJob sums[rf::MAX_JOBS];
         int most = 0, nsum = 0, nj = 0;
         int64_t longest = 0;  // steps of a slab
+        double bytes = 0.0;   // of the results
         for (int i = first; i < first + cnt; ++i) {
             if (!rebuild_f32_ok(h_in[i], h_out[i])) {
                 const dad_status rc = gen_rebuild(L[i], R[i], K[i], h_in[i], h_out[i], DAD_F32, G[i], slabs[i], sp[i], s);
@@ -280,6 +287,7 @@ dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R,
             jb.wg = (int)wg;
             if (jb.wg > most) most = jb.wg;
             if (ceil_div(jb.chunk, rf::BK) > longest) longest = ceil_div(jb.chunk, rf::BK);
+            bytes += 4.0 * h_in[i] * h_out[i];
             if (sp[i].splits > 1) sums[nsum++] = SumJob{slabs[i], G[i], nullptr, h_in[i] * h_out[i], sp[i].splits};
         }
         if (nj) {
@@ -287,10 +295,13 @@ dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R,
             // a short contraction is all first loads and stores: those overlap between workgroups of a compute unit
             const dim3 grid((unsigned)most, (unsigned)nj), block(64 * rf::NW);
             const auto launch = [&](auto tb, auto cap) {
+                constexpr int CAP = decltype(cap)::value, LDS = rf::NW * 4 * 64 * 16;
                 if (longest >= 8)
-                    hipLaunchKernelGGL((k_rebuild_f32_mfma<decltype(cap)::value, false>), grid, block, CU_LDS, s, tb);
+                    hipLaunchKernelGGL((k_rebuild_f32_mfma<CAP, false, false>), grid, block, CU_LDS, s, tb);
+                else if (bytes > 200.0 * (1 << 20))
+                    hipLaunchKernelGGL((k_rebuild_f32_mfma<CAP, true, true>), grid, block, LDS, s, tb);
                 else
-                    hipLaunchKernelGGL((k_rebuild_f32_mfma<decltype(cap)::value, true>), grid, block, rf::NW * 4 * 64 * 16, s, tb);
+                    hipLaunchKernelGGL((k_rebuild_f32_mfma<CAP, true, false>), grid, block, LDS, s, tb);
             };
             if (nj <= 4)
                 launch_jobs<4>(jobs, nj, launch);
@@ -307,9 +318,9 @@ dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R,
 }
 
 dad_status rebuild_f32_prepare_device() {
-    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<1, false>), CU_LDS));
-    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<4, false>), CU_LDS));
-    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<rf::MAX_JOBS, false>), CU_LDS));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<1, false, false>), CU_LDS));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<4, false, false>), CU_LDS));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_f32_mfma<rf::MAX_JOBS, false, false>), CU_LDS));
     return DAD_OK;
 }
 

@@ -65,6 +65,16 @@ def test_grouped_rank_rebuild_short_and_long(gpu, K):
                 assert torch.equal(G, alone)
 
 
+def test_grouped_rank_rebuild_of_large_results(gpu):
+    """A launch whose results are larger than 200 MiB (non-temporal stores) against one call each."""
+    pairs = [_pair(20, 4000, 4001, 60 + i, gpu) for i in range(4)]
+    single = [dad.reconstruct_grad(L, R) for L, R in pairs]
+    for (L, R), a, b in zip(pairs, single, dad.reconstruct_grad_grouped(pairs)):
+        assert torch.equal(a, b)
+    assert torch.equal(dad.reconstruct_grad_grouped(pairs[:1])[0], single[0])
+    _check_against_oracle(single[1], *pairs[1], 1e-6)
+
+
 def test_grouped_rebuild_bf16_whole_and_ragged_rows(gpu):
     """Runs of whole 256-tiles that share a launch: all of whole K stages, and with a ragged K among them."""
     whole, ragged = _pair(2048, 256, 512, 21, gpu, torch.bfloat16), _pair(2077, 512, 256, 22, gpu, torch.bfloat16)
