@@ -328,7 +328,7 @@ struct alignas(64) NnJob {  // Vt (r x Npad) <- (X Pt^T)^T
     int64_t N;
     int h;
     int cs;      // workgroups that share a row (direct_nn_splits)
-    int ks, wg;  // set by direct_nn: waves of a workgroup that share a row, workgroups
+    int wg;      // set by direct_nn: workgroups
 };
 struct alignas(64) TnJob {  // out (r x h), or `splits` slabs of it, <- Vt X
     const void* X;
