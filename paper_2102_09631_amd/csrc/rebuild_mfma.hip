@@ -59,32 +59,43 @@ __device__ __forceinline__ int rb_logical_id(int total) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Any K, h_in, h_out (each operand at least eight elements).  T = output tile edge, WM x WN waves, BK rows of K
-// per stage.  Tiles go global -> registers -> LDS, the next stage's loads in flight during the matrix
-// instructions of the current one; 16-byte loads at any element alignment (odd widths).
+// Any K, h_in, h_out (each operand at least eight elements).  128-tile, 2 x 2 waves of 64 x 64, 32 rows of K per stage.
+// Tiles go global -> registers -> LDS with 16-byte loads at any element alignment (odd widths).
+// What bounds it: the loads, about 30 bytes per clock and compute unit through the registers, and with two workgroups per unit
+// the LDS.  So nothing else is left on the path: four stages of loads are in flight, fragments are read one contraction
+// step ahead of their products (the last step of a stage behind the next one's barrier), and the loop over whole stages has no
+// branch, as a wait behind one drains every load.  A stage of 32 rows takes 0.32 us where one workgroup has a unit to itself, 0.67
+// for two; with one stage in flight and fragments read at the products it was 0.72.  13000 x 1000 x 1000: 300 us
+// in one chunk, 132 so and 52 in eight; 3767 x 1300 x 2052: 92 -> 50 us.
 // Columns beyond the matrix may hold anything, because their products land in results that are not
-// stored: a chunk that crosses the end of a row simply reads on into the next one.  Only a chunk that
-// would cross the end of the matrix is loaded from further down and replaced element by element when it
-// is stored.  Rows beyond K are zeroed at the store.
+// stored: a chunk that crosses the end of a row simply reads on into the next one.  A chunk that
+// would cross the end of the matrix is loaded from further down, and a stage that has such chunks or rows beyond K is mended in
+// LDS before it is multiplied.
 // Results leave with L as the matrix instruction's row operand: the 32 lanes of a half wave write 32
 // consecutive columns of one row of G, whatever its alignment.
 // ---------------------------------------------------------------------------------------------
 typedef u32x4 u32x4_b2 __attribute__((aligned(2)));
 
-template <int T, int WM, int WN, int BK>
-__global__ __launch_bounds__(64 * WM * WN, 2) void k_rebuild_bf16(const bf16_t* __restrict__ L, const bf16_t* __restrict__ R,
-                                                               float* __restrict__ out, int64_t K, int h_in, int h_out,
-                                                               int64_t chunk, int tiles_m, int tiles_n, int total) {
-    constexpr int THREADS = 64 * WM * WN, ROWB = T * 2, TILEB = BK * ROWB, CPR = T / 8;
-    constexpr int RPP = THREADS / CPR, NP = BK / RPP;  // rows per pass of the workgroup, passes per operand tile
-    constexpr int FA = T / (32 * WM), FB = T / (32 * WN);
-    // Stages summed by the matrix instructions before they are added to the rest: one running sum over all of K
+namespace ra {
+constexpr int TILE = 128, THREADS = 256, ROWB = TILE * 2;
+constexpr int TILEB = rb::BK * ROWB, SLOTB = 2 * TILEB;  // an operand's tile, a stage
+constexpr int SETS = 4;                                  // stages in flight in registers (two slots in LDS)
+constexpr int LDS = 2 * SLOTB;
+}  // namespace ra
+
+__global__ __launch_bounds__(ra::THREADS, 2) void k_rebuild_bf16(const bf16_t* __restrict__ L, const bf16_t* __restrict__ R,
+                                                              float* __restrict__ out, int64_t K, int h_in, int h_out,
+                                                              int64_t chunk, int tiles_m, int tiles_n, int total) {
+    constexpr int TILE = ra::TILE, ROWB = ra::ROWB, BK = rb::BK, SETS = ra::SETS, TILEB = ra::TILEB, SLOTB = ra::SLOTB;
+    constexpr int CPR = TILE / 8, RPP = ra::THREADS / CPR;  // chunks per row, rows per pass of the workgroup (two passes per tile)
+    static_assert(2 * RPP == BK, "two loads per thread and operand cover a stage");
+    // Rounds of four stages summed by the matrix instructions before they are added to the rest: one running sum over all of K
     // rounds at full height K / 16 times.  K = 3072, 1152 x 2101, error against fp64: 2.5e-7 with one sum,
-    // 0.92e-7 folded (fp32 FMA kernel before: 1.3e-7); 1300 x 2052, K = 3767, whole pass of a layer 295 -> 298 us.
-    constexpr int FOLD = 4;
+    // 0.92e-7 folded every 256 rows.
+    constexpr int FOLD = 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave / WN, wn = wave % WN;
+    const int wm = wave >> 1, wn = wave & 1;
     const int lid = rb_logical_id(total);
     const int tiles = tiles_m * tiles_n;
     const int split = lid / tiles, tile = lid - split * tiles;
@@ -96,7 +107,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_rebuild_bf16(const bf16_t* 
         qn = tile % tiles_n;
         pm = tile / tiles_n;
     }
-    const int p0 = pm * T, q0 = qn * T;
+    const int p0 = pm * TILE, q0 = qn * TILE;
     const int64_t kbeg = (int64_t)split * chunk;
     const int64_t kend = (kbeg + chunk < K) ? kbeg + chunk : K;
     const int nk = (int)((kend - kbeg + BK - 1) / BK);
@@ -104,105 +115,151 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_rebuild_bf16(const bf16_t* 
     const int c = t % CPR, r0 = t / CPR;  // this thread's chunk and first row of a tile
     const int pc = p0 + c * 8, qc = q0 + c * 8;
     const int64_t last_l = K * h_in - 8, last_r = K * h_out - 8;  // last element a 16-byte load may start at
-    u32x4 sl[NP], sr[NP];
-    auto fetch = [&](int kt) {
+    // Stages before `safe` lie inside the chunk and both matrices, the overrun of their last row's columns included.
+    auto whole = [&](int h, int col0) {
+        const int64_t room = K * h - (col0 + TILE), rows = room < 0 ? 0 : room / h + 1;  // rows k with k h + col0 + TILE <= K h
+        return rows < kend ? rows : kend;
+    };
+    const int64_t safe_l = whole(h_in, p0), safe_r = whole(h_out, q0), safe_rows = (safe_l < safe_r ? safe_l : safe_r) - kbeg;
+    const int safe = safe_rows <= 0 ? 0 : (int)(safe_rows / BK);
+
+    u32x4 sl[SETS][2], sr[SETS][2];
+    int ol[2], orr[2];  // offsets of the thread's loads in a stage
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            int64_t k = kbeg + (int64_t)kt * BK + r0 + RPP * i;
-            if (k > K - 1) k = K - 1;
-            const int64_t il = k * h_in + pc, ir = k * h_out + qc;
-            sl[i] = *reinterpret_cast<const u32x4_b2*>(L + (il < last_l ? il : last_l));
-            sr[i] = *reinterpret_cast<const u32x4_b2*>(R + (ir < last_r ? ir : last_r));
+    for (int i = 0; i < 2; ++i) {
+        ol[i] = (r0 + RPP * i) * h_in + pc;
+        orr[i] = (r0 + RPP * i) * h_out + qc;
+    }
+    // Loads of stage kt; one beyond the last repeats it, so that every wait is for a known number of younger loads.
+    auto fetch = [&](int set, int kt) {
+        const int64_t k0 = kbeg + (int64_t)(kt < nk ? kt : nk - 1) * BK;
+        const int64_t bl = k0 * h_in, br = k0 * h_out;
+        const int lim_l = last_l - bl < INT32_MAX ? (int)(last_l - bl) : INT32_MAX, lim_r = last_r - br < INT32_MAX ? (int)(last_r - br) : INT32_MAX;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            sl[set][i] = *reinterpret_cast<const u32x4_b2*>(L + bl + (ol[i] < lim_l ? ol[i] : lim_l));
+            sr[set][i] = *reinterpret_cast<const u32x4_b2*>(R + br + (orr[i] < lim_r ? orr[i] : lim_r));
         }
     };
-    auto commit = [&](int kt, int stage) {
-        char* base = smem + stage * 2 * TILEB;
-        const int64_t k0 = kbeg + (int64_t)kt * BK;
-        // no row beyond K and no chunk across the end of either matrix in this stage
-        const bool inner = k0 + BK <= kend && (k0 + BK - 1) * h_in + p0 + T - 8 <= last_l &&
-                           (k0 + BK - 1) * h_out + q0 + T - 8 <= last_r;
-        if (!inner) {
+    auto put = [&](char* slot, int set, int i) {
+        const int at = rb_lds_off<ROWB>(r0 + RPP * i, c);
+        *reinterpret_cast<u32x4*>(slot + at) = sl[set][i];
+        *reinterpret_cast<u32x4*>(slot + TILEB + at) = sr[set][i];
+    };
+    // Stage kt, landed in its slot and not whole: chunks that crossed the end of the matrix again element by element, rows beyond
+    // the K chunk zeros.
+    auto mend = [&](char* slot, int kt) {
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const bool left = i < 2;
+            const bf16_t* const X = left ? L : R;
+            const int h = left ? h_in : h_out, col = left ? pc : qc, row = r0 + RPP * (i & 1);
+            const int64_t k = kbeg + (int64_t)kt * BK + row, at = k * h + col;
+            if (k < kend && at <= (left ? last_l : last_r)) continue;
+            uint32_t e[8];
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int64_t k = k0 + r0 + RPP * i;
-                auto edge = [&](u32x4& v, const bf16_t* X, int h, int col, int64_t last) {
-                    if (k >= kend) {
-                        v = u32x4{0, 0, 0, 0};
-                    } else if (k * h + col > last) {
-                        const bf16_t* row = X + k * h;
-                        uint32_t e[8];
-                        for (int u = 0; u < 8; ++u) e[u] = col + u < h ? row[col + u] : 0u;
-                        v = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
-                    }
-                };
-                edge(sl[i], L, h_in, pc, last_l);
-                edge(sr[i], R, h_out, qc, last_r);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            *reinterpret_cast<u32x4*>(base + rb_lds_off<ROWB>(r0 + RPP * i, c)) = sl[i];
-            *reinterpret_cast<u32x4*>(base + TILEB + rb_lds_off<ROWB>(r0 + RPP * i, c)) = sr[i];
+            for (int u = 0; u < 8; ++u) e[u] = k < kend && col + u < h ? X[at + u] : 0u;
+            *reinterpret_cast<u32x4*>(slot + (left ? 0 : TILEB) + rb_lds_off<ROWB>(row, c)) =
+                u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
         }
     };
 
-    f32x16 acc[FA][FB], sum[FA][FB];
+    f32x16 acc[2][2], sum[2][2];
 #pragma unroll
-    for (int a = 0; a < FA; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < FB; ++b)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = sum[a][b][v] = 0.f;
     auto fold = [&]() {
 #pragma unroll
-        for (int a = 0; a < FA; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < FB; ++b)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     sum[a][b][v] += acc[a][b][v];
                     acc[a][b][v] = 0.f;
                 }
     };
-
-    fetch(0);
-    commit(0, 0);
-    fetch(nk > 1 ? 1 : 0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const char* tl = smem + (kt & 1) * 2 * TILEB;
+    bf16x8 fa[2][2], fb[2][2];
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            bf16x8 fa[FA], fb[FB];
+    for (int a = 0; a < 2; ++a) fa[1][a] = fb[1][a] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};  // the step before the first multiplies zeros
+    auto mma = [&](int set) {
 #pragma unroll
-            for (int a = 0; a < FA; ++a) fa[a] = rb_frag<ROWB>(tl, wm * (FA * 32) + a * 32, ks * 16, lane);
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < FB; ++b) fb[b] = rb_frag<ROWB>(tl + TILEB, wn * (FB * 32) + b * 32, ks * 16, lane);
-#pragma unroll
-            for (int a = 0; a < FA; ++a)
-#pragma unroll
-                for (int b = 0; b < FB; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-        }
-        if (kt + 1 < nk) {
-            commit(kt + 1, (kt + 1) & 1);
-            if (kt + 2 < nk) fetch(kt + 2);
+            for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][a], fb[set][b], acc[a][b], 0, 0, 0);
+    };
+    auto step = [&](auto cur_c, int kt, bool inner) {  // inner: known to be whole
+        constexpr int CUR = decltype(cur_c)::value, NEXT = (CUR + 1) % SETS;
+        __syncthreads();  // stage kt is in LDS, and everyone is done with stage kt - 1
+        char* const cur = smem + (CUR & 1) * SLOTB;
+        char* const next = smem + (NEXT & 1) * SLOTB;
+        if (!inner && kt >= safe) {
+            mend(cur, kt);
             __syncthreads();
         }
-        if (kt % FOLD == FOLD - 1) fold();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a) fa[ks][a] = rb_frag<ROWB>(cur, wm * 64 + a * 32, ks * 16, lane);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) fb[ks][b] = rb_frag<ROWB>(cur + TILEB, wn * 64 + b * 32, ks * 16, lane);
+            mma(ks ^ 1);
+            put(next, NEXT, ks);
+            if (ks == 1) fetch(NEXT, kt + 1 + SETS);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // MFMA
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);             // LDS read
+                if (m & 1) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    const std::integral_constant<int, 0> s0;
+    const std::integral_constant<int, 1> s1;
+    const std::integral_constant<int, 2> s2;
+    const std::integral_constant<int, 3> s3;
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) fetch(i, i);
+    put(smem, 0, 0);
+    put(smem, 0, 1);
+    fetch(0, SETS);
+    const int rounds = (safe < nk ? safe : nk) / SETS;
+    int kt = 0;
+    for (int done = 0; done < rounds;) {
+        const int to = done + FOLD < rounds ? done + FOLD : rounds;
+        for (; done < to; ++done, kt += SETS) {
+            step(s0, kt, true);
+            step(s1, kt + 1, true);
+            step(s2, kt + 2, true);
+            step(s3, kt + 3, true);
+        }
+        fold();
     }
+    for (; kt < nk; kt += SETS) {
+        step(s0, kt, false);
+        if (kt + 1 < nk) step(s1, kt + 1, false);
+        if (kt + 2 < nk) step(s2, kt + 2, false);
+        if (kt + 3 < nk) step(s3, kt + 3, false);
+        if (kt & SETS) fold();
+    }
+    mma(1);
     fold();
 
     // lane: column q = lane % 32, rows p = 8 (v / 4) + 4 (lane / 32) + v % 4 of each 32 x 32 block
     float* o = out + (int64_t)split * h_in * h_out;
 #pragma unroll
-    for (int a = 0; a < FA; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < FB; ++b) {
-            const int q = q0 + (wn * FB + b) * 32 + (lane & 31);
+        for (int b = 0; b < 2; ++b) {
+            const int q = q0 + (wn * 2 + b) * 32 + (lane & 31);
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int p = p0 + (wm * FA + a) * 32 + ((v >> 2) << 3) + ((lane >> 5) << 2) + (v & 3);
+                const int p = p0 + (wm * 2 + a) * 32 + ((v >> 2) << 3) + ((lane >> 5) << 2) + (v & 3);
                 if (p < h_in && q < h_out) o[(int64_t)p * h_out + q] = sum[a][b][v];
             }
         }
@@ -484,9 +541,6 @@ __global__ __launch_bounds__(64 * WM * WN) void k_rebuild_bf16_dma_jobs(RebuildJ
 
 
 
-// Tile edge of the register-staged kernel: 128 with four waves (two workgroups per CU).
-constexpr int RB_ANY_TILE = 128, RB_ANY_BK = 64;
-
 // The direct-to-LDS kernel takes whole output tiles.
 static bool rebuild_whole_tiles(int64_t K, int64_t h_in, int64_t h_out) {
     return K >= 256 && h_in % 128 == 0 && h_out % 128 == 0 && h_in <= (1 << 20) && h_out <= (1 << 20);
@@ -497,21 +551,22 @@ bool rebuild_fast_ok(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt) {
     return dt == DAD_BF16 && K * h_in >= 8 && K * h_out >= 8;
 }
 
-// K chunks of the register-staged kernel.  A stage of 64 rows takes about 0.5 us whatever the number of
-// workgroups up to two per CU; more than one chunk adds the slab traffic and the launch that sums it.
+// K chunks of the register-staged kernel, by a time in us.  A stage takes 0.32 us and up to 0.1 more as the units fill, 0.67 for
+// two workgroups of a unit; more than one chunk adds the slab traffic and the launch that sums it.
 static SplitPlan rebuild_any_split(int64_t K, int64_t h_in, int64_t h_out) {
-    const int64_t tiles = ceil_div(h_in, RB_ANY_TILE) * ceil_div(h_out, RB_ANY_TILE);
+    const int64_t tiles = ceil_div(h_in, ra::TILE) * ceil_div(h_out, ra::TILE);
     double best_t = 0.0;
     int64_t best = 1;
     for (int64_t s = 1; s <= 64; ++s) {
-        if (s > 1 && K / s < 2 * RB_ANY_BK) break;
-        const double stages = (double)ceil_div(ceil_div(K, s), RB_ANY_BK);
-        double t = (double)ceil_div(tiles * s, 512) * (3.0 + 0.5 * stages);
-        if (s > 1) t += 4.0 + (2.0 * s + 1.0) * h_in * h_out * 4.0 / 4e6;
+        if (s > 1 && K / s < 4 * rb::BK) break;
+        const double stages = (double)ceil_div(ceil_div(K, s), rb::BK), wg = (double)(tiles * s);
+        const double stage = wg <= CU_COUNT ? 0.32 + 0.1 * wg / CU_COUNT : 0.67 * (double)ceil_div(tiles * s, 2 * CU_COUNT);
+        double t = 6.0 + stages * stage;
+        if (s > 1) t += 3.5 + (2.0 * s + 1.0) * h_in * h_out * 4.0 / 6e6;
         if (s == 1 || t < best_t * 0.98) best_t = t, best = s;
     }
     SplitPlan sp;
-    sp.chunk = (int64_t)align_up((size_t)ceil_div(K, best), RB_ANY_BK);
+    sp.chunk = (int64_t)align_up((size_t)ceil_div(K, best), rb::BK);
     sp.splits = (int)ceil_div(K, sp.chunk);
     return sp;
 }
@@ -589,11 +644,10 @@ dad_status fast_rebuild(const void* L, const void* R, const RowBlocks* lb, const
                          : launch_rebuild_dma<256, 2, 4>(L, R, lb, rbk, dst, K, h_in, h_out, sp, s);
         if (rc != DAD_OK) return rc;
     } else {
-        const int lds = 4 * RB_ANY_BK * RB_ANY_TILE * 2;
-        const int tm = (int)ceil_div(h_in, RB_ANY_TILE), tn = (int)ceil_div(h_out, RB_ANY_TILE);
+        const int tm = (int)ceil_div(h_in, ra::TILE), tn = (int)ceil_div(h_out, ra::TILE);
         const int total = tm * tn * sp.splits;
         ProfScope prof(KID_REBUILD_BF16, s);
-        hipLaunchKernelGGL((k_rebuild_bf16<RB_ANY_TILE, 2, 2, RB_ANY_BK>), dim3((unsigned)total), dim3(256), lds, s,
+        hipLaunchKernelGGL(k_rebuild_bf16, dim3((unsigned)total), dim3(ra::THREADS), ra::LDS, s,
                            (const bf16_t*)L, (const bf16_t*)R, dst, K, (int)h_in, (int)h_out, sp.chunk, tm, tn, total);
         DAD_LAUNCH_CHECK();
     }

@@ -35,6 +35,17 @@ def test_rebuild_bf16_edges(gpu, K, h_in, h_out):
     assert torch.equal(G, dad.reconstruct_grad(dev(A, "bf16", gpu), dev(D, "bf16", gpu)))  # fixed summation order
 
 
+# the register-staged kernel: stages of 32 rows around the four in flight and the rounds of four, K chunks with a short last one,
+# and narrow operands, whose overrun of a 128-tile takes several rows or stages off the loop over whole stages
+@pytest.mark.parametrize("K", [31, 32, 33, 95, 127, 128, 129, 160, 191, 257, 288, 419])
+@pytest.mark.parametrize("h_in,h_out", [(130, 9), (3, 200), (127, 513)])
+def test_rebuild_bf16_stages(gpu, K, h_in, h_out):
+    rng = np.random.default_rng([35, K, h_in, h_out])
+    A, D = grid(rng.standard_normal((K, h_in)), "bf16"), grid(rng.standard_normal((K, h_out)), "bf16")
+    G = dad.reconstruct_grad(dev(A, "bf16", gpu), dev(D, "bf16", gpu))
+    assert O.rel_fro(G.cpu().numpy(), O.full_grad(A, D)) <= 1.5e-7  # at most two sums of 256 rows, as below
+
+
 # long sums: 256 rows are summed by the matrix instructions (16 roundings of about 3.4e-8 at a third of the height, 8e-8
 # together), then added to the rest (K / 256 roundings, 7e-8 at K = 3072); one running sum is at 2.5e-7
 # (the direct-to-LDS kernel on 128-tiles: 2176 columns, K that is not a multiple of 32)
