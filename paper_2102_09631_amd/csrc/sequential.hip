@@ -8,6 +8,8 @@
 // so this route costs r times the block form; it exists because it is the paper's own recurrence.
 #include "dad_internal.h"
 
+#include <type_traits>
+
 namespace dad {
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -226,6 +228,286 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The recurrence on M (fixed counts): one launch per application.  A row of M gives its part of M^T (M g) by itself,
+// v = row . g and then v * row, so a workgroup keeps a few rows in registers for both products and leaves a slab of M^T M g.
+// The next launch starts with what a launch of its own did before: every workgroup adds the slabs, subtracts the peel and
+// normalises, all in fp64 and alike, while its rows of M are on their way.  One workgroup more than the rows need keeps the
+// books: it ends the component before, forms the peel of the running vector for the next launch, and latches the status.
+// What bounds it: latency (a launch, the slabs' round trip through the memory side, two barriers per batch of rows), which is why the
+// slabs are few (SEQ_SLABS) and the threads are split into G groups that take slabs and rows in turn.
+// A whole call, 768 x 768, N = 4096, 8 components, two applications: 66 launches and 434 us with a launch per product, update, start
+// and end; 27 and 200 us so (a launch 7 to 8 us).  300 x 3999: 684 -> 479; 3999 x 200, 16 components: 737 -> 379; 1024 x 4096,
+// N = 300, 16 components: 1470 -> 1090; 4096 x 4096, four components: 843 -> 830 (M itself takes most of it).
+// Rows wider than SEQ_ROW_MOST, and the adaptive mode (its stop test sits between an update and the next product), keep a launch per step.
+// Column layout: thread c of a group holds columns at .. at + 3, at = min(4 c, h_out - 4), and those of the thread before it count
+// as zero in g; slabs and peel are kept by thread, 4 c + e.
+// ------------------------------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_b4 __attribute__((aligned(4)));
+
+constexpr int SEQ_SLABS = 64;           // at most (64 units read M faster than the launch takes); each workgroup reads them all
+constexpr int64_t SEQ_ROW_MOST = 4096;  // columns of one workgroup: 1024 threads of four
+constexpr int SEQ_ROWS = 4;             // rows of a group in flight, twice
+
+enum { SEQ_FIRST = 1, SEQ_LAST = 2 };  // the launch that starts a component, the one that ends its iteration
+
+struct SeqProduct {
+    const float* M;
+    const float* x;       // start vector (first launch)
+    const float* slabs;   // of the application before, `blocks` of them
+    const double* peel;
+    float* slabs_out;
+    double* peel_out;
+    float* p;             // M g (last launch)
+    float* g;             // the running vector, as the last launch leaves it
+    float *Qt, *sGt, *sigma;
+    int* hdr;
+    int h_in, h_out, j, blocks, batches, mode, clear_hdr;
+};
+
+// Thread groups of a workgroup; their threads (whole waves).
+static int seq_lanes(int64_t h_out) { return (int)align_up((size_t)ceil_div(h_out, 4), 64); }
+static int seq_groups(int64_t h_out) {
+    const int n = seq_lanes(h_out);
+    return n <= 128 ? 8 : n <= 256 ? 4 : n <= 512 ? 2 : 1;
+}
+static int seq_batches(int64_t h_in, int64_t h_out) { return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * SEQ_SLABS); }
+static int seq_blocks(int64_t h_in, int64_t h_out) {
+    return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * seq_batches(h_in, h_out));
+}
+
+// v[i], i < 4, summed over the wave: lane l returns the sum of v[l & 3].
+template <typename T> __device__ __forceinline__ T wave_sum4(const T (&v)[4]) {
+    const int lane = threadIdx.x & 63;
+    const bool b0 = lane & 1, b1 = lane & 2;
+    // the lane keeps the values whose index ends in its own low bits, and hands the others over
+    T a0 = (b0 ? v[1] : v[0]) + __shfl_xor(b0 ? v[0] : v[1], 1, 64);
+    T a1 = (b0 ? v[3] : v[2]) + __shfl_xor(b0 ? v[2] : v[3], 1, 64);
+    T s = (b1 ? a1 : a0) + __shfl_xor(b1 ? a0 : a1, 2, 64);
+#pragma unroll
+    for (int o = 4; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
+    return s;
+}
+
+template <int G>
+__global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double sums[2][16][4];  // per wave
+    const int n = blockDim.x / G, grp = threadIdx.x / n, c = threadIdx.x - grp * n;  // n: threads of a group, whole waves
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpg = n >> 6, w0 = grp * wpg;
+    const int h = a.h_out, pitch = 4 * n;
+    const int at = 4 * c < h - 4 ? 4 * c : h - 4;
+    bool own[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) own[e] = 4 * c < h && at + e >= 4 * c;
+    const bool books = (int)blockIdx.x == a.blocks, first = a.mode & SEQ_FIRST, last = a.mode & SEQ_LAST;
+
+    f32x4 m[2][SEQ_ROWS];
+    auto row0 = [&](int b) { return (((int)blockIdx.x * a.batches + b) * G + grp) * SEQ_ROWS; };
+    auto load = [&](auto set_c, int b) {
+        constexpr int set = decltype(set_c)::value;
+#pragma unroll
+        for (int i = 0; i < SEQ_ROWS; ++i) {
+            const int row = row0(b) + i;
+            m[set][i] = *reinterpret_cast<const f32x4_b4*>(a.M + (int64_t)(row < a.h_in ? row : a.h_in - 1) * h + at);
+        }
+    };
+    const std::integral_constant<int, 0> s0;
+    const std::integral_constant<int, 1> s1;
+    if (!books) load(s0, 0);
+
+    // the vector: every group has all of it
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    double(*red)[4] = reinterpret_cast<double(*)[4]>(smem);  // [threadIdx.x]
+    if (first) {
+        const f32x4 x = *reinterpret_cast<const f32x4_b4*>(a.x + at);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (double)x[e];
+    } else {
+        constexpr int P = G < 8 ? 16 : 8;  // slabs in flight: mostly all of a group
+        const float* src = a.slabs + 4 * c;
+        double z[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = a.peel[4 * c + e];
+        for (int b = grp; b < a.blocks; b += P * G) {
+            f32x4 t[P];
+#pragma unroll
+            for (int u = 0; u < P; ++u) t[u] = *reinterpret_cast<const f32x4*>(src + (int64_t)(b + u * G < a.blocks ? b + u * G : a.blocks - 1) * pitch);
+#pragma unroll
+            for (int u = 0; u < P; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += b + u * G < a.blocks ? (double)t[u][e] : 0.0;
+        }
+        if constexpr (G > 1) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = v[e];
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = red[c][e];
+#pragma unroll
+                for (int q = 1; q < G; ++q) v[e] += red[q * n + c][e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] -= z[e];
+    }
+    double sq = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = own[e] ? v[e] : 0.0;
+        sq += v[e] * v[e];
+    }
+    sq = wave_sum(sq);
+    if (lane == 0) sums[0][wave][0] = sq;
+    if (books && a.clear_hdr && threadIdx.x < 64) a.hdr[threadIdx.x] = 0;
+    __syncthreads();
+    double ss = 0.0;
+    for (int w = 0; w < wpg; ++w) ss += sums[0][w0 + w][0];
+    const bool gone = !(ss > 0.0);  // nothing left in this direction (or NaN): latch and leave the vector finite
+    if (books && gone && threadIdx.x == 0) a.hdr[0] = 1;
+    const double inv = gone ? 1.0 : 1.0 / sqrt(ss);
+    float g[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g[e] = (float)(v[e] * inv);
+
+    if (!books) {
+        f32x4 y = {0.f, 0.f, 0.f, 0.f};
+        auto rows = [&](auto set_c, int b) {
+            constexpr int set = decltype(set_c)::value;
+            float d[SEQ_ROWS];
+#pragma unroll
+            for (int i = 0; i < SEQ_ROWS; ++i) {
+                d[i] = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) d[i] = fmaf(m[set][i][e], g[e], d[i]);
+            }
+            double t = wave_sum4(d);
+            if (lane < 4) sums[(b + 1) & 1][wave][lane] = t;
+            __syncthreads();
+            const int r0 = row0(b);
+#pragma unroll
+            for (int i = 0; i < SEQ_ROWS; ++i) {
+                double s = 0.0;
+                for (int w = 0; w < wpg; ++w) s += sums[(b + 1) & 1][w0 + w][i];
+                const float x = r0 + i < a.h_in ? (float)s : 0.f;
+                if (last) {
+                    if (c == 0 && r0 + i < a.h_in) a.p[r0 + i] = x;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = fmaf(x, m[set][i][e], y[e]);
+                }
+            }
+        };
+        for (int b = 0; b < a.batches; b += 2) {
+            if (b + 1 < a.batches) load(s1, b + 1);
+            rows(s0, b);
+            if (b + 1 < a.batches) {
+                if (b + 2 < a.batches) load(s0, b + 2);
+                rows(s1, b + 1);
+            }
+        }
+        if (last) return;
+        f32x4* ysum = reinterpret_cast<f32x4*>(smem);
+        if constexpr (G > 1) {
+            ysum[threadIdx.x] = y;  // the sums over slabs were read before the barriers above
+            __syncthreads();
+#pragma unroll
+            for (int q = 1; q < G; ++q)
+                if (grp == 0) y += ysum[q * n + c];
+        }
+        if (grp == 0) *reinterpret_cast<f32x4*>(a.slabs_out + (int64_t)blockIdx.x * pitch + 4 * c) = y;
+        return;
+    }
+
+    // the books
+    if (first && a.j > 0) {  // sigma = ||p||, q = p / sigma and sG = sigma g of the component before
+        double t = 0.0;
+        for (int k = threadIdx.x; k < a.h_in; k += blockDim.x) t += (double)a.p[k] * (double)a.p[k];
+        t = wave_sum(t);
+        if (lane == 0) sums[1][wave][0] = t;
+        __syncthreads();
+        double pp = 0.0;
+        for (int w = 0; w < (int)blockDim.x >> 6; ++w) pp += sums[1][w][0];
+        double sigma = sqrt(pp);
+        if (!(sigma > 0.0)) {
+            if (threadIdx.x == 0) a.hdr[0] = 1;
+            sigma = 0.0;
+        }
+        const double is = sigma > 0.0 ? 1.0 / sigma : 0.0;
+        float* q_row = a.Qt + (int64_t)(a.j - 1) * a.h_in;
+        float* sg_row = a.sGt + (int64_t)(a.j - 1) * h;
+        for (int k = threadIdx.x; k < a.h_in; k += blockDim.x) q_row[k] = (float)((double)a.p[k] * is);
+        for (int k = threadIdx.x; k < h; k += blockDim.x) sg_row[k] = (float)(sigma * (double)a.g[k]);
+        if (a.sigma && threadIdx.x == 0) a.sigma[a.j - 1] = (float)sigma;
+        __threadfence_block();
+        __syncthreads();
+    }
+    if (last) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (grp == 0 && own[e]) a.g[at + e] = g[e];
+        return;
+    }
+    // peel: sum over the found pairs of sG_i (sG_i . g), the groups taking four pairs at a time in turn
+    double z[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i0 = 0, turn = 0; i0 < a.j; i0 += 4 * G, turn ^= 1) {
+        const int i1 = i0 + 4 * grp;
+        f32x4 sg[4];
+        double d[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sg[u] = *reinterpret_cast<const f32x4_b4*>(a.sGt + (int64_t)(i1 + u < a.j ? i1 + u : 0) * h + at);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            d[u] = 0.0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d[u] += (double)sg[u][e] * (double)g[e];
+        }
+        const double t = wave_sum4(d);
+        if (turn == 0) __syncthreads();  // every reader of the buffer's last contents is done
+        if (lane < 4) sums[turn][wave][lane] = t;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            double s = 0.0;
+            for (int w = 0; w < wpg; ++w) s += sums[turn][w0 + w][u];
+            if (i1 + u < a.j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z[e] += s * (double)sg[u][e];
+        }
+    }
+    if constexpr (G > 1) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = z[e];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            z[e] = red[c][e];
+#pragma unroll
+            for (int q = 1; q < G; ++q) z[e] += red[q * n + c][e];
+        }
+    }
+    if (grp == 0)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a.peel_out[4 * c + e] = z[e];
+}
+
+static dad_status seq_product(const SeqProduct& a, hipStream_t s) {
+    const int groups = seq_groups(a.h_out), threads = groups * seq_lanes(a.h_out), lds = groups > 1 ? threads * 32 : 0;
+    const dim3 grid((unsigned)a.blocks + 1);
+    ProfScope prof(KID_SEQ_VECTOR, s);
+    switch (groups) {
+        case 8: hipLaunchKernelGGL(k_seq_product<8>, grid, dim3(threads), lds, s, a); break;
+        case 4: hipLaunchKernelGGL(k_seq_product<4>, grid, dim3(threads), lds, s, a); break;
+        case 2: hipLaunchKernelGGL(k_seq_product<2>, grid, dim3(threads), lds, s, a); break;
+        default: hipLaunchKernelGGL(k_seq_product<1>, grid, dim3(threads), lds, s, a); break;
+    }
+    DAD_LAUNCH_CHECK();
+    return DAD_OK;
+}
+
 // The recurrence is a chain of short launches, and a product with M = A^T Delta is one of them where a product with
 // the factors is two and a slab sum: M is made first wherever dense_wins says so.  768 x 768, N = 4096, bf16, 8
 // components: 624 us on the factors, 444 us on M (of which M 20 us).
@@ -237,6 +519,8 @@ struct SeqPlan {
     size_t off_panel;
     size_t total;
     bool dense;        // some number of components is faster on the gradient: the workspace holds it
+    bool fused;        // and a workgroup holds its rows: k_seq_product
+    size_t slab_bytes, peel_bytes;  // of one application: two of each over the slabs M was made from, which are done with by then
 };
 
 // The size query knows neither the components nor their applications; from 64 vectors' worth of products on nothing
@@ -251,6 +535,15 @@ static SeqPlan plan_sequential(int64_t N, int64_t h_in, int64_t h_out, dad_dtype
     p.dense = dense_wins(N, h_in, h_out, dt, SEQ_MANY_PRODUCTS);
     const size_t factors = p.c.off_Yt + vec;  // nothing is orthonormalised: the layout ends with its Yt
     p.off_panel = p.dense && p.d.total > factors ? p.d.total : factors;
+    p.fused = p.dense && h_out >= 4 && h_out <= SEQ_ROW_MOST;
+    p.slab_bytes = p.peel_bytes = 0;
+    if (p.fused) {
+        const size_t pitch = 4 * (size_t)seq_lanes(h_out);
+        p.slab_bytes = (size_t)seq_blocks(h_in, h_out) * pitch * 4;
+        p.peel_bytes = pitch * 8;
+        const size_t end = align_up(p.d.off_slabs + 2 * (p.slab_bytes + p.peel_bytes), 256);
+        if (end > p.off_panel) p.off_panel = end;
+    }
     p.total = p.off_panel + vec;
     return p;
 }
@@ -327,6 +620,30 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
     };
     const float* const p_vec = dense ? static_cast<const float*>(V) : Ut;
     if (dense) DAD_TRY(launch_rebuild(A, D, N, h_in, h_out, dt, M, reinterpret_cast<float*>(ws + p.d.off_slabs), p.d.rb, s));
+    if (dense && p.fused && !adaptive) {
+        SeqProduct a = {};
+        char* const slabs = ws + p.d.off_slabs;
+        char* const peels = slabs + 2 * p.slab_bytes;
+        a.M = M, a.p = static_cast<float*>(V), a.g = panel, a.Qt = Qt, a.sGt = sGt, a.sigma = sigma, a.hdr = hdr;
+        a.h_in = (int)h_in, a.h_out = (int)h_out, a.blocks = seq_blocks(h_in, h_out), a.batches = seq_batches(h_in, h_out);
+        for (int j = 0; j < r; ++j)
+            for (int it = 0; it <= n_iter; ++it) {
+                a.j = j, a.mode = (it == 0 ? SEQ_FIRST : 0) | (it == n_iter ? SEQ_LAST : 0), a.clear_hdr = j == 0 && it == 0;
+                a.x = G0 + (int64_t)j * h_out;
+                const int to = it & 1, from = to ^ 1;
+                a.slabs = reinterpret_cast<const float*>(slabs + from * p.slab_bytes);
+                a.peel = reinterpret_cast<const double*>(peels + from * p.peel_bytes);
+                a.slabs_out = reinterpret_cast<float*>(slabs + to * p.slab_bytes);
+                a.peel_out = reinterpret_cast<double*>(peels + to * p.peel_bytes);
+                DAD_TRY(seq_product(a, s));
+            }
+        ProfScope prof(KID_SEQ_VECTOR, s);
+        const int j = r - 1;
+        hipLaunchKernelGGL(k_seq_finish, dim3(1), dim3(1024), 0, s, p_vec, (const float*)panel, Qt + (int64_t)j * h_in,
+                           sGt + (int64_t)j * h_out, sigma ? sigma + j : (float*)nullptr, h_in, h_out, hdr, j, theta, eff_rank);
+        DAD_LAUNCH_CHECK();
+        return DAD_OK;
+    }
     for (int j = 0; j < r; ++j) {
         {
             ProfScope prof(KID_SEQ_VECTOR, s);

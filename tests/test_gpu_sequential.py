@@ -114,6 +114,25 @@ def test_sequential_on_the_factors_and_on_the_gradient(gpu, N, h_in, h_out, r, n
     check(out, "f32", 4 * np.finfo(np.float32).eps * (sv[0] / sv[r - 1]) ** 2)
 
 
+# one launch per application on the gradient: eight, four, two groups of threads and one, widths around them and beyond the widest,
+# several batches of rows per workgroup with a short last one, more found pairs than one turn of the peel takes
+@pytest.mark.parametrize("N,h_in,h_out,r,n_iter,dtype", [(300, 33, 40, 9, 2, "f32"), (400, 2100, 130, 3, 2, "f32"),
+                                                          (600, 300, 515, 40, 1, "f32"), (1500, 530, 1026, 20, 2, "f32"),
+                                                          (1500, 270, 2049, 12, 2, "bf16"), (900, 70, 4095, 6, 2, "bf16"),
+                                                          (900, 70, 4097, 3, 2, "bf16"), (4096, 1300, 512, 5, 3, "bf16"),
+                                                          (600, 64, 9, 4, 2, "f32"), (600, 40, 4, 2, 2, "f32")])
+def test_sequential_products_on_the_gradient(gpu, N, h_in, h_out, r, n_iter, dtype):
+    rng = np.random.default_rng([27, N, h_in, h_out])
+    A = rng.standard_normal((N, h_in)).astype(np.float32)
+    D = (rng.standard_normal((N, h_out)) * (0.98 ** np.arange(N))[:, None]).astype(np.float32)
+    if dtype == "bf16":
+        A, D = bf16_round(A), bf16_round(D)
+    G0 = rng.standard_normal((r, h_out)).astype(np.float32)
+    out = run(A, D, G0, r, n_iter, dtype, gpu)
+    sv = np.linalg.svd(A.astype(np.float64).T @ D.astype(np.float64), compute_uv=False)
+    check(out, "f32", 4 * np.finfo(np.float32).eps * (sv[0] / sv[r - 1]) ** 2)  # as above
+
+
 def test_sequential_converges_to_truncated_svd(gpu):
     """With a planted gap and enough iterations the pairs are the leading singular triplets:
     the product equals the truncated SVD (Eckart-Young optimum) and sigma the singular values."""
