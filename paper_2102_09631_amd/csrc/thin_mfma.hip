@@ -272,17 +272,12 @@ __global__ __launch_bounds__(256) void k_thin_tn_bf16_dma(const SRC X, const bf1
             if ((int)blockIdx.x >= strips * splits) return;
         }
     }
-    // Workgroups are handed to the eight XCDs round-robin by their linear index.  All column strips
-    // of one row chunk go to the same XCD, so that the chunk of V they share is fetched into one L2.
-    int strip, split;
-    if ((splits & 7) == 0) {
-        const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
-        split = xcd + 8 * (q / strips);
-        strip = q % strips;
-    } else {
-        strip = blockIdx.x % strips;
-        split = blockIdx.x / strips;
-    }
+    // Workgroups are handed to the eight XCDs round-robin by their linear index.  Each XCD takes a contiguous run of
+    // (row chunk, column strip) pairs, so that the strips that share a chunk of V read it through one L2, or two where a chunk crosses
+    // the end of a run.
+    const int pairs = strips * splits, turn = blockIdx.x & 7, run = pairs >> 3, more = pairs & 7;
+    const int id = turn * run + (turn < more ? turn : more) + ((int)blockIdx.x >> 3);
+    const int split = id / strips, strip = id - split * strips;
     const int p0 = strip * PW;
     const int64_t nbeg = (int64_t)split * chunk_rows;
     const int64_t nend = (nbeg + chunk_rows < N) ? nbeg + chunk_rows : N;
