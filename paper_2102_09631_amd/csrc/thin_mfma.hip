@@ -28,16 +28,17 @@ typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
 // MFMA 32x32 result layout) leave as bf16 through LDS, so that the tile goes out as contiguous
 // 16-byte stores.  planes = 2 also writes the rounding remainder: plane 0 holds hi = bf16(x), plane 1
 // (N * r elements further on) lo = bf16(x - hi), and hi + lo carries 16 significand bits of x.
-// vs is LDS for planes * RT * r bf16 values; the caller has finished reading its tiles.
+// vs is LDS for planes * RT * r bf16 values that nobody reads any more; holds: this wave has a part of the tile.
 template <int JT, int RT>
 __device__ __forceinline__ void store_planes(const f32x16 (&acc)[JT], bf16_t* vs, bf16_t* __restrict__ V, int64_t N,
-                                             int64_t n0, int64_t rows_here, int r, int planes, int row0, int nthreads) {
+                                             int64_t n0, int64_t rows_here, int r, int planes, int row0, int nthreads,
+                                             bool holds) {
     const int t = threadIdx.x, lane = t & 63;
     bf16_t* vlo = vs + RT * r;
 #pragma unroll
     for (int j = 0; j < JT; ++j) {
         const int col = j * 32 + (lane & 31);
-        if (col < r) {
+        if (holds && col < r) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = row0 + ((v >> 2) << 3) + ((lane >> 5) << 2) + (v & 3);
@@ -70,12 +71,17 @@ constexpr int BK = 64;              // contraction columns per stage (128 B of e
 // ------------------------------------------------------------------------------------------------
 // SRC is `const bf16_t*` (one allocation) or RowBlocks (the sites' blocks in place; a workgroup's
 // rows lie in one block because every block holds a multiple of 256 rows).
+// SHARES (factors of few rows): the walk over the contraction columns is summed in four shares of its stages, (s0 + s1) +
+// (s2 + s3), whatever the launch.  KS = 1: a workgroup of W waves takes them one after the other.  KS = 2, 4: as many groups of
+// W waves each take a half or a share at the same time and are summed through LDS: W = 1, 2 by itself leaves a compute unit with
+// too few loads in flight (two stages of 4 KiB of rows per wave) and too long a walk.  1024 x 768, r = 16: 7.7 us a launch with
+// one wave per 32 rows, 5.8 with four.
 // job_stride != 0 (RowBlocks only): the blocks are independent jobs of N rows each (a batch of equal
 // reductions); block j multiplies the panel and writes the V that lie j * job_stride bytes after Pb
 // and V, and counts its workgroups from its own first row, so that a job's result does not depend
 // on the batch it runs in.
-template <int RP, int W, int NS, typename SRC>
-__global__ __launch_bounds__(64 * W) void k_thin_nn_bf16_dma(const SRC X, const bf16_t* __restrict__ Pb,
+template <int RP, int W, int KS, bool SHARES, int NS, typename SRC>
+__global__ __launch_bounds__(64 * W * KS) void k_thin_nn_bf16_dma(const SRC X, const bf16_t* __restrict__ Pb,
                                                             bf16_t* __restrict__ V, int64_t N, int h, int r, int nt,
                                                             int planes, int64_t job_stride) {
     constexpr int JT = RP / 32, RT = 32 * W, ROWB = 128;
@@ -84,7 +90,7 @@ __global__ __launch_bounds__(64 * W) void k_thin_nn_bf16_dma(const SRC X, const 
     constexpr int PL = (PI + W - 1) / W;     // per wave (waves beyond PI repeat earlier pieces)
     constexpr int LOADS = 4 + PL;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % W, group = (threadIdx.x >> 6) / W;
     int64_t n0 = (int64_t)blockIdx.x * RT;
     if constexpr (!std::is_pointer<SRC>::value) {
         if (job_stride != 0) {  // the job's own width, if the jobs differ in it
@@ -108,7 +114,11 @@ __global__ __launch_bounds__(64 * W) void k_thin_nn_bf16_dma(const SRC X, const 
     // 128-byte row pieces over the memory channels instead of piling onto the few channels that one
     // common offset maps to when the row pitch is a large power of two.  The start depends on the rows, not on the workgroup size, so that a row's sum
     // is taken in the same order whatever W the launch uses.
-    int kidx = (int)(((unsigned)(n0 / 256) * 5u) % (unsigned)nk);
+    static_assert(KS == 1 || SHARES, "a group takes whole shares");
+    const int share = (nk + 3) / 4, mine = share * (4 / KS);  // stages; the last groups may have fewer or none
+    const int kbeg = group * mine < nk ? group * mine : nk;
+    const int nown = nk - kbeg < mine ? nk - kbeg : mine, steps = KS == 1 ? nk : mine;
+    int kidx = (int)(((unsigned)(n0 / 256) * 5u + (unsigned)kbeg) % (unsigned)nk);
 
     const char* gx[4];
 #pragma unroll
@@ -126,7 +136,8 @@ __global__ __launch_bounds__(64 * W) void k_thin_nn_bf16_dma(const SRC X, const 
         const int c = (lane & 7) ^ ((row >> 1) & 7);
         gp[i] = reinterpret_cast<const char*>(Pb + (int64_t)row * h) + c * 16;
     }
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    char* const ring = smem + group * (NS * STAGEB);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
 
     auto issue = [&](int stage) {
         const uint32_t base = lds0 + stage * STAGEB;
@@ -143,43 +154,85 @@ __global__ __launch_bounds__(64 * W) void k_thin_nn_bf16_dma(const SRC X, const 
         kidx = (kidx + 1 == nk) ? 0 : kidx + 1;
     };
 
-    f32x16 acc[JT];
+    f32x16 acc[JT], half0[JT], half1[JT];
 #pragma unroll
     for (int j = 0; j < JT; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[j][v] = half0[j][v] = half1[j][v] = 0.f;
+    auto share_done = [&](f32x16 (&half)[JT]) {
+#pragma unroll
+        for (int j = 0; j < JT; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                half[j][v] += acc[j][v];
+                acc[j][v] = 0.f;
+            }
+    };
 
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
-        if (s < nk) issue(s);
+        if (s < nown) issue(s);
 
     const int mrow = lane & 31, swz = (mrow >> 1) & 7, khalf = lane >> 5;
     int slot = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-        if (kt + NS - 2 < nk)
-            wait_vmcnt<LOADS * (NS - 2)>();
-        else
-            wait_vmcnt<0>();
-        __syncthreads();  // tile kt complete in LDS (the panel part comes from other waves); slot of kt-1 free
-        if (kt + NS - 1 < nk) issue(slot == 0 ? NS - 1 : slot - 1);
-        const char* xb = smem + slot * STAGEB + (wave * 32 + mrow) * ROWB;
-        const char* pb = smem + slot * STAGEB + XTILEB + mrow * ROWB;
+    auto walk = [&](int from, int to) {
+        for (int kt = from; kt < to; ++kt) {
+            if (kt + NS - 2 < nown)
+                wait_vmcnt<LOADS * (NS - 2)>();
+            else
+                wait_vmcnt<0>();
+            __syncthreads();  // tile kt complete in LDS (the panel part comes from other waves); slot of kt-1 free
+            if (kt + NS - 1 < nown) issue(slot == 0 ? NS - 1 : slot - 1);
+            if (KS == 1 || kt < nown) {
+                const char* xb = ring + slot * STAGEB + (wave * 32 + mrow) * ROWB;
+                const char* pb = ring + slot * STAGEB + XTILEB + mrow * ROWB;
 #pragma unroll
-        for (int ks = 0; ks < nn::BK / 16; ++ks) {
-            const int c = ((ks * 2 + khalf) ^ swz) << 4;
-            bf16x8 fa = *reinterpret_cast<const bf16x8*>(xb + c);
+                for (int ks = 0; ks < nn::BK / 16; ++ks) {
+                    const int c = ((ks * 2 + khalf) ^ swz) << 4;
+                    bf16x8 fa = *reinterpret_cast<const bf16x8*>(xb + c);
 #pragma unroll
-            for (int j = 0; j < JT; ++j) {
-                bf16x8 fb = *reinterpret_cast<const bf16x8*>(pb + j * 32 * ROWB + c);
-                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[j], 0, 0, 0);
+                    for (int j = 0; j < JT; ++j) {
+                        bf16x8 fb = *reinterpret_cast<const bf16x8*>(pb + j * 32 * ROWB + c);
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[j], 0, 0, 0);
+                    }
+                }
             }
+            slot = slot == NS - 1 ? 0 : slot + 1;
         }
-        slot = slot == NS - 1 ? 0 : slot + 1;
+    };
+    if constexpr (SHARES) {
+#pragma unroll
+        for (int i = 0; i < 4 / KS; ++i) {
+            walk(i * share < steps ? i * share : steps, (i + 1) * share < steps ? (i + 1) * share : steps);
+            share_done(i < 2 ? half0 : half1);
+        }
+    } else {
+        walk(0, steps);
+        share_done(half0);
     }
     __syncthreads();
 
+    // the groups' parts, and the halves of a group that has both
+    f32x16* parts = reinterpret_cast<f32x16*>(smem);  // [group - 1][wave][j][lane]
+    if constexpr (KS > 1) {
+        if (group)
+#pragma unroll
+            for (int j = 0; j < JT; ++j) parts[(((group - 1) * W + wave) * JT + j) * 64 + lane] = half0[j];
+        __syncthreads();
+        if (group == 0)
+#pragma unroll
+            for (int j = 0; j < JT; ++j) {
+                auto part = [&](int g) { return parts[(((g - 1) * W + wave) * JT + j) * 64 + lane]; };
+                if constexpr (KS == 2) half0[j] += part(1);
+                if constexpr (KS == 4) half0[j] = (half0[j] + part(1)) + (part(2) + part(3));
+            }
+    } else if constexpr (SHARES) {
+#pragma unroll
+        for (int j = 0; j < JT; ++j) half0[j] += half1[j];
+    }
     // epilogue: fp32 -> bf16 through LDS so the tile leaves as contiguous 16-byte stores
-    store_planes<JT, RT>(acc, reinterpret_cast<bf16_t*>(smem), V, N, n0, RT, r, planes, wave * 32, 64 * W);
+    store_planes<JT, RT>(half0, reinterpret_cast<bf16_t*>(parts + (KS - 1) * W * JT * 64), V, N, n0, RT, r, planes, wave * 32, 64 * W * KS,
+                         group == 0);
 }
 
 // Start of a compress call on the direct-to-LDS path: Gb <- bf16(G0) with rows r..RP-1 zero, the same
@@ -450,20 +503,20 @@ dad_status launch_panel_init(const float* G0, void* Gb, void* Ub, int64_t h_in, 
     return DAD_OK;
 }
 
-constexpr int nn_dma_lds(int rp, int w, int ns) { return ns * (32 * w * 128 + rp * 128); }
+constexpr int nn_dma_lds(int rp, int w, int ks, int ns) { return ks * ns * (32 * w * 128 + rp * 128); }
 constexpr int tn_dma_lds(int r, int pw, int bk, int nv) { return 3 * (bk * pw * 2 + nv * bk * r * 2 + 256); }
 
-template <int RP, int W, int NS>
+template <int RP, int W, int KS, bool SHARES, int NS>
 static dad_status dma_thin_nn_cfg(const void* X, const RowBlocks* xb, const void* Pb, void* out, int64_t N, int64_t h,
                                   int r, int planes, int jobs, int64_t job_stride, hipStream_t s) {
-    const int lds = nn_dma_lds(RP, W, NS);
-    const dim3 grid((unsigned)(jobs * (N / (32 * W)))), block(64 * W);
+    const int lds = nn_dma_lds(RP, W, KS, NS);
+    const dim3 grid((unsigned)(jobs * (N / (32 * W)))), block(64 * W * KS);
     const int nt = stream_once(jobs * N, h) ? 1 : 0;
     if (xb)
-        hipLaunchKernelGGL((k_thin_nn_bf16_dma<RP, W, NS, RowBlocks>), grid, block, lds, s, *xb, (const bf16_t*)Pb,
+        hipLaunchKernelGGL((k_thin_nn_bf16_dma<RP, W, KS, SHARES, NS, RowBlocks>), grid, block, lds, s, *xb, (const bf16_t*)Pb,
                            (bf16_t*)out, N, (int)h, r, nt, planes, jobs > 1 || job_stride ? job_stride : (int64_t)0);
     else
-        hipLaunchKernelGGL((k_thin_nn_bf16_dma<RP, W, NS, const bf16_t*>), grid, block, lds, s, (const bf16_t*)X,
+        hipLaunchKernelGGL((k_thin_nn_bf16_dma<RP, W, KS, SHARES, NS, const bf16_t*>), grid, block, lds, s, (const bf16_t*)X,
                            (const bf16_t*)Pb, (bf16_t*)out, N, (int)h, r, nt, planes, (int64_t)0);
     DAD_LAUNCH_CHECK();
     return DAD_OK;
@@ -485,13 +538,21 @@ dad_status dma_thin_nn(const void* X, const RowBlocks* xb, const void* Pb, void*
     // which take workgroups round-robin, each receive workgroups of every job and finish together.
     const bool per_job = job_stride != 0 && xb->h[0] != 0;
     const int64_t rows = per_job ? N : jobs * N;
-#define DAD_NN_W(W) \
-    (r <= 32 ? dma_thin_nn_cfg<32, W, 3>(X, xb, Pb, out, N, h, r, planes, jobs, job_stride, s) \
-             : dma_thin_nn_cfg<64, W, 3>(X, xb, Pb, out, N, h, r, planes, jobs, job_stride, s))
-    if (rows / 256 >= want) return DAD_NN_W(8);
-    if (rows / 128 >= want) return DAD_NN_W(4);
-    if (rows / 64 >= want) return DAD_NN_W(2);
-    return DAD_NN_W(1);
+    // The shorter ones also have groups of waves share the contraction: four up to 8192 rows, two from there on, where four
+    // (96 to 144 KiB of LDS) keep the launches of other lanes off a unit.  Whole layer passes: 4096 x 768 x 3072, r = 16, 204 -> 171 us;
+    // 8192 x 1024 x 4096, r = 32, 326 -> 304 with two and 280 with four groups, but two layers of 8192 x 1024 on two lanes 271 -> 262
+    // with two and 273 with four.  At 16384 rows a lone layer gains 2 % and an encoder block on four lanes loses 1 %: one group,
+    // unless the rows are those of a batch (four sites of 4096 x 768 x 3072: 274 us before, 262 with two groups).
+    // SHARES goes by one job's rows, so that a job of a batch adds in the order of a call of its own.
+#define DAD_NN_W(W, KS, SHARES) \
+    (r <= 32 ? dma_thin_nn_cfg<32, W, KS, SHARES, 3>(X, xb, Pb, out, N, h, r, planes, jobs, job_stride, s) \
+             : dma_thin_nn_cfg<64, W, KS, SHARES, 3>(X, xb, Pb, out, N, h, r, planes, jobs, job_stride, s))
+    const bool shares = N / 64 < want;
+    if (rows / 256 >= want) return shares ? DAD_NN_W(8, 1, true) : DAD_NN_W(8, 1, false);
+    if (rows / 128 >= want) return shares ? DAD_NN_W(4, 1, true) : DAD_NN_W(4, 1, false);
+    if (rows / 64 >= want) return shares ? DAD_NN_W(2, 2, true) : DAD_NN_W(2, 1, false);
+    if (rows / 32 >= want) return DAD_NN_W(1, 2, true);
+    return DAD_NN_W(1, 4, true);
 #undef DAD_NN_W
 }
 
@@ -558,11 +619,13 @@ dad_status dma_thin_tn(const void* X, const RowBlocks* xb, const void* V, float*
 // Once per device: the direct-to-LDS kernels use more than the 64 KiB of dynamic LDS a kernel gets
 // without asking.
 dad_status thin_prepare_device() {
-#define DAD_NN_ATTR(RP, W)                                                                             \
-    DAD_HIP_TRY(set_max_lds((k_thin_nn_bf16_dma<RP, W, 3, const bf16_t*>), nn_dma_lds(RP, W, 3))); \
-    DAD_HIP_TRY(set_max_lds((k_thin_nn_bf16_dma<RP, W, 3, RowBlocks>), nn_dma_lds(RP, W, 3)))
-    DAD_NN_ATTR(32, 1); DAD_NN_ATTR(32, 2); DAD_NN_ATTR(32, 4); DAD_NN_ATTR(32, 8);
-    DAD_NN_ATTR(64, 1); DAD_NN_ATTR(64, 2); DAD_NN_ATTR(64, 4); DAD_NN_ATTR(64, 8);
+#define DAD_NN_ATTR(RP, W, KS, SHARES)                                                                                 \
+    DAD_HIP_TRY(set_max_lds((k_thin_nn_bf16_dma<RP, W, KS, SHARES, 3, const bf16_t*>), nn_dma_lds(RP, W, KS, 3))); \
+    DAD_HIP_TRY(set_max_lds((k_thin_nn_bf16_dma<RP, W, KS, SHARES, 3, RowBlocks>), nn_dma_lds(RP, W, KS, 3)))
+    DAD_NN_ATTR(32, 1, 4, true); DAD_NN_ATTR(32, 1, 2, true); DAD_NN_ATTR(32, 2, 2, true); DAD_NN_ATTR(32, 2, 1, false); DAD_NN_ATTR(32, 4, 1, true); DAD_NN_ATTR(32, 4, 1, false);
+    DAD_NN_ATTR(32, 8, 1, true); DAD_NN_ATTR(32, 8, 1, false);
+    DAD_NN_ATTR(64, 1, 4, true); DAD_NN_ATTR(64, 1, 2, true); DAD_NN_ATTR(64, 2, 2, true); DAD_NN_ATTR(64, 2, 1, false); DAD_NN_ATTR(64, 4, 1, true); DAD_NN_ATTR(64, 4, 1, false);
+    DAD_NN_ATTR(64, 8, 1, true); DAD_NN_ATTR(64, 8, 1, false);
 #undef DAD_NN_ATTR
 #define DAD_TN_ATTR(R, PW, BK)                                                                              \
     DAD_HIP_TRY(set_max_lds((k_thin_tn_bf16_dma<R, PW, BK, 1, const bf16_t*>), tn_dma_lds(R, PW, BK, 1))); \

@@ -443,3 +443,20 @@ def test_mixed_group_runs_its_layers_side_by_side(gpu):
         grp.run()
     chain, nodes = _longest_chain(graph)
     assert chain <= 0.6 * nodes, (chain, nodes)
+
+
+# The contraction over columns is summed in four shares however a launch divides them: by four, two or no groups of waves, and with one
+# to eight waves of rows.  Widths of 2, 6 and 10 stages (shares of 1, 2 and 3, the last ones short or empty).
+@pytest.mark.parametrize("r", [16, 64])
+@pytest.mark.parametrize("N,count", [(256, 3), (8192, 1), (8192, 2), (4096, 8), (8192, 8), (16384, 2)])
+@pytest.mark.parametrize("hi,ho", [(128, 384), (640, 128)])
+def test_shares_of_a_contraction_do_not_depend_on_the_batch(gpu, N, count, hi, ho, r):
+    layers = [_layer(N, hi, ho, r, 700 + i, gpu, torch.bfloat16) for i in range(count)]
+    single = [dad.compress_rank(A, D, r, 2, G0, check=True) for A, D, G0 in layers]
+    Pts, Gts = dad.CompressGroup(layers, r, 2, lanes=1).run(check=True)
+    torch.cuda.synchronize()
+    for (p1, g1), p2, g2 in zip(single, Pts, Gts):
+        assert torch.equal(p1, p2) and torch.equal(g1, g2)
+    A, D, G0 = layers[-1]
+    ref = O.rank_r_grad(*O.block_spi(A.float().cpu().numpy(), D.float().cpu().numpy(), G0.cpu().numpy(), 2))
+    assert O.rel_fro(dad.reconstruct_grad(Pts[-1], Gts[-1]).cpu().numpy(), ref) <= 2e-2  # as above
