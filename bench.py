@@ -453,8 +453,9 @@ def backprop(args, w, dad, W, torch, np, dev):
 def sequential(args, w, dad, W, torch, np, dev):
     """Algorithm 2 one singular pair at a time (dad_compress_rank_sequential) on the stacked factors
     of ONE block of the model (its distinct layer shapes): r components x (4 n_iter + 2) thin passes,
-    each over a whole factor, or, for a layer the library iterates on its gradient, r x (2 n_iter + 1)
-    passes over that (fp32, built once from the factors).  A step is one pass over that block; the metric is the time per layer,
+    each over a whole factor, or, for a layer the library iterates on its gradient, r x (n_iter + 1)
+    passes over that (fp32, built once from the factors), r x n_iter more where its rows are too wide for one workgroup.
+    A step is one pass over that block; the metric is the time per layer,
     to be read beside compress_us_per_layer of the default mode (the block form of the same method)."""
     tdt = torch.bfloat16 if w.dtype == "bf16" else torch.float32
     es = 2 if w.dtype == "bf16" else 4
@@ -500,17 +501,19 @@ def sequential(args, w, dad, W, torch, np, dev):
         for k, v in one.items():
             kern[k] = (kern[k][0] + v[0], kern[k][1] + v[1]) if k in kern else (v[0], v[1])
         if any(k.startswith("k_rebuild") and v[1] > 0 for k, v in one.items()):
-            moved = float(passes) * hi * ho * 4
+            # k_seq_product takes both products of an application from one read of the gradient
+            reads = r * (n_iter + 1) if one.get("k_seq_product", (0, 0))[1] > 0 else passes
+            moved = float(reads) * hi * ho * 4
             bytes_ += moved + float(N) * (hi + ho) * es + hi * ho * 4.0
             on_gradient += 1
         else:
             moved = float(passes) * N * (hi + ho) * es
             bytes_ += moved
         thin_bytes += moved
-    thin = {k: v for k, v in kern.items() if k.startswith("k_thin") and v[1] > 0}
+    thin = {k: v for k, v in kern.items() if k.startswith(("k_thin", "k_seq_product")) and v[1] > 0}
     thin_ms = sum(v[0] for v in thin.values())
     dom = max(thin, key=lambda k: thin[k][0])
-    k_rate = thin_bytes / (thin_ms * 1e-3) / 1e9       # all thin launches together stream `thin_bytes`
+    k_rate = thin_bytes / (thin_ms * 1e-3) / 1e9       # all these launches together stream `thin_bytes`
     roofline = {"kernel": "+".join(sorted(thin)), "dominant": dom, "bound": "hbm", "achieved": k_rate,
                 "peak": PEAK_HBM_GBPS, "unit": "GB/s", "frac": k_rate / PEAK_HBM_GBPS,
                 "avg_us": thin_ms * 1e3 / sum(v[1] for v in thin.values()), "traffic": None}

@@ -200,7 +200,7 @@ enum KernelId {
     KID_STACK = 0, KID_THIN_NN_BF16, KID_THIN_TN_BF16, KID_REDUCE, KID_GRAM, KID_APPLY, KID_APPLY2, KID_REBUILD_BF16,
     KID_THIN_NN, KID_THIN_TN, KID_REBUILD, KID_PANEL_INIT, KID_REBUILD_BF16_DMA, KID_BACKPROP_BF16, KID_BACKPROP,
     KID_GRAM_TILES, KID_GRAM_GATHER, KID_NS_STEP, KID_NS_PROJECT, KID_REBUILD_F32, KID_REDUCE_WIDE, KID_SEQ_VECTOR,
-    KID_DIRECT_NN, KID_DIRECT_TN, KID_DIRECT_NN_TALL,
+    KID_DIRECT_NN, KID_DIRECT_TN, KID_DIRECT_NN_TALL, KID_SEQ_PRODUCT,
     KID_COUNT
 };
 

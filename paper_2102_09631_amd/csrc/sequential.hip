@@ -497,7 +497,7 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
 static dad_status seq_product(const SeqProduct& a, hipStream_t s) {
     const int groups = seq_groups(a.h_out), threads = groups * seq_lanes(a.h_out), lds = groups > 1 ? threads * 32 : 0;
     const dim3 grid((unsigned)a.blocks + 1);
-    ProfScope prof(KID_SEQ_VECTOR, s);
+    ProfScope prof(KID_SEQ_PRODUCT, s);
     switch (groups) {
         case 8: hipLaunchKernelGGL(k_seq_product<8>, grid, dim3(threads), lds, s, a); break;
         case 4: hipLaunchKernelGGL(k_seq_product<4>, grid, dim3(threads), lds, s, a); break;
