@@ -136,6 +136,13 @@ def test_reduction_edges(gpu, dtype, N, h_in, h_out, r):
     assert torch.equal(Pt, Pt2) and torch.equal(Gt, Gt2)
 
 
+# a wide panel is shared by waves with rows of their own from N > 8160 on: fp32 from 33 columns, bf16 from 49
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,h_in,h_out,r", [(8160, 90, 130, 33), (8161, 90, 130, 33), (8161, 131, 100, 49), (8193, 70, 72, 64), (12290, 130, 90, 48)])
+def test_reduction_wide_panels(gpu, dtype, N, h_in, h_out, r):
+    test_reduction_edges(gpu, dtype, N, h_in, h_out, r)
+
+
 # wide fp32 rows: thin_nn adds sums of 64 columns (16 matrix instructions) and of its waves.  An application is four
 # contractions of about 1.2e-7 each, 3e-7 for the pair's product; one running sum over a wave's share of a row is at 6.5e-7
 @pytest.mark.parametrize("N,h_in,h_out,r", [(186, 4096, 4096, 35), (64, 4096, 4096, 16), (128, 6000, 5000, 4), (187, 4093, 4090, 35)])
