@@ -143,6 +143,24 @@ def test_reduction_wide_panels(gpu, dtype, N, h_in, h_out, r):
     test_reduction_edges(gpu, dtype, N, h_in, h_out, r)
 
 
+# V = Delta G by itself: A picks 128 rows of it, which the contraction over rows then copies exactly.  The rows' sums are added up as
+# those of four parts of the columns, by waves or by quarters of a walk.  An addition rounds by 2.4e-8 (rms) of its partial sum: m
+# sums of 64 columns (bf16 128) per part come to sqrt(m / 2) of that, 9.8e-8 at m = 32, and one chain of 128 to 1.9e-7
+@pytest.mark.parametrize("dtype,N,h_out,r", [("f32", 8200, 4096, 64), ("f32", 8200, 8192, 64), ("f32", 9000, 8190, 33), ("f32", 16352, 4100, 49),
+                                             ("f32", 16353, 4096, 20), ("f32", 8192, 8192, 40), ("bf16", 8200, 8192, 64), ("bf16", 12001, 8190, 49),
+                                             ("bf16", 17000, 8192, 5)])
+def test_rows_of_the_panel_product_are_summed_in_parts(gpu, dtype, N, h_out, r):
+    rng = np.random.default_rng([37, N, h_out, r])
+    D = dev(rng.standard_normal((N, h_out)).astype(np.float32), dtype, gpu)
+    rows = torch.arange(130, device=gpu) * N // 130
+    A = torch.zeros((N, 130), dtype=D.dtype, device=gpu)
+    A[rows, torch.arange(130, device=gpu)] = 1
+    G0 = torch.from_numpy(rng.standard_normal((r, h_out)).astype(np.float32)).to(gpu)
+    Pt, Gt = dad.compress_rank(A, D, r, 1, G0, check=True)
+    ref = Gt.cpu().numpy().astype(np.float64) @ D[rows].float().cpu().numpy().astype(np.float64).T
+    assert O.rel_fro(Pt.cpu().numpy(), ref) <= 1e-7
+
+
 # wide fp32 rows: thin_nn adds sums of 64 columns (16 matrix instructions) and of its waves.  An application is four
 # contractions of about 1.2e-7 each, 3e-7 for the pair's product; one running sum over a wave's share of a row is at 6.5e-7
 @pytest.mark.parametrize("N,h_in,h_out,r", [(186, 4096, 4096, 35), (64, 4096, 4096, 16), (128, 6000, 5000, 4), (187, 4093, 4090, 35)])
