@@ -136,11 +136,27 @@ def test_reduction_edges(gpu, dtype, N, h_in, h_out, r):
     assert torch.equal(Pt, Pt2) and torch.equal(Gt, Gt2)
 
 
-# a wide panel is shared by waves with rows of their own from N > 8160 on: fp32 from 33 columns, bf16 from 49
+# a wide panel is shared by waves with rows of their own from N > 8192 on: fp32 from 33 columns, bf16 from 49
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,h_in,h_out,r", [(8160, 90, 130, 33), (8161, 90, 130, 33), (8161, 131, 100, 49), (8193, 70, 72, 64), (12290, 130, 90, 48)])
 def test_reduction_wide_panels(gpu, dtype, N, h_in, h_out, r):
     test_reduction_edges(gpu, dtype, N, h_in, h_out, r)
+
+
+# 512 tiles of 16 rows are one round of two-tile workgroups: their waves keep sharing the columns
+@pytest.mark.parametrize("dtype,r", [("f32", 33), ("f32", 64), ("bf16", 64)])
+@pytest.mark.parametrize("N,tall", [(8161, False), (8192, False), (8193, True)])
+def test_wide_panels_of_one_round_of_workgroups(gpu, dtype, r, N, tall):
+    A, D = dev(np.ones((N, 130), np.float32), dtype, gpu), dev(np.ones((N, 130), np.float32), dtype, gpu)
+    G0 = torch.ones((r, 130), device=gpu)
+    dad.profile_enable(True)
+    try:
+        dad.profile_reset()
+        dad.compress_rank(A, D, r, 1, G0)
+        names = dad.profile_read()
+    finally:
+        dad.profile_enable(False)
+    assert ("k_thin_nn_tall" in names) == tall and ("k_thin_nn_direct" in names) == (not tall)
 
 
 # V = Delta G by itself: A picks 128 rows of it, which the contraction over rows then copies exactly.  The rows' sums are added up as
