@@ -551,14 +551,30 @@ bool rebuild_fast_ok(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt) {
     return dt == DAD_BF16 && K * h_in >= 8 && K * h_out >= 8;
 }
 
-// K chunks of the register-staged kernel, by a time in us.  A stage takes 0.32 us and up to 0.1 more as the units fill, 0.67 for
-// two workgroups of a unit; more than one chunk adds the slab traffic and the launch that sums it.
-static SplitPlan rebuild_any_split(int64_t K, int64_t h_in, int64_t h_out) {
-    const int64_t tiles = ceil_div(h_in, ra::TILE) * ceil_div(h_out, ra::TILE);
+// Most K chunks of the register-staged kernel.  Every chunk is a slab of the workspace, and a workspace that was large enough for a
+// product stays large enough: the limit is what paid at 3 us and 0.5 us per 64 rows of a round of two workgroups per unit, which is
+// what the size query goes by.  36 shapes, without it and with it: mostly alike, 15224 x 3602 x 1237 245 and 263 us (four more slabs of
+// 18 MB), 743 x 128 x 1269 13 and 16, 13131 x 4375 x 2343 507 and 435.
+static int64_t rebuild_any_slabs(int64_t K, int64_t tiles, int64_t h_in, int64_t h_out) {
     double best_t = 0.0;
     int64_t best = 1;
     for (int64_t s = 1; s <= 64; ++s) {
         if (s > 1 && K / s < 4 * rb::BK) break;
+        const double stages = (double)ceil_div(ceil_div(K, s), 2 * rb::BK);
+        double t = (double)ceil_div(tiles * s, 2 * CU_COUNT) * (3.0 + 0.5 * stages);
+        if (s > 1) t += 4.0 + (2.0 * s + 1.0) * h_in * h_out * 4.0 / 4e6;
+        if (s == 1 || t < best_t * 0.98) best_t = t, best = s;
+    }
+    return ceil_div(K, (int64_t)align_up((size_t)ceil_div(K, best), 2 * rb::BK));
+}
+
+// K chunks of the register-staged kernel, by a time in us.  A stage takes 0.32 us and up to 0.1 more as the units fill, 0.67 for
+// two workgroups of a unit; more than one chunk adds the slab traffic and the launch that sums it.
+static SplitPlan rebuild_any_split(int64_t K, int64_t h_in, int64_t h_out) {
+    const int64_t tiles = ceil_div(h_in, ra::TILE) * ceil_div(h_out, ra::TILE), most = rebuild_any_slabs(K, tiles, h_in, h_out);
+    double best_t = 0.0;
+    int64_t best = 1;
+    for (int64_t s = 1; s <= most; ++s) {
         const double stages = (double)ceil_div(ceil_div(K, s), rb::BK), wg = (double)(tiles * s);
         const double stage = wg <= CU_COUNT ? 0.32 + 0.1 * wg / CU_COUNT : 0.67 * (double)ceil_div(tiles * s, 2 * CU_COUNT);
         double t = 6.0 + stages * stage;

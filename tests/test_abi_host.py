@@ -158,6 +158,13 @@ def test_reconstruct_workspace_is_whole_slabs(lib, dt):
             assert rest == 0 and slabs != 1
 
 
+# a workspace that was enough for a bf16 product of any width stays enough, and none where none was needed
+@pytest.mark.parametrize("K,h_in,h_out,slabs", [(743, 128, 1269, 0), (993, 3328, 99, 0), (20142, 4800, 2857, 0), (1152, 2101, 3072, 0),
+                                                (3772, 1280, 15, 20), (7030, 239, 1092, 10), (13000, 1000, 1000, 6), (8192, 1300, 2052, 2)])
+def test_bf16_products_of_any_width_ask_for_no_more_slabs(lib, K, h_in, h_out, slabs):
+    assert lib.dad_reconstruct_workspace_bytes(K, h_in, h_out, dad.DAD_BF16) <= slabs * h_in * h_out * 4
+
+
 # more slabs than the time of a product needs are not asked for
 @pytest.mark.parametrize("K,h_in,h_out,slabs", [(97792, 2432, 874, 8), (90119, 7296, 5504, 0), (75465, 6400, 7552, 0), (30000, 784, 1024, 7)])
 def test_fp32_products_ask_for_few_slabs(lib, K, h_in, h_out, slabs):
