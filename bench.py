@@ -454,7 +454,8 @@ def sequential(args, w, dad, W, torch, np, dev):
     """Algorithm 2 one singular pair at a time (dad_compress_rank_sequential) on the stacked factors
     of ONE block of the model (its distinct layer shapes): r components x (4 n_iter + 2) thin passes,
     each over a whole factor, or, for a layer the library iterates on its gradient, r x (n_iter + 1)
-    passes over that (fp32, built once from the factors), r x n_iter more where its rows are too wide for one workgroup.
+    passes over that (fp32, built once from the factors), r x n_iter more where its rows are too wide for one workgroup or the
+    workspace has no room for what one launch leaves to the next.
     A step is one pass over that block; the metric is the time per layer,
     to be read beside compress_us_per_layer of the default mode (the block form of the same method)."""
     tdt = torch.bfloat16 if w.dtype == "bf16" else torch.float32
@@ -501,8 +502,9 @@ def sequential(args, w, dad, W, torch, np, dev):
         for k, v in one.items():
             kern[k] = (kern[k][0] + v[0], kern[k][1] + v[1]) if k in kern else (v[0], v[1])
         if any(k.startswith("k_rebuild") and v[1] > 0 for k, v in one.items()):
-            # k_seq_product takes both products of an application from one read of the gradient
-            reads = r * (n_iter + 1) if one.get("k_seq_product", (0, 0))[1] > 0 else passes
+            # k_seq_product takes both products of an application from one read of the gradient where no launch follows it
+            one_read = one.get("k_seq_product", (0, 0))[1] > 0 and one.get("k_thin_tn_direct", (0, 0))[1] == 0
+            reads = r * (n_iter + 1) if one_read else passes
             moved = float(reads) * hi * ho * 4
             bytes_ += moved + float(N) * (hi + ho) * es + hi * ho * 4.0
             on_gradient += 1

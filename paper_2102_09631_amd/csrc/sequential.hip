@@ -239,9 +239,14 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
 // A whole call, 768 x 768, N = 4096, 8 components, two applications: 66 launches and 434 us with a launch per product, update, start
 // and end; 27 and 200 us so (a launch 7 to 8 us).  300 x 3999: 684 -> 479; 3999 x 200, 16 components: 737 -> 379; 1024 x 4096,
 // N = 300, 16 components: 1470 -> 1090; 4096 x 4096, four components: 843 -> 830 (M itself takes most of it).
+// PAIR: two launches per application, where the workspace, which was sized for a launch per step, has no room for the slabs.  This one takes M g
+// alone, with every unit, and k_thin_tn_direct M^T of that; the next one adds the slabs of that launch, which fit where they always were.  With two
+// running vectors in turn in place of peels each workgroup forms the peel for itself, and a launch ends the component.
+// N = 64, 784 x 128, 4 components: 165 us with a launch per step, 138 so (76 with slabs); N = 4096, 3072 x 768, 8 components: 453, 360 (268);
+// N = 300, 1024 x 4096, 16 components: 1455, 1083 (1096).
 // Rows wider than SEQ_ROW_MOST, and the adaptive mode (its stop test sits between an update and the next product), keep a launch per step.
-// Column layout: thread c of a group holds columns at .. at + 3, at = min(4 c, h_out - 4), and those of the thread before it count
-// as zero in g; slabs and peel are kept by thread, 4 c + e.
+// Column layout: thread c of a group holds columns at .. at + 3, at = min(4 c, h_out - 4); those of the thread before it count
+// as zero in g and have the same values in both otherwise.
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_b4 __attribute__((aligned(4)));
@@ -249,21 +254,23 @@ typedef f32x4 f32x4_b4 __attribute__((aligned(4)));
 constexpr int SEQ_SLABS = 64;           // at most (64 units read M faster than the launch takes); each workgroup reads them all
 constexpr int64_t SEQ_ROW_MOST = 4096;  // columns of one workgroup: 1024 threads of four
 constexpr int SEQ_ROWS = 4;             // rows of a group in flight, twice
+constexpr int SEQ_UNITS = CU_COUNT - 1;  // workgroups of rows of the PAIR form, one to a unit with the books
 
 enum { SEQ_FIRST = 1, SEQ_LAST = 2 };  // the launch that starts a component, the one that ends its iteration
 
 struct SeqProduct {
     const float* M;
     const float* x;       // start vector (first launch)
-    const float* slabs;   // of the application before, `blocks` of them
-    const double* peel;
+    const float* slabs;   // of the application before, `nslabs` of them
+    const double* peel;   // and the peel of its vector, or (PAIR) that vector
+    const float* g_before;
     float* slabs_out;
     double* peel_out;
-    float* p;             // M g (last launch)
-    float* g;             // the running vector, as the last launch leaves it
+    float* p;             // M g (last launch; PAIR: every one, and zeros behind it up to h_pad)
+    float* g;             // the running vector, as the last launch leaves it (PAIR: every one)
     float *Qt, *sGt, *sigma;
     int* hdr;
-    int h_in, h_out, j, blocks, batches, mode, clear_hdr;
+    int h_in, h_pad, h_out, j, blocks, batches, nslabs, mode, clear_hdr;
 };
 
 // Thread groups of a workgroup; their threads (whole waves).
@@ -272,9 +279,10 @@ static int seq_groups(int64_t h_out) {
     const int n = seq_lanes(h_out);
     return n <= 128 ? 8 : n <= 256 ? 4 : n <= 512 ? 2 : 1;
 }
-static int seq_batches(int64_t h_in, int64_t h_out) { return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * SEQ_SLABS); }
-static int seq_blocks(int64_t h_in, int64_t h_out) {
-    return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * seq_batches(h_in, h_out));
+// Batches of rows of a workgroup, of at most `most` workgroups; their number.
+static int seq_batches(int64_t h_in, int64_t h_out, int most) { return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * most); }
+static int seq_blocks(int64_t h_in, int64_t h_out, int most) {
+    return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * seq_batches(h_in, h_out, most));
 }
 
 // v[i], i < 4, summed over the wave: lane l returns the sum of v[l & 3].
@@ -290,13 +298,13 @@ template <typename T> __device__ __forceinline__ T wave_sum4(const T (&v)[4]) {
     return s;
 }
 
-template <int G>
+template <int G, bool PAIR>
 __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ double sums[2][16][4];  // per wave
     const int n = blockDim.x / G, grp = threadIdx.x / n, c = threadIdx.x - grp * n;  // n: threads of a group, whole waves
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wpg = n >> 6, w0 = grp * wpg;
-    const int h = a.h_out, pitch = 4 * n;
+    const int h = a.h_out;
     const int at = 4 * c < h - 4 ? 4 * c : h - 4;
     bool own[4];
 #pragma unroll
@@ -320,24 +328,79 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
     // the vector: every group has all of it
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     double(*red)[4] = reinterpret_cast<double(*)[4]>(smem);  // [threadIdx.x]
+    // peel of x: sum over the found pairs of sG_i (sG_i . x), the groups taking four pairs at a time in turn; for the first group
+    // (PAIR: for all)
+    auto peel_of = [&](const float(&x)[4], double(&z)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = 0.0;
+        for (int i0 = 0, turn = 0; i0 < a.j; i0 += 4 * G, turn ^= 1) {
+            const int i1 = i0 + 4 * grp;
+            f32x4 sg[4];
+            double d[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sg[u] = *reinterpret_cast<const f32x4_b4*>(a.sGt + (int64_t)(i1 + u < a.j ? i1 + u : 0) * h + at);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                d[u] = 0.0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) d[u] += (double)sg[u][e] * (double)x[e];
+            }
+            const double t = wave_sum4(d);
+            if (turn == 0) __syncthreads();  // every reader of the buffer's last contents is done
+            if (lane < 4) sums[turn][wave][lane] = t;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                double s = 0.0;
+                for (int w = 0; w < wpg; ++w) s += sums[turn][w0 + w][u];
+                if (i1 + u < a.j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z[e] += s * (double)sg[u][e];
+            }
+        }
+        __syncthreads();
+        if constexpr (G > 1) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = z[e];
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                z[e] = red[c][e];
+#pragma unroll
+                for (int q = 1; q < G; ++q) z[e] += red[q * n + c][e];
+            }
+            if constexpr (PAIR) __syncthreads();
+        }
+    };
     if (first) {
         const f32x4 x = *reinterpret_cast<const f32x4_b4*>(a.x + at);
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = (double)x[e];
     } else {
         constexpr int P = G < 8 ? 16 : 8;  // slabs in flight: mostly all of a group
-        const float* src = a.slabs + 4 * c;
+        const float* src = a.slabs + at;
         double z[4];
+        if constexpr (PAIR) {
+            float x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) z[e] = a.peel[4 * c + e];
-        for (int b = grp; b < a.blocks; b += P * G) {
+            for (int e = 0; e < 4; ++e) x[e] = own[e] ? a.g_before[at + e] : 0.f;
+            if (a.j > 0)
+                peel_of(x, z);
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z[e] = 0.0;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z[e] = a.peel[at + e];
+        }
+        for (int b = grp; b < a.nslabs; b += P * G) {
             f32x4 t[P];
 #pragma unroll
-            for (int u = 0; u < P; ++u) t[u] = *reinterpret_cast<const f32x4*>(src + (int64_t)(b + u * G < a.blocks ? b + u * G : a.blocks - 1) * pitch);
+            for (int u = 0; u < P; ++u) t[u] = *reinterpret_cast<const f32x4_b4*>(src + (int64_t)(b + u * G < a.nslabs ? b + u * G : a.nslabs - 1) * h);
 #pragma unroll
             for (int u = 0; u < P; ++u)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += b + u * G < a.blocks ? (double)t[u][e] : 0.0;
+                for (int e = 0; e < 4; ++e) v[e] += b + u * G < a.nslabs ? (double)t[u][e] : 0.0;
         }
         if constexpr (G > 1) {
 #pragma unroll
@@ -392,7 +455,7 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
                 double s = 0.0;
                 for (int w = 0; w < wpg; ++w) s += sums[(b + 1) & 1][w0 + w][i];
                 const float x = r0 + i < a.h_in ? (float)s : 0.f;
-                if (last) {
+                if (PAIR || last) {
                     if (c == 0 && r0 + i < a.h_in) a.p[r0 + i] = x;
                 } else {
 #pragma unroll
@@ -408,7 +471,7 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
                 rows(s1, b + 1);
             }
         }
-        if (last) return;
+        if (PAIR || last) return;
         f32x4* ysum = reinterpret_cast<f32x4*>(smem);
         if constexpr (G > 1) {
             ysum[threadIdx.x] = y;  // the sums over slabs were read before the barriers above
@@ -417,12 +480,13 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
             for (int q = 1; q < G; ++q)
                 if (grp == 0) y += ysum[q * n + c];
         }
-        if (grp == 0) *reinterpret_cast<f32x4*>(a.slabs_out + (int64_t)blockIdx.x * pitch + 4 * c) = y;
+        if (grp == 0 && 4 * c < h) *reinterpret_cast<f32x4_b4*>(a.slabs_out + (int64_t)blockIdx.x * h + at) = y;
         return;
     }
 
     // the books
-    if (first && a.j > 0) {  // sigma = ||p||, q = p / sigma and sG = sigma g of the component before
+    if (PAIR && (int)threadIdx.x < a.h_pad - a.h_in) a.p[a.h_in + threadIdx.x] = 0.f;
+    if (!PAIR && first && a.j > 0) {  // sigma = ||p||, q = p / sigma and sG = sigma g of the component before
         double t = 0.0;
         for (int k = threadIdx.x; k < a.h_in; k += blockDim.x) t += (double)a.p[k] * (double)a.p[k];
         t = wave_sum(t);
@@ -444,65 +508,30 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
         __threadfence_block();
         __syncthreads();
     }
-    if (last) {
+    if (PAIR || last) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (grp == 0 && own[e]) a.g[at + e] = g[e];
         return;
     }
-    // peel: sum over the found pairs of sG_i (sG_i . g), the groups taking four pairs at a time in turn
-    double z[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int i0 = 0, turn = 0; i0 < a.j; i0 += 4 * G, turn ^= 1) {
-        const int i1 = i0 + 4 * grp;
-        f32x4 sg[4];
-        double d[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) sg[u] = *reinterpret_cast<const f32x4_b4*>(a.sGt + (int64_t)(i1 + u < a.j ? i1 + u : 0) * h + at);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            d[u] = 0.0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) d[u] += (double)sg[u][e] * (double)g[e];
-        }
-        const double t = wave_sum4(d);
-        if (turn == 0) __syncthreads();  // every reader of the buffer's last contents is done
-        if (lane < 4) sums[turn][wave][lane] = t;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            double s = 0.0;
-            for (int w = 0; w < wpg; ++w) s += sums[turn][w0 + w][u];
-            if (i1 + u < a.j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) z[e] += s * (double)sg[u][e];
-        }
-    }
-    if constexpr (G > 1) {
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = z[e];
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            z[e] = red[c][e];
-#pragma unroll
-            for (int q = 1; q < G; ++q) z[e] += red[q * n + c][e];
-        }
-    }
+    double z[4];
+    peel_of(g, z);
     if (grp == 0)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a.peel_out[4 * c + e] = z[e];
+        for (int e = 0; e < 4; ++e)
+            if (own[e]) a.peel_out[at + e] = z[e];
 }
 
+template <bool PAIR>
 static dad_status seq_product(const SeqProduct& a, hipStream_t s) {
     const int groups = seq_groups(a.h_out), threads = groups * seq_lanes(a.h_out), lds = groups > 1 ? threads * 32 : 0;
     const dim3 grid((unsigned)a.blocks + 1);
     ProfScope prof(KID_SEQ_PRODUCT, s);
     switch (groups) {
-        case 8: hipLaunchKernelGGL(k_seq_product<8>, grid, dim3(threads), lds, s, a); break;
-        case 4: hipLaunchKernelGGL(k_seq_product<4>, grid, dim3(threads), lds, s, a); break;
-        case 2: hipLaunchKernelGGL(k_seq_product<2>, grid, dim3(threads), lds, s, a); break;
-        default: hipLaunchKernelGGL(k_seq_product<1>, grid, dim3(threads), lds, s, a); break;
+        case 8: hipLaunchKernelGGL((k_seq_product<8, PAIR>), grid, dim3(threads), lds, s, a); break;
+        case 4: hipLaunchKernelGGL((k_seq_product<4, PAIR>), grid, dim3(threads), lds, s, a); break;
+        case 2: hipLaunchKernelGGL((k_seq_product<2, PAIR>), grid, dim3(threads), lds, s, a); break;
+        default: hipLaunchKernelGGL((k_seq_product<1, PAIR>), grid, dim3(threads), lds, s, a); break;
     }
     DAD_LAUNCH_CHECK();
     return DAD_OK;
@@ -520,7 +549,8 @@ struct SeqPlan {
     size_t total;
     bool dense;        // some number of components is faster on the gradient: the workspace holds it
     bool fused;        // and a workgroup holds its rows: k_seq_product
-    size_t slab_bytes, peel_bytes;  // of one application: two of each over the slabs M was made from, which are done with by then
+    bool pair;         // two launches per application: no room for
+    size_t slab_bytes, peel_bytes;  // those of one application, two of each over the slabs M was made from, which are done with by then
 };
 
 // The size query knows neither the components nor their applications; from 64 vectors' worth of products on nothing
@@ -536,14 +566,9 @@ static SeqPlan plan_sequential(int64_t N, int64_t h_in, int64_t h_out, dad_dtype
     const size_t factors = p.c.off_Yt + vec;  // nothing is orthonormalised: the layout ends with its Yt
     p.off_panel = p.dense && p.d.total > factors ? p.d.total : factors;
     p.fused = p.dense && h_out >= 4 && h_out <= SEQ_ROW_MOST;
-    p.slab_bytes = p.peel_bytes = 0;
-    if (p.fused) {
-        const size_t pitch = 4 * (size_t)seq_lanes(h_out);
-        p.slab_bytes = (size_t)seq_blocks(h_in, h_out) * pitch * 4;
-        p.peel_bytes = pitch * 8;
-        const size_t end = align_up(p.d.off_slabs + 2 * (p.slab_bytes + p.peel_bytes), 256);
-        if (end > p.off_panel) p.off_panel = end;
-    }
+    p.peel_bytes = align_up((size_t)h_out * 8, 256);
+    p.slab_bytes = p.fused ? align_up((size_t)seq_blocks(h_in, h_out, SEQ_SLABS) * h_out * 4, 256) : 0;
+    p.pair = p.d.off_slabs + 2 * (p.slab_bytes + p.peel_bytes) > p.off_panel;
     p.total = p.off_panel + vec;
     return p;
 }
@@ -624,8 +649,35 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
         SeqProduct a = {};
         char* const slabs = ws + p.d.off_slabs;
         char* const peels = slabs + 2 * p.slab_bytes;
+        const int most = p.pair ? SEQ_UNITS : SEQ_SLABS;
         a.M = M, a.p = static_cast<float*>(V), a.g = panel, a.Qt = Qt, a.sGt = sGt, a.sigma = sigma, a.hdr = hdr;
-        a.h_in = (int)h_in, a.h_out = (int)h_out, a.blocks = seq_blocks(h_in, h_out), a.batches = seq_batches(h_in, h_out);
+        a.h_in = (int)h_in, a.h_pad = (int)direct_npad(h_in), a.h_out = (int)h_out;
+        a.blocks = seq_blocks(h_in, h_out, most), a.batches = seq_batches(h_in, h_out, most);
+        auto end = [&](int j, const float* g) {
+            ProfScope prof(KID_SEQ_VECTOR, s);
+            hipLaunchKernelGGL(k_seq_finish, dim3(1), dim3(1024), 0, s, p_vec, g, Qt + (int64_t)j * h_in, sGt + (int64_t)j * h_out,
+                               sigma ? sigma + j : (float*)nullptr, h_in, h_out, hdr, j, theta, eff_rank);
+            DAD_LAUNCH_CHECK();
+            return DAD_OK;
+        };
+        if (p.pair) {
+            float* const vectors[2] = {panel, Ut};
+            const int splits = c.tn_out.splits;
+            a.slabs = splits == 1 ? Yt : part, a.nslabs = splits;
+            const TnJob product = {M, a.p, splits == 1 ? Yt : part, h_in, c.tn_out.chunk, (int)h_out, splits};
+            for (int j = 0; j < r; ++j) {
+                for (int it = 0; it <= n_iter; ++it) {
+                    a.j = j, a.mode = it == 0 ? SEQ_FIRST : 0, a.clear_hdr = j == 0 && it == 0;
+                    a.x = G0 + (int64_t)j * h_out;
+                    a.g = vectors[it & 1], a.g_before = vectors[(it & 1) ^ 1];
+                    DAD_TRY(seq_product<true>(a, s));
+                    if (it < n_iter) DAD_TRY(direct_tn(&product, 1, 1, DAD_F32, s, nullptr));
+                }
+                DAD_TRY(end(j, a.g));
+            }
+            return DAD_OK;
+        }
+        a.nslabs = a.blocks;
         for (int j = 0; j < r; ++j)
             for (int it = 0; it <= n_iter; ++it) {
                 a.j = j, a.mode = (it == 0 ? SEQ_FIRST : 0) | (it == n_iter ? SEQ_LAST : 0), a.clear_hdr = j == 0 && it == 0;
@@ -635,14 +687,9 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
                 a.peel = reinterpret_cast<const double*>(peels + from * p.peel_bytes);
                 a.slabs_out = reinterpret_cast<float*>(slabs + to * p.slab_bytes);
                 a.peel_out = reinterpret_cast<double*>(peels + to * p.peel_bytes);
-                DAD_TRY(seq_product(a, s));
+                DAD_TRY(seq_product<false>(a, s));
             }
-        ProfScope prof(KID_SEQ_VECTOR, s);
-        const int j = r - 1;
-        hipLaunchKernelGGL(k_seq_finish, dim3(1), dim3(1024), 0, s, p_vec, (const float*)panel, Qt + (int64_t)j * h_in,
-                           sGt + (int64_t)j * h_out, sigma ? sigma + j : (float*)nullptr, h_in, h_out, hdr, j, theta, eff_rank);
-        DAD_LAUNCH_CHECK();
-        return DAD_OK;
+        return end(r - 1, panel);
     }
     for (int j = 0; j < r; ++j) {
         {

@@ -179,6 +179,13 @@ def test_sequential_workspace_is_the_gradient_and_vectors(lib, N, h_in, h_out, d
     assert need <= (1 + slabs) * h_in * h_out * 4 + 4 * (2 * N + 40 * (h_in + h_out)) + (1 << 20)
 
 
+# a workspace that was enough for the recurrence stays enough
+@pytest.mark.parametrize("N,h_in,h_out,dt,was", [(300, 33, 40, 0, 6656), (64, 784, 128, 0, 408576), (21, 9, 256, 0, 12800), (600, 300, 515, 0, 626688), (1188, 3682, 256, 0, 3803904),
+                                                 (4096, 3072, 768, 1, 9495808), (900, 70, 4095, 1, 1199616), (95, 615, 1664, 1, 4116224), (20142, 4800, 2857, 1, 55022848), (4096, 768, 768, 1, 11809024)])
+def test_sequential_workspace_asks_for_no_more(lib, N, h_in, h_out, dt, was):
+    assert lib.dad_compress_sequential_workspace_bytes(N, h_in, h_out, dt) <= was
+
+
 def test_grouped_compress_rejects_bad_arguments_on_host(lib):
     p = 0x1000
     D = dad.CompressDesc
