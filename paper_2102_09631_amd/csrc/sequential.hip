@@ -234,16 +234,16 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
 // The next launch starts with what a launch of its own did before: every workgroup adds the slabs, subtracts the peel and
 // normalises, all in fp64 and alike, while its rows of M are on their way.  One workgroup more than the rows need keeps the
 // books: it ends the component before, forms the peel of the running vector for the next launch, and latches the status.
-// What bounds it: latency (a launch, the slabs' round trip through the memory side, two barriers per batch of rows), which is why the
-// slabs are few (SEQ_SLABS) and the threads are split into G groups that take slabs and rows in turn.
-// A whole call, 768 x 768, N = 4096, 8 components, two applications: 66 launches and 434 us with a launch per product, update, start
-// and end; 27 and 200 us so (a launch 7 to 8 us).  300 x 3999: 684 -> 479; 3999 x 200, 16 components: 737 -> 379; 1024 x 4096,
-// N = 300, 16 components: 1470 -> 1090; 4096 x 4096, four components: 843 -> 830 (M itself takes most of it).
-// PAIR: two launches per application, where the workspace, which was sized for a launch per step, has no room for the slabs.  This one takes M g
+// What bounds it: latency (a launch, the slabs' round trip through the memory side, a barrier per batch of rows), which is why the slabs are
+// few (SEQ_SLABS) and the threads are split into G groups that take slabs and rows in turn.
+// A whole call, 768 x 768, N = 4096, 8 components, two applications: 72 launches beside those that make M, 434 us, with a launch per
+// product, update, start and end; 25 and 200 us so (a launch 7 to 8 us).
+// PAIR: two launches per application, where the workspace, which was sized for a launch per step, has no room for the slabs, or
+// where M is long for 64 workgroups (seq_slabs_win).  This one takes M g
 // alone, with every unit, and k_thin_tn_direct M^T of that; the next one adds the slabs of that launch, which fit where they always were.  With two
 // running vectors in turn in place of peels each workgroup forms the peel for itself, and a launch ends the component.
 // N = 64, 784 x 128, 4 components: 165 us with a launch per step, 138 so (76 with slabs); N = 4096, 3072 x 768, 8 components: 453, 360 (268);
-// N = 300, 1024 x 4096, 16 components: 1455, 1083 (1096).
+// N = 300, 1024 x 4096, 16 components: 1455, 1083 (1096); N = 32768, 16384 x 4096, 8 components: 6465, 5806 (8255).
 // Rows wider than SEQ_ROW_MOST, and the adaptive mode (its stop test sits between an update and the next product), keep a launch per step.
 // Column layout: thread c of a group holds columns at .. at + 3, at = min(4 c, h_out - 4); those of the thread before it count
 // as zero in g and have the same values in both otherwise.
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef f32x4 f32x4_b4 __attribute__((aligned(4)));
 
-constexpr int SEQ_SLABS = 64;           // at most (64 units read M faster than the launch takes); each workgroup reads them all
+constexpr int SEQ_SLABS = 64;           // at most; each workgroup reads them all
 constexpr int64_t SEQ_ROW_MOST = 4096;  // columns of one workgroup: 1024 threads of four
 constexpr int SEQ_ROWS = 4;             // rows of a group in flight, twice
 constexpr int SEQ_UNITS = CU_COUNT - 1;  // workgroups of rows of the PAIR form, one to a unit with the books
@@ -283,6 +283,16 @@ static int seq_groups(int64_t h_out) {
 static int seq_batches(int64_t h_in, int64_t h_out, int most) { return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * most); }
 static int seq_blocks(int64_t h_in, int64_t h_out, int most) {
     return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * seq_batches(h_in, h_out, most));
+}
+
+// 64 workgroups read M at 1.7 TB/s (a batch of theirs, 4 MB, 2.4 us), against 5 to 6 TB/s of two launches on all units.  Whole calls, N = 4096, two
+// applications, 4 and 16 components, slabs and PAIR: 8192 x 1024 (8 batches) 328 and 355, 1050 and 1195 us; 12288 x 1024 453 and 447, 1450 and 1476; 4096 x 2048
+// (8) 341 and 354, 1100 and 1211; 12288 x 256 (6) 188 and 205, 24576 x 256 (12) 299 and 294, 24576 x 128 279 and 262, 957 and 912.  Rows of one group also
+// make wide slabs: 512 x 3072 (2) 192 and 202, 728 and 821; 1024 x 2304 (4) 217 and 202, 748 and 781; 512 x 4096 (2) 237 and 230, 911 and 960;
+// 1024 x 3072 (4) 252 and 226, 883 and 888; 1024 x 4096 311 and 270, 1102 and 1090.
+static bool seq_slabs_win(int64_t h_in, int64_t h_out) {
+    const int64_t batches = seq_batches(h_in, h_out, SEQ_SLABS);
+    return seq_groups(h_out) > 1 ? batches <= 8 : batches * h_out <= 9216;
 }
 
 // v[i], i < 4, summed over the wave: lane l returns the sum of v[l & 3].
@@ -549,7 +559,7 @@ struct SeqPlan {
     size_t total;
     bool dense;        // some number of components is faster on the gradient: the workspace holds it
     bool fused;        // and a workgroup holds its rows: k_seq_product
-    bool pair;         // two launches per application: no room for
+    bool pair;         // two launches per application: faster, or no room for
     size_t slab_bytes, peel_bytes;  // those of one application, two of each over the slabs M was made from, which are done with by then
 };
 
@@ -568,7 +578,7 @@ static SeqPlan plan_sequential(int64_t N, int64_t h_in, int64_t h_out, dad_dtype
     p.fused = p.dense && h_out >= 4 && h_out <= SEQ_ROW_MOST;
     p.peel_bytes = align_up((size_t)h_out * 8, 256);
     p.slab_bytes = p.fused ? align_up((size_t)seq_blocks(h_in, h_out, SEQ_SLABS) * h_out * 4, 256) : 0;
-    p.pair = p.d.off_slabs + 2 * (p.slab_bytes + p.peel_bytes) > p.off_panel;
+    p.pair = !seq_slabs_win(h_in, h_out) || p.d.off_slabs + 2 * (p.slab_bytes + p.peel_bytes) > p.off_panel;
     p.total = p.off_panel + vec;
     return p;
 }
