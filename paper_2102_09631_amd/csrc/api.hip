@@ -132,7 +132,8 @@ DensePlan plan_dense(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt
 
 // Both sides in microseconds.  A product on the factors is two launches over Delta and A and, as one of the two
 // contractions runs over rows, mostly a slab sum; on M it is one launch.  A launch of the direct kernels takes 4 us and
-// its matrix's bytes at 5 TB/s.  M costs the launch and its flops at the rate of the kernel that makes it.
+// its matrix's bytes at 5 TB/s.  M costs the launch and its flops at the rate of the kernel that makes it, in bf16 of ragged widths that of
+// the one before it: workspaces are sized by this rule and don't grow with a faster kernel.
 bool dense_wins(int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt, int64_t products) {
     if (!direct_ok(h_in, h_out, dt)) return false;  // the guarded kernels
     const double flops = 2.0 * N * h_in * h_out, both = (double)N * (h_in + h_out) * elem_size(dt);

@@ -548,8 +548,8 @@ static dad_status seq_product(const SeqProduct& a, hipStream_t s) {
 }
 
 // The recurrence is a chain of short launches, and a product with M = A^T Delta is one of them where a product with
-// the factors is two and a slab sum: M is made first wherever dense_wins says so.  768 x 768, N = 4096, bf16, 8
-// components: 624 us on the factors, 444 us on M (of which M 20 us).
+// the factors is two and a slab sum: M is made first wherever seq_dense_wins says so.  768 x 768, N = 4096, bf16, 8
+// components: 624 us on the factors, 198 us on M (of which M 20 us).
 // The workspace holds the layout of the route taken, products on the factors (c) or on the gradient (d), and behind
 // it the running vector (h_out fp32).
 struct SeqPlan {
@@ -583,6 +583,23 @@ static SeqPlan plan_sequential(int64_t N, int64_t h_in, int64_t h_out, dad_dtype
     return p;
 }
 
+// Whether a call whose workspace holds M makes it.  The adaptive mode asks for one component's first products for certain (dense_wins).
+// Fixed counts, in microseconds: on the factors a product as in dense_wins and a vector launch at the start, the end and after each
+// application; on M the launches of k_seq_product's two forms.  149 shapes (128 to 40000 rows, widths 48 to 4500, 1 to 16
+// components, both types) timed on both routes: the calls take 0.3 % more than with the faster one each time, 3.1 % with the products alone
+// counted, two launches each, and ragged bf16 products at 0.25e9 flops per us.  N = 4974, 3023 x 469, one component: 150 us on the factors, 79 on M.
+static bool seq_dense_wins(const SeqPlan& p, int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt, int r, int n_iter, bool adaptive) {
+    if (!p.dense) return false;
+    if (adaptive || !p.fused) return dense_wins(N, h_in, h_out, dt, adaptive ? 5 : (int64_t)r * (2 * (int64_t)n_iter + 1));
+    const bool whole = N >= 256 && h_in % 128 == 0 && h_out % 128 == 0;
+    const double rate = dt == DAD_F32 ? 0.8e8 : whole ? 0.8e9 : 0.4e9;  // flops per us
+    const double h = (double)h_out, bytes = (double)h_in * h * 4.0, both = (double)N * (h_in + h) * elem_size(dt), n = n_iter;
+    const double factors = r * ((2.0 * n + 1.0) * (8.0 + both / 5e6 + (N > 256 ? 2.5 : 0.0)) + (n + 2.0) * (4.0 + 2e-3 * h));
+    const double pair = (n + 1.0) * (6.0 + 1e-3 * h + bytes / 5e6) + n * (5.0 + bytes / 5e6) + 5.0;
+    const double slabs = (n + 1.0) * (4.0 + 2.2e-3 * h + bytes / 2.2e6);
+    return 12.0 + 2.0 * N * h_in * h / rate + r * (p.pair ? pair : slabs) < 0.95 * factors;
+}
+
 }  // namespace dad
 
 using namespace dad;
@@ -604,9 +621,8 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
                                     float* Qt, float* sGt, float* sigma, int* eff_rank, int* iters, void* workspace,
                                     hipStream_t s) {
     char* ws = static_cast<char*>(workspace);
-    // The products asked for for certain: all of them, or one component's first ones in the adaptive mode.
     const bool adaptive = theta >= 0.f;
-    const bool dense = p.dense && dense_wins(N, h_in, h_out, dt, adaptive ? 5 : (int64_t)r * (2 * (int64_t)n_iter + 1));
+    const bool dense = seq_dense_wins(p, N, h_in, h_out, dt, r, n_iter, adaptive);
     const CompressPlan& c = dense ? p.d.m : p.c;
     int* hdr = reinterpret_cast<int*>(ws + c.off_flag);
     void* V = ws + c.off_V;

@@ -165,6 +165,28 @@ def test_sequential_forms_of_the_products(gpu, pair, N, h_in, h_out, r, n_iter, 
     check(out, "f32", 4 * np.finfo(np.float32).eps * (sv[0] / sv[r - 1]) ** 2)  # as above
 
 
+# which matrices a call multiplies with, on either side of the cost: few components, M of ragged widths, fp32 factors
+@pytest.mark.parametrize("N,h_in,h_out,r,n_iter,dtype,on_m", [
+    (4974, 3023, 469, 1, 2, "bf16", True), (704, 1351, 1030, 2, 2, "bf16", True), (8192, 2049, 2049, 4, 2, "bf16", True), (452, 3152, 1429, 4, 2, "f32", True),
+    (9041, 4352, 896, 1, 2, "f32", False), (712, 3840, 2304, 1, 2, "f32", False), (11543, 1992, 2469, 1, 2, "bf16", False)])
+def test_sequential_route_by_cost(gpu, N, h_in, h_out, r, n_iter, dtype, on_m):
+    rng = np.random.default_rng([29, N, h_in, h_out])
+    A, D = (to_dev(rng.standard_normal((N, h), dtype=np.float32), dtype, gpu) for h in (h_in, h_out))
+    G0 = torch.from_numpy(rng.standard_normal((r, h_out), dtype=np.float32)).to(gpu)
+    dad.profile_enable(True)
+    try:
+        dad.profile_reset()
+        Qt, sGt, sigma = dad.compress_rank_sequential(A, D, r, n_iter, G0, check=True)
+        names = dad.profile_read()
+    finally:
+        dad.profile_enable(False)
+    assert ("k_seq_product" in names) == on_m
+    # p = M g and sigma q = p, whichever way M was applied; fp32 sums of N products and of h_out
+    M = A.double().T @ D.double()
+    g = sGt.double() / sigma.double()[:, None]
+    assert O.rel_fro((sigma.double()[:, None] * Qt.double()).cpu().numpy(), (g @ M.T).cpu().numpy()) <= 1e-5
+
+
 def test_sequential_converges_to_truncated_svd(gpu):
     """With a planted gap and enough iterations the pairs are the leading singular triplets:
     the product equals the truncated SVD (Eckart-Young optimum) and sigma the singular values."""
