@@ -241,9 +241,9 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
 // PAIR: two launches per application, where the workspace, which was sized for a launch per step, has no room for the slabs, or
 // where M is long for 64 workgroups (seq_slabs_win).  This one takes M g
 // alone, with every unit, and k_thin_tn_direct M^T of that; the next one adds the slabs of that launch, which fit where they always were.  With two
-// running vectors in turn in place of peels each workgroup forms the peel for itself, and a launch ends the component.
-// N = 64, 784 x 128, 4 components: 165 us with a launch per step, 138 so (76 with slabs); N = 4096, 3072 x 768, 8 components: 453, 360 (268);
-// N = 300, 1024 x 4096, 16 components: 1455, 1083 (1096); N = 32768, 16384 x 4096, 8 components: 6465, 5806 (8255).
+// running vectors in turn in place of peels each workgroup forms the peel for itself.
+// N = 64, 784 x 128, 4 components: 167 us with a launch per step, 135 so (75 with slabs); N = 4096, 3072 x 768, 8 components: 463, 342 (269);
+// N = 300, 1024 x 4096, 16 components: 1517, 1017 (1089); N = 32768, 16384 x 4096, 8 components: 6605, 5798 (8372).
 // Rows wider than SEQ_ROW_MOST, and the adaptive mode (its stop test sits between an update and the next product), keep a launch per step.
 // Column layout: thread c of a group holds columns at .. at + 3, at = min(4 c, h_out - 4); those of the thread before it count
 // as zero in g and have the same values in both otherwise.
@@ -262,11 +262,12 @@ struct SeqProduct {
     const float* M;
     const float* x;       // start vector (first launch)
     const float* slabs;   // of the application before, `nslabs` of them
-    const double* peel;   // and the peel of its vector, or (PAIR) that vector
-    const float* g_before;
+    const double* peel;   // and the peel of its vector
+    const float* g_before;  // the running vector of the launch before (PAIR; first launch: of the component before)
+    const float* p_before;  // M g of the component before (first launch)
     float* slabs_out;
     double* peel_out;
-    float* p;             // M g (last launch; PAIR: every one, and zeros behind it up to h_pad)
+    float* p;             // M g (last launch; PAIR: every one, with zeros from h_in to h_pad)
     float* g;             // the running vector, as the last launch leaves it (PAIR: every one)
     float *Qt, *sGt, *sigma;
     int* hdr;
@@ -286,13 +287,13 @@ static int seq_blocks(int64_t h_in, int64_t h_out, int most) {
 }
 
 // 64 workgroups read M at 1.7 TB/s (a batch of theirs, 4 MB, 2.4 us), against 5 to 6 TB/s of two launches on all units.  Whole calls, N = 4096, two
-// applications, 4 and 16 components, slabs and PAIR: 8192 x 1024 (8 batches) 328 and 355, 1050 and 1195 us; 12288 x 1024 453 and 447, 1450 and 1476; 4096 x 2048
-// (8) 341 and 354, 1100 and 1211; 12288 x 256 (6) 188 and 205, 24576 x 256 (12) 299 and 294, 24576 x 128 279 and 262, 957 and 912.  Rows of one group also
-// make wide slabs: 512 x 3072 (2) 192 and 202, 728 and 821; 1024 x 2304 (4) 217 and 202, 748 and 781; 512 x 4096 (2) 237 and 230, 911 and 960;
-// 1024 x 3072 (4) 252 and 226, 883 and 888; 1024 x 4096 311 and 270, 1102 and 1090.
+// applications, 4 and 16 components, slabs and PAIR: 8192 x 1024 (8 batches) 325 and 337, 1046 and 1112 us; 12288 x 1024 444 and 421, 1445 and 1353; 4096 x 2048
+// (8) 339 and 338, 1094 and 1133; 16384 x 512 (8) 295 and 334; 12288 x 256 (6) 186 and 208, 24576 x 256 (12) 295 and 298, 24576 x 128 279 and 271.  Rows of one
+// group also make wide slabs: 768 x 3072 (3) 222 and 225, 796 and 885; 1024 x 2304 (4) 215 and 192, 747 and 730; 512 x 4096 (2) 237 and 221, 907 and 915;
+// 1024 x 3072 (4) 251 and 215, 881 and 835; 1024 x 4096 306 and 255, 1102 and 1025.
 static bool seq_slabs_win(int64_t h_in, int64_t h_out) {
     const int64_t batches = seq_batches(h_in, h_out, SEQ_SLABS);
-    return seq_groups(h_out) > 1 ? batches <= 8 : batches * h_out <= 9216;
+    return seq_groups(h_out) > 1 ? batches <= 8 : batches <= 3 && batches * h_out <= 9216;
 }
 
 // v[i], i < 4, summed over the wave: lane l returns the sum of v[l & 3].
@@ -496,9 +497,9 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
 
     // the books
     if (PAIR && (int)threadIdx.x < a.h_pad - a.h_in) a.p[a.h_in + threadIdx.x] = 0.f;
-    if (!PAIR && first && a.j > 0) {  // sigma = ||p||, q = p / sigma and sG = sigma g of the component before
+    if (first && a.j > 0) {  // sigma = ||p||, q = p / sigma and sG = sigma g of the component before
         double t = 0.0;
-        for (int k = threadIdx.x; k < a.h_in; k += blockDim.x) t += (double)a.p[k] * (double)a.p[k];
+        for (int k = threadIdx.x; k < a.h_in; k += blockDim.x) t += (double)a.p_before[k] * (double)a.p_before[k];
         t = wave_sum(t);
         if (lane == 0) sums[1][wave][0] = t;
         __syncthreads();
@@ -512,8 +513,8 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
         const double is = sigma > 0.0 ? 1.0 / sigma : 0.0;
         float* q_row = a.Qt + (int64_t)(a.j - 1) * a.h_in;
         float* sg_row = a.sGt + (int64_t)(a.j - 1) * h;
-        for (int k = threadIdx.x; k < a.h_in; k += blockDim.x) q_row[k] = (float)((double)a.p[k] * is);
-        for (int k = threadIdx.x; k < h; k += blockDim.x) sg_row[k] = (float)(sigma * (double)a.g[k]);
+        for (int k = threadIdx.x; k < a.h_in; k += blockDim.x) q_row[k] = (float)((double)a.p_before[k] * is);  // PAIR: in place
+        for (int k = threadIdx.x; k < h; k += blockDim.x) sg_row[k] = (float)(sigma * (double)a.g_before[k]);
         if (a.sigma && threadIdx.x == 0) a.sigma[a.j - 1] = (float)sigma;
         __threadfence_block();
         __syncthreads();
@@ -595,7 +596,7 @@ static bool seq_dense_wins(const SeqPlan& p, int64_t N, int64_t h_in, int64_t h_
     const double rate = dt == DAD_F32 ? 0.8e8 : whole ? 0.8e9 : 0.4e9;  // flops per us
     const double h = (double)h_out, bytes = (double)h_in * h * 4.0, both = (double)N * (h_in + h) * elem_size(dt), n = n_iter;
     const double factors = r * ((2.0 * n + 1.0) * (8.0 + both / 5e6 + (N > 256 ? 2.5 : 0.0)) + (n + 2.0) * (4.0 + 2e-3 * h));
-    const double pair = (n + 1.0) * (6.0 + 1e-3 * h + bytes / 5e6) + n * (5.0 + bytes / 5e6) + 5.0;
+    const double pair = (n + 1.0) * (6.0 + 1e-3 * h + bytes / 5e6) + n * (5.0 + bytes / 5e6);
     const double slabs = (n + 1.0) * (4.0 + 2.2e-3 * h + bytes / 2.2e6);
     return 12.0 + 2.0 * N * h_in * h / rate + r * (p.pair ? pair : slabs) < 0.95 * factors;
 }
@@ -677,9 +678,10 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
         char* const peels = slabs + 2 * p.slab_bytes;
         const int most = p.pair ? SEQ_UNITS : SEQ_SLABS;
         a.M = M, a.p = static_cast<float*>(V), a.g = panel, a.Qt = Qt, a.sGt = sGt, a.sigma = sigma, a.hdr = hdr;
-        a.h_in = (int)h_in, a.h_pad = (int)direct_npad(h_in), a.h_out = (int)h_out;
+        a.h_in = a.h_pad = (int)h_in, a.h_out = (int)h_out;
         a.blocks = seq_blocks(h_in, h_out, most), a.batches = seq_batches(h_in, h_out, most);
-        auto end = [&](int j, const float* g) {
+        auto end = [&](const float* g) {
+            const int j = r - 1;
             ProfScope prof(KID_SEQ_VECTOR, s);
             hipLaunchKernelGGL(k_seq_finish, dim3(1), dim3(1024), 0, s, p_vec, g, Qt + (int64_t)j * h_in, sGt + (int64_t)j * h_out,
                                sigma ? sigma + j : (float*)nullptr, h_in, h_out, hdr, j, theta, eff_rank);
@@ -687,22 +689,25 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
             return DAD_OK;
         };
         if (p.pair) {
+            // p of a component waits for its end in its row of Qt, as the next one's first launch writes V already
             float* const vectors[2] = {panel, Ut};
             const int splits = c.tn_out.splits;
             a.slabs = splits == 1 ? Yt : part, a.nslabs = splits;
-            const TnJob product = {M, a.p, splits == 1 ? Yt : part, h_in, c.tn_out.chunk, (int)h_out, splits};
-            for (int j = 0; j < r; ++j) {
+            const TnJob product = {M, static_cast<const float*>(V), splits == 1 ? Yt : part, h_in, c.tn_out.chunk, (int)h_out, splits};
+            for (int j = 0; j < r; ++j)
                 for (int it = 0; it <= n_iter; ++it) {
+                    const bool waits = it == n_iter && j + 1 < r;
                     a.j = j, a.mode = it == 0 ? SEQ_FIRST : 0, a.clear_hdr = j == 0 && it == 0;
                     a.x = G0 + (int64_t)j * h_out;
-                    a.g = vectors[it & 1], a.g_before = vectors[(it & 1) ^ 1];
+                    a.p = waits ? Qt + (int64_t)j * h_in : static_cast<float*>(V), a.h_pad = (int)(waits ? h_in : direct_npad(h_in));
+                    a.p_before = j > 0 ? Qt + (int64_t)(j - 1) * h_in : nullptr;
+                    a.g = vectors[it & 1], a.g_before = vectors[(it == 0 ? n_iter : it - 1) & 1];
                     DAD_TRY(seq_product<true>(a, s));
                     if (it < n_iter) DAD_TRY(direct_tn(&product, 1, 1, DAD_F32, s, nullptr));
                 }
-                DAD_TRY(end(j, a.g));
-            }
-            return DAD_OK;
+            return end(a.g);
         }
+        a.p_before = a.p, a.g_before = a.g;
         a.nslabs = a.blocks;
         for (int j = 0; j < r; ++j)
             for (int it = 0; it <= n_iter; ++it) {
@@ -715,7 +720,7 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
                 a.peel_out = reinterpret_cast<double*>(peels + to * p.peel_bytes);
                 DAD_TRY(seq_product<false>(a, s));
             }
-        return end(r - 1, panel);
+        return end(panel);
     }
     for (int j = 0; j < r; ++j) {
         {
