@@ -72,7 +72,7 @@ constexpr int BK = 64;              // contraction columns per stage (128 B of e
 // SRC is `const bf16_t*` (one allocation) or RowBlocks (the sites' blocks in place; a workgroup's
 // rows lie in one block because every block holds a multiple of 256 rows).
 // SHARES (factors of few rows): the walk over the contraction columns is summed in four shares of its stages, (s0 + s1) +
-// (s2 + s3), whatever the launch.  KS = 1: a workgroup of W waves takes them one after the other.  KS = 2, 4: as many groups of
+// (s2 + s3), whatever the launch; up to two stages are one share, as they are without SHARES.  KS = 1: a workgroup of W waves takes them one after the other.  KS = 2, 4: as many groups of
 // W waves each take a half or a share at the same time and are summed through LDS: W = 1, 2 by itself leaves a compute unit with
 // too few loads in flight (two stages of 4 KiB of rows per wave) and too long a walk.  1024 x 768, r = 16: 7.7 us a launch with
 // one wave per 32 rows, 5.8 with four.
@@ -115,9 +115,9 @@ __global__ __launch_bounds__(64 * W * KS) void k_thin_nn_bf16_dma(const SRC X, c
     // common offset maps to when the row pitch is a large power of two.  The start depends on the rows, not on the workgroup size, so that a row's sum
     // is taken in the same order whatever W the launch uses.
     static_assert(KS == 1 || SHARES, "a group takes whole shares");
-    const int share = (nk + 3) / 4, mine = share * (4 / KS);  // stages; the last groups may have fewer or none
+    const int share = nk <= 2 ? nk : (nk + 3) / 4, mine = share * (4 / KS);  // stages; the last groups may have fewer or none
     const int kbeg = group * mine < nk ? group * mine : nk;
-    const int nown = nk - kbeg < mine ? nk - kbeg : mine, steps = KS == 1 ? nk : mine;
+    const int nown = nk - kbeg < mine ? nk - kbeg : mine, steps = mine < nk ? mine : nk;
     int kidx = (int)(((unsigned)(n0 / 256) * 5u + (unsigned)kbeg) % (unsigned)nk);
 
     const char* gx[4];
@@ -543,16 +543,17 @@ dad_status dma_thin_nn(const void* X, const RowBlocks* xb, const void* Pb, void*
     // 8192 x 1024 x 4096, r = 32, 326 -> 304 with two and 280 with four groups, but two layers of 8192 x 1024 on two lanes 271 -> 262
     // with two and 273 with four.  At 16384 rows a lone layer gains 2 % and an encoder block on four lanes loses 1 %: one group,
     // unless the rows are those of a batch (four sites of 4096 x 768 x 3072: 274 us before, 262 with two groups).
-    // SHARES goes by one job's rows, so that a job of a batch adds in the order of a call of its own.
+    // SHARES goes by one job's rows, so that a job of a batch adds in the order of a call of its own.  Not for two stages of columns: groups without any
+    // and the additions only cost (two layers of 9984 x 128 x 128, r = 64, in one launch 203 us without shares, 228 in two groups).
 #define DAD_NN_W(W, KS, SHARES) \
     (r <= 32 ? dma_thin_nn_cfg<32, W, KS, SHARES, 3>(X, xb, Pb, out, N, h, r, planes, jobs, job_stride, s) \
              : dma_thin_nn_cfg<64, W, KS, SHARES, 3>(X, xb, Pb, out, N, h, r, planes, jobs, job_stride, s))
-    const bool shares = N / 64 < want;
+    const bool shares = N / 64 < want && h > 2 * nn::BK;
     if (rows / 256 >= want) return shares ? DAD_NN_W(8, 1, true) : DAD_NN_W(8, 1, false);
     if (rows / 128 >= want) return shares ? DAD_NN_W(4, 1, true) : DAD_NN_W(4, 1, false);
     if (rows / 64 >= want) return shares ? DAD_NN_W(2, 2, true) : DAD_NN_W(2, 1, false);
-    if (rows / 32 >= want) return DAD_NN_W(1, 2, true);
-    return DAD_NN_W(1, 4, true);
+    if (!shares) return DAD_NN_W(1, 1, false);
+    return rows / 32 >= want ? DAD_NN_W(1, 2, true) : DAD_NN_W(1, 4, true);
 #undef DAD_NN_W
 }
 
@@ -622,9 +623,9 @@ dad_status thin_prepare_device() {
 #define DAD_NN_ATTR(RP, W, KS, SHARES)                                                                                 \
     DAD_HIP_TRY(set_max_lds((k_thin_nn_bf16_dma<RP, W, KS, SHARES, 3, const bf16_t*>), nn_dma_lds(RP, W, KS, 3))); \
     DAD_HIP_TRY(set_max_lds((k_thin_nn_bf16_dma<RP, W, KS, SHARES, 3, RowBlocks>), nn_dma_lds(RP, W, KS, 3)))
-    DAD_NN_ATTR(32, 1, 4, true); DAD_NN_ATTR(32, 1, 2, true); DAD_NN_ATTR(32, 2, 2, true); DAD_NN_ATTR(32, 2, 1, false); DAD_NN_ATTR(32, 4, 1, true); DAD_NN_ATTR(32, 4, 1, false);
+    DAD_NN_ATTR(32, 1, 4, true); DAD_NN_ATTR(32, 1, 2, true); DAD_NN_ATTR(32, 1, 1, false); DAD_NN_ATTR(32, 2, 2, true); DAD_NN_ATTR(32, 2, 1, false); DAD_NN_ATTR(32, 4, 1, true); DAD_NN_ATTR(32, 4, 1, false);
     DAD_NN_ATTR(32, 8, 1, true); DAD_NN_ATTR(32, 8, 1, false);
-    DAD_NN_ATTR(64, 1, 4, true); DAD_NN_ATTR(64, 1, 2, true); DAD_NN_ATTR(64, 2, 2, true); DAD_NN_ATTR(64, 2, 1, false); DAD_NN_ATTR(64, 4, 1, true); DAD_NN_ATTR(64, 4, 1, false);
+    DAD_NN_ATTR(64, 1, 4, true); DAD_NN_ATTR(64, 1, 2, true); DAD_NN_ATTR(64, 1, 1, false); DAD_NN_ATTR(64, 2, 2, true); DAD_NN_ATTR(64, 2, 1, false); DAD_NN_ATTR(64, 4, 1, true); DAD_NN_ATTR(64, 4, 1, false);
     DAD_NN_ATTR(64, 8, 1, true); DAD_NN_ATTR(64, 8, 1, false);
 #undef DAD_NN_ATTR
 #define DAD_TN_ATTR(R, PW, BK)                                                                              \

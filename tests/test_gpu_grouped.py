@@ -460,3 +460,16 @@ def test_shares_of_a_contraction_do_not_depend_on_the_batch(gpu, N, count, hi, h
     A, D, G0 = layers[-1]
     ref = O.rank_r_grad(*O.block_spi(A.float().cpu().numpy(), D.float().cpu().numpy(), G0.cpu().numpy(), 2))
     assert O.rel_fro(dad.reconstruct_grad(Pts[-1], Gts[-1]).cpu().numpy(), ref) <= 2e-2  # as above
+
+
+# widths of two stages are one share, also in a launch whose widest job has four
+@pytest.mark.parametrize("r", [16, 64])
+@pytest.mark.parametrize("N", [256, 2048, 4096, 9984])
+@pytest.mark.parametrize("widths", [[(128, 128), (128, 128)], [(128, 640), (640, 128), (128, 128)], [(128, 256), (384, 128)]])
+def test_narrow_layers_of_a_batch(gpu, N, widths, r):
+    layers = [_layer(N, hi, ho, r, 740 + i, gpu, torch.bfloat16) for i, (hi, ho) in enumerate(widths)]
+    single = [dad.compress_rank(A, D, r, 2, G0, check=True) for A, D, G0 in layers]
+    Pts, Gts = dad.CompressGroup(layers, r, 2, lanes=1).run(check=True)
+    torch.cuda.synchronize()
+    for (p1, g1), p2, g2 in zip(single, Pts, Gts):
+        assert torch.equal(p1, p2) and torch.equal(g1, g2)
