@@ -388,7 +388,7 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = (double)x[e];
     } else {
-        constexpr int P = G < 8 ? 16 : 8;  // slabs in flight: mostly all of a group
+        constexpr int P = G < 8 ? 16 : 8;  // slabs in flight: all of a group's from G = 4 on
         const float* src = a.slabs + at;
         double z[4];
         if constexpr (PAIR) {

@@ -327,7 +327,8 @@ __global__ __launch_bounds__(256) void k_thin_tn_bf16_dma(const SRC X, const bf1
     }
     // Workgroups are handed to the eight XCDs round-robin by their linear index.  Each XCD takes a contiguous run of
     // (row chunk, column strip) pairs, so that the strips that share a chunk of V read it through one L2, or two where a chunk crosses
-    // the end of a run.
+    // the end of a run.  That is with eight chunks or more; with fewer a chunk is longer than a run and is read through 8 / chunks of them and
+    // up to one more.
     const int pairs = strips * splits, turn = blockIdx.x & 7, run = pairs >> 3, more = pairs & 7;
     const int id = turn * run + (turn < more ? turn : more) + ((int)blockIdx.x >> 3);
     const int split = id / strips, strip = id - split * strips;
