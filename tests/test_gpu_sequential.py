@@ -252,3 +252,29 @@ def test_sequential_replays_from_a_hip_graph(gpu):
         torch.cuda.synchronize()
         for x, y in zip((Qt, sGt, sig), ref):
             assert torch.equal(x, y)
+
+
+# the test above is of the form with two launches per application; this one of that with one
+def test_sequential_with_slabs_replays_from_a_hip_graph(gpu):
+    rng = np.random.default_rng(30)
+    N, h_in, h_out, r = 2000, 33, 40, 5
+    A, D = (torch.from_numpy(rng.standard_normal((N, h)).astype(np.float32)).to(gpu) for h in (h_in, h_out))
+    G0 = torch.from_numpy(rng.standard_normal((r, h_out)).astype(np.float32)).to(gpu)
+    ws = torch.empty(dad.lib().dad_compress_sequential_workspace_bytes(N, h_in, h_out, dad.DAD_F32), dtype=torch.uint8, device=gpu)
+    out = dad.compress_rank_sequential(A, D, r, 2, G0, workspace=ws)
+    torch.cuda.synchronize()
+    ref = [x.clone() for x in out]
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            dad.compress_rank_sequential(A, D, r, 2, G0, Qt=out[0], sGt=out[1], sigma=out[2], workspace=ws)
+    for _ in range(3):
+        for x in out:
+            x.zero_()
+        ws.fill_(0xFF)  # nothing of an earlier call is read
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(out, ref):
+            assert torch.equal(x, y)
