@@ -242,8 +242,8 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
 // where M is long for 64 workgroups (seq_slabs_win).  This one takes M g
 // alone, with every unit, and k_thin_tn_direct M^T of that; the next one adds the slabs of that launch, which fit where they always were.  With two
 // running vectors in turn in place of peels each workgroup forms the peel for itself.
-// N = 64, 784 x 128, 4 components: 167 us with a launch per step, 135 so (75 with slabs); N = 4096, 3072 x 768, 8 components: 463, 342 (269);
-// N = 300, 1024 x 4096, 16 components: 1517, 1017 (1089); N = 32768, 16384 x 4096, 8 components: 6605, 5798 (8372).
+// N = 64, 784 x 128, 4 components: 155 us with a launch per step, 119 so (79 with slabs); N = 4096, 3072 x 768, 8 components: 435, 310 (270);
+// N = 300, 1024 x 4096, 16 components: 1507, 973 (1097); N = 32768, 16384 x 4096, 8 components: 6654, 5860 (8458).
 // Rows wider than SEQ_ROW_MOST, and the adaptive mode (its stop test sits between an update and the next product), keep a launch per step.
 // Column layout: thread c of a group holds columns at .. at + 3, at = min(4 c, h_out - 4); those of the thread before it count
 // as zero in g and have the same values in both otherwise.
@@ -286,14 +286,14 @@ static int seq_blocks(int64_t h_in, int64_t h_out, int most) {
     return (int)ceil_div(h_in, (int64_t)SEQ_ROWS * seq_groups(h_out) * seq_batches(h_in, h_out, most));
 }
 
-// 64 workgroups read M at 1.7 TB/s (a batch of theirs, 4 MB, 2.4 us), against 5 to 6 TB/s of two launches on all units.  Whole calls, N = 4096, two
-// applications, 4 and 16 components, slabs and PAIR: 8192 x 1024 (8 batches) 325 and 337, 1046 and 1112 us; 12288 x 1024 444 and 421, 1445 and 1353; 4096 x 2048
-// (8) 339 and 338, 1094 and 1133; 16384 x 512 (8) 295 and 334; 12288 x 256 (6) 186 and 208, 24576 x 256 (12) 295 and 298, 24576 x 128 279 and 271.  Rows of one
-// group also make wide slabs: 768 x 3072 (3) 222 and 225, 796 and 885; 1024 x 2304 (4) 215 and 192, 747 and 730; 512 x 4096 (2) 237 and 221, 907 and 915;
-// 1024 x 3072 (4) 251 and 215, 881 and 835; 1024 x 4096 306 and 255, 1102 and 1025.
+// 64 workgroups read M at 1.7 TB/s (a batch of theirs, 4 MB, 2.4 us), against 5 to 6 TB/s of two launches on all units, and wide rows make
+// wide slabs.  Whole calls, N = 4096, two applications, 4 and 16 components, slabs and PAIR: 8192 x 1024 (8 batches) 324 and 324, 1048 and 1063 us;
+// 12288 x 1024 442 and 401, 1443 and 1292; 3072 x 2048 (6) 278 and 260, 906 and 879; 16384 x 512 (8) 292 and 330; 16384 x 256 (8) 225 and 245, 732 and 829;
+// 24576 x 256 (12) 294 and 300; 24576 x 128 279 and 273.  Rows of one group: 768 x 2304 192 and 188, 686 and 736; 1024 x 2304 216 and 184, 750 and 694;
+// 256 x 3072 167 and 160, 676 and 666; 768 x 3072 225 and 211, 797 and 826; 256 x 4096 202 and 176, 835 and 781; 1024 x 4096 308 and 245, 1100 and 983.
 static bool seq_slabs_win(int64_t h_in, int64_t h_out) {
     const int64_t batches = seq_batches(h_in, h_out, SEQ_SLABS);
-    return seq_groups(h_out) > 1 ? batches <= 8 : batches <= 3 && batches * h_out <= 9216;
+    return seq_groups(h_out) > 1 && batches <= 8 && batches * h_out <= 8192;
 }
 
 // v[i], i < 4, summed over the wave: lane l returns the sum of v[l & 3].
@@ -339,8 +339,8 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
     // the vector: every group has all of it
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     double(*red)[4] = reinterpret_cast<double(*)[4]>(smem);  // [threadIdx.x]
-    // peel of x: sum over the found pairs of sG_i (sG_i . x), the groups taking four pairs at a time in turn; for the first group
-    // (PAIR: for all)
+    // peel of x: sum over the found pairs of sG_i (sG_i . x), the groups taking four pairs at a time in turn; each group's part.  PAIR: nothing was
+    // read from `sums` before
     auto peel_of = [&](const float(&x)[4], double(&z)[4]) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) z[e] = 0.0;
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
                 for (int e = 0; e < 4; ++e) d[u] += (double)sg[u][e] * (double)x[e];
             }
             const double t = wave_sum4(d);
-            if (turn == 0) __syncthreads();  // every reader of the buffer's last contents is done
+            if (turn == 0 && (!PAIR || i0 > 0)) __syncthreads();  // every reader of the buffer's last contents is done
             if (lane < 4) sums[turn][wave][lane] = t;
             __syncthreads();
 #pragma unroll
@@ -369,19 +369,6 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
                     for (int e = 0; e < 4; ++e) z[e] += s * (double)sg[u][e];
             }
         }
-        __syncthreads();
-        if constexpr (G > 1) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = z[e];
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                z[e] = red[c][e];
-#pragma unroll
-                for (int q = 1; q < G; ++q) z[e] += red[q * n + c][e];
-            }
-            if constexpr (PAIR) __syncthreads();
-        }
     };
     if (first) {
         const f32x4 x = *reinterpret_cast<const f32x4_b4*>(a.x + at);
@@ -390,28 +377,33 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
     } else {
         constexpr int P = G < 8 ? 16 : 8;  // slabs in flight: all of a group's from G = 4 on
         const float* src = a.slabs + at;
+        auto slab = [&](int b) -> f32x4 { return *reinterpret_cast<const f32x4_b4*>(src + (int64_t)(b < a.nslabs ? b : a.nslabs - 1) * h); };
         double z[4];
-        if constexpr (PAIR) {
+        if constexpr (PAIR) {  // a few slabs, the first ones on their way during the peel; v is the group's part of both
+            f32x4 t = slab(grp);
             float x[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = own[e] ? a.g_before[at + e] : 0.f;
-            if (a.j > 0)
-                peel_of(x, z);
-            else
+            peel_of(x, z);
+            for (int b = grp; b < a.nslabs; b += G) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) z[e] = 0.0;
+                for (int e = 0; e < 4; ++e) v[e] += (double)t[e];
+                if (b + G < a.nslabs) t = slab(b + G);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] -= z[e];
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) z[e] = a.peel[at + e];
-        }
-        for (int b = grp; b < a.nslabs; b += P * G) {
-            f32x4 t[P];
+            for (int b = grp; b < a.nslabs; b += P * G) {
+                f32x4 t[P];
 #pragma unroll
-            for (int u = 0; u < P; ++u) t[u] = *reinterpret_cast<const f32x4_b4*>(src + (int64_t)(b + u * G < a.nslabs ? b + u * G : a.nslabs - 1) * h);
+                for (int u = 0; u < P; ++u) t[u] = slab(b + u * G);
 #pragma unroll
-            for (int u = 0; u < P; ++u)
+                for (int u = 0; u < P; ++u)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += b + u * G < a.nslabs ? (double)t[u][e] : 0.0;
+                    for (int e = 0; e < 4; ++e) v[e] += b + u * G < a.nslabs ? (double)t[u][e] : 0.0;
+            }
         }
         if constexpr (G > 1) {
 #pragma unroll
@@ -424,8 +416,11 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
                 for (int q = 1; q < G; ++q) v[e] += red[q * n + c][e];
             }
         }
+        if constexpr (!PAIR)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] -= z[e];
+            for (int e = 0; e < 4; ++e) v[e] -= z[e];
+        else if constexpr (G == 1)
+            __syncthreads();  // the peel's sums have been read
     }
     double sq = 0.0;
 #pragma unroll
@@ -527,6 +522,18 @@ __global__ __launch_bounds__(1024) void k_seq_product(const SeqProduct a) {
     }
     double z[4];
     peel_of(g, z);
+    if constexpr (G > 1) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = z[e];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            z[e] = red[c][e];
+#pragma unroll
+            for (int q = 1; q < G; ++q) z[e] += red[q * n + c][e];
+        }
+    }
     if (grp == 0)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -542,7 +549,9 @@ static dad_status seq_product(const SeqProduct& a, hipStream_t s) {
         case 8: hipLaunchKernelGGL((k_seq_product<8, PAIR>), grid, dim3(threads), lds, s, a); break;
         case 4: hipLaunchKernelGGL((k_seq_product<4, PAIR>), grid, dim3(threads), lds, s, a); break;
         case 2: hipLaunchKernelGGL((k_seq_product<2, PAIR>), grid, dim3(threads), lds, s, a); break;
-        default: hipLaunchKernelGGL((k_seq_product<1, PAIR>), grid, dim3(threads), lds, s, a); break;
+        default:
+            if constexpr (!PAIR) return DAD_ERR_SHAPE;  // seq_slabs_win
+            else hipLaunchKernelGGL((k_seq_product<1, PAIR>), grid, dim3(threads), lds, s, a);
     }
     DAD_LAUNCH_CHECK();
     return DAD_OK;
@@ -586,17 +595,18 @@ static SeqPlan plan_sequential(int64_t N, int64_t h_in, int64_t h_out, dad_dtype
 
 // Whether a call whose workspace holds M makes it.  The adaptive mode asks for one component's first products for certain (dense_wins).
 // Fixed counts, in microseconds: on the factors a product as in dense_wins and a vector launch at the start, the end and after each
-// application; on M the launches of k_seq_product's two forms.  149 shapes (128 to 40000 rows, widths 48 to 4500, 1 to 16
-// components, both types) timed on both routes: the calls take 0.3 % more than with the faster one each time, 3.1 % with the products alone
-// counted, two launches each, and ragged bf16 products at 0.25e9 flops per us.  N = 4974, 3023 x 469, one component: 150 us on the factors, 79 on M.
+// application; on M the launches of k_seq_product's two forms.  Of 424 shapes that were faster on M by this rule or one near it (128 to 40000 rows,
+// widths 48 to 4500, 1 to 16 components, both types) none is slower on the route taken by 3 %; with the products alone counted, two launches each,
+// and ragged bf16 products at 0.25e9 flops per us, 149 drawn shapes took 3 % more on average.  N = 4974, 3023 x 469, one component: 150 us on the
+// factors, 79 on M.
 static bool seq_dense_wins(const SeqPlan& p, int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt, int r, int n_iter, bool adaptive) {
     if (!p.dense) return false;
     if (adaptive || !p.fused) return dense_wins(N, h_in, h_out, dt, adaptive ? 5 : (int64_t)r * (2 * (int64_t)n_iter + 1));
     const bool whole = N >= 256 && h_in % 128 == 0 && h_out % 128 == 0;
     const double rate = dt == DAD_F32 ? 0.8e8 : whole ? 0.8e9 : 0.4e9;  // flops per us
     const double h = (double)h_out, bytes = (double)h_in * h * 4.0, both = (double)N * (h_in + h) * elem_size(dt), n = n_iter;
-    const double factors = r * ((2.0 * n + 1.0) * (8.0 + both / 5e6 + (N > 256 ? 2.5 : 0.0)) + (n + 2.0) * (4.0 + 2e-3 * h));
-    const double pair = (n + 1.0) * (6.0 + 1e-3 * h + bytes / 5e6) + n * (5.0 + bytes / 5e6);
+    const double factors = r * ((2.0 * n + 1.0) * (8.0 + both / 5e6 + (N > 256 ? 2.5 : 0.0)) + (n + 2.0) * (4.0 + 1.2e-3 * h));
+    const double pair = (n + 1.0) * (5.0 + 1e-3 * h + bytes / 5e6) + n * (5.0 + bytes / 5e6);
     const double slabs = (n + 1.0) * (4.0 + 2.2e-3 * h + bytes / 2.2e6);
     return 12.0 + 2.0 * N * h_in * h / rate + r * (p.pair ? pair : slabs) < 0.95 * factors;
 }

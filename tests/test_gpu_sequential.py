@@ -134,14 +134,14 @@ def test_sequential_products_on_the_gradient(gpu, N, h_in, h_out, r, n_iter, dty
 
 
 # the same in both forms: one launch per application where the workspace has room for its slabs (many rows: those M was made from) and M is short for 64
-# workgroups (8 batches of rows; in one group of threads 3, and 9216 columns of all batches), two elsewhere.  Every number of thread groups, one to five batches of rows with a short last one, all 64 slabs, the narrowest and the widest rows
+# workgroups (8 batches of rows, 8192 columns of all batches, rows of at most 2048), two elsewhere.  Every number of thread groups, one to five batches of rows with a short last one, all 64 slabs, the narrowest and the widest rows
 @pytest.mark.parametrize("pair,N,h_in,h_out,r,n_iter,dtype", [
     (False, 2000, 33, 40, 9, 2, "f32"), (False, 3000, 40, 4, 3, 2, "f32"), (False, 3000, 5000, 130, 6, 2, "bf16"), (False, 3000, 4096, 130, 5, 1, "bf16"),
     (False, 4000, 8300, 200, 3, 2, "f32"), (False, 4000, 300, 515, 36, 1, "f32"), (False, 4000, 4100, 516, 4, 2, "bf16"),
-    (False, 1500, 530, 1026, 12, 3, "f32"), (False, 3000, 1300, 1028, 4, 2, "bf16"), (False, 3000, 270, 2049, 12, 2, "bf16"),
-    (False, 4096, 700, 2304, 4, 2, "bf16"), (False, 4000, 70, 4096, 6, 2, "bf16"),
-    (False, 4096, 16384, 60, 3, 2, "bf16"), (True, 4096, 16385, 60, 3, 2, "bf16"), (False, 4096, 700, 3070, 4, 2, "bf16"),
-    (True, 4096, 700, 3076, 4, 2, "bf16"), (True, 4096, 900, 2304, 4, 2, "bf16"),
+    (False, 1500, 530, 1026, 12, 3, "f32"), (False, 3000, 1300, 1028, 4, 2, "bf16"), (True, 3000, 270, 2049, 12, 2, "bf16"),
+    (True, 4096, 700, 2304, 4, 2, "bf16"), (True, 4000, 70, 4096, 6, 2, "bf16"),
+    (False, 4096, 16384, 60, 3, 2, "bf16"), (True, 4096, 16385, 60, 3, 2, "bf16"), (False, 8192, 2049, 1600, 3, 2, "bf16"),
+    (True, 8192, 2049, 1700, 3, 2, "bf16"), (False, 3000, 270, 2048, 12, 2, "bf16"),
     (True, 300, 33, 40, 9, 2, "f32"), (True, 24, 40, 4, 2, 2, "f32"), (True, 300, 5000, 60, 4, 2, "f32"), (True, 400, 20000, 37, 3, 3, "f32"),
     (True, 700, 4200, 700, 40, 2, "f32"), (True, 500, 2300, 1030, 5, 2, "f32"), (True, 400, 2300, 2052, 9, 2, "f32"),
     (True, 400, 1100, 4096, 9, 2, "f32"), (True, 900, 70, 4095, 20, 2, "bf16")])
