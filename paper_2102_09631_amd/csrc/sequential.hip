@@ -238,10 +238,10 @@ __global__ __launch_bounds__(1024) void k_seq_finish(const float* __restrict__ p
 // few (SEQ_SLABS) and the threads are split into G groups that take slabs and rows in turn.
 // A whole call, 768 x 768, N = 4096, 8 components, two applications: 72 launches beside those that make M, 434 us, with a launch per
 // product, update, start and end; 25 and 200 us so (a launch 7 to 8 us).
-// PAIR: two launches per application, where the workspace, which was sized for a launch per step, has no room for the slabs, or
-// where M is long for 64 workgroups (seq_slabs_win).  This one takes M g
-// alone, with every unit, and k_thin_tn_direct M^T of that; the next one adds the slabs of that launch, which fit where they always were.  With two
-// running vectors in turn in place of peels each workgroup forms the peel for itself.
+// PAIR: two launches per application, where the workspace, which was sized for a launch per step, has no room for the slabs, or where M is
+// long for 64 workgroups or its rows are wide (seq_slabs_win).  This one takes M g alone, with every unit, and k_thin_tn_direct M^T of that; the
+// next one adds the slabs of that launch, which fit where they always were.  With two running vectors in turn in place of peels each
+// workgroup forms the peel for itself.
 // N = 64, 784 x 128, 4 components: 155 us with a launch per step, 119 so (79 with slabs); N = 4096, 3072 x 768, 8 components: 435, 310 (270);
 // N = 300, 1024 x 4096, 16 components: 1507, 973 (1097); N = 32768, 16384 x 4096, 8 components: 6654, 5860 (8458).
 // Rows wider than SEQ_ROW_MOST, and the adaptive mode (its stop test sits between an update and the next product), keep a launch per step.
