@@ -5,6 +5,8 @@
 
 namespace dad {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // ---------------------------------------------------------------- thin N x h by h x r
 // out[n][j] = sum_k X[n][k] * Pt[j][k]   (V = Delta G and W = A U of Eq. 6); the N x r result is fp32
 // whatever the factors' element type.
@@ -201,20 +203,18 @@ __global__ __launch_bounds__(256) void k_reduce_slabs(JobTable<SumJob, CAP> tb, 
     }
 }
 
-// Large slabs (split-K partials of the gradient rebuild): bandwidth bound, 16 bytes per thread.
-__global__ __launch_bounds__(256) void k_reduce_slabs_wide(const float4* __restrict__ part, float4* __restrict__ out,
-                                                           int64_t n4, int splits) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// Large slabs (split-K partials of the gradient rebuild): bandwidth bound, 16 bytes per thread.  The jobs of a group share a launch (four
+// gradients of 16384 rows, 768 to 3072 wide, with their sums: 236 us with a launch for each, 231).  Eight slabs in flight per thread
+// with a sum for every fourth, the order of the kernel above: 13399 x 768 x 3072, seven slabs, 78 -> 85 us.
+template <int CAP>
+__global__ __launch_bounds__(256) void k_reduce_slabs_wide(JobTable<SumJob, CAP> tb) {
+    const SumJob& jb = tb.j[blockIdx.y];
+    const int64_t n4 = jb.n / 4, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
-    float4 a = part[i];
-    for (int s = 1; s < splits; ++s) {
-        const float4 v = part[(int64_t)s * n4 + i];
-        a.x += v.x;
-        a.y += v.y;
-        a.z += v.z;
-        a.w += v.w;
-    }
-    out[i] = a;
+    const f32x4* part = reinterpret_cast<const f32x4*>(jb.part);
+    f32x4 a = part[i];
+    for (int s = 1; s < jb.splits; ++s) a += part[(int64_t)s * n4 + i];
+    reinterpret_cast<f32x4*>(jb.out)[i] = a;
 }
 
 // ---------------------------------------------------------------- G = L^T R, 64 x 64 tiles, split over K
@@ -338,46 +338,39 @@ dad_status gen_thin_nn(const void* X, const float* Pt, void* out, float* partial
     return reduce_slabs(part, (float*)out, N * r, sp.splits, s, nullptr, skip);
 }
 
-// Sums of at least 2^20 elements without a bf16 copy take 16 bytes per thread.
-static bool reduce_is_wide(const SumJob& j, const int* skip) { return j.n >= (1 << 20) && j.n % 4 == 0 && !j.out_bf16 && !skip; }
+// Sums of at least 2^19 elements without a bf16 copy take 16 bytes per thread (16384 x 768 x 768, fourteen slabs: 36.7 -> 33.5 us with the
+// gradient); with fewer the slabs' latency counts, which the kernel above shares among four waves (8192 x 1024 x 1024, r = 64, six
+// slabs of 65536 elements: whole reduction 263 us, 275).
+static bool reduce_is_wide(const SumJob& j, const int* skip) { return j.n >= (1 << 19) && j.n % 4 == 0 && !j.out_bf16 && !skip; }
 
 dad_status reduce_slabs(const SumJob* jobs, int count, hipStream_t s, const int* skip) {
-    SumJob t[MAX_JOBS];
-    int n = 0;
-    int64_t most = 0;
-    auto flush = [&]() -> dad_status {
-        if (n == 0) return DAD_OK;
-        ProfScope prof(KID_REDUCE, s);
-        const dim3 grid((unsigned)ceil_div(most, 64), (unsigned)n);
-        const auto launch = [&](auto tb, auto cap) {
-            hipLaunchKernelGGL(k_reduce_slabs<decltype(cap)::value>, grid, dim3(256), 0, s, tb, skip);
-        };
-        if (n <= 4)
-            launch_jobs<4>(t, n, launch);
-        else
-            launch_jobs<MAX_JOBS>(t, n, launch);
-        DAD_LAUNCH_CHECK();
-        n = 0;
-        most = 0;
-        return DAD_OK;
-    };
-    for (int i = 0; i < count; ++i) {
-        const SumJob& j = jobs[i];
-        if (reduce_is_wide(j, skip)) {
-            ProfScope prof(KID_REDUCE_WIDE, s);
-            hipLaunchKernelGGL(k_reduce_slabs_wide, dim3((unsigned)ceil_div(j.n / 4, 256)), dim3(256), 0, s,
-                               reinterpret_cast<const float4*>(j.part), reinterpret_cast<float4*>(j.out), j.n / 4, j.splits);
+    for (const bool wide : {true, false}) {
+        for (int i = 0; i < count;) {
+            SumJob t[MAX_JOBS];
+            int n = 0;
+            int64_t most = 0;
+            for (; i < count && n < MAX_JOBS; ++i) {
+                if (reduce_is_wide(jobs[i], skip) != wide) continue;
+                t[n++] = jobs[i];
+                if (jobs[i].n > most) most = jobs[i].n;
+            }
+            if (n == 0) continue;
+            ProfScope prof(wide ? KID_REDUCE_WIDE : KID_REDUCE, s);
+            const dim3 grid((unsigned)ceil_div(most, wide ? 1024 : 64), (unsigned)n);
+            const auto launch = [&](auto tb, auto cap) {
+                if (wide)
+                    hipLaunchKernelGGL(k_reduce_slabs_wide<decltype(cap)::value>, grid, dim3(256), 0, s, tb);
+                else
+                    hipLaunchKernelGGL(k_reduce_slabs<decltype(cap)::value>, grid, dim3(256), 0, s, tb, skip);
+            };
+            if (n <= 4)
+                launch_jobs<4>(t, n, launch);
+            else
+                launch_jobs<MAX_JOBS>(t, n, launch);
             DAD_LAUNCH_CHECK();
-            continue;
-        }
-        t[n++] = j;
-        if (j.n > most) most = j.n;
-        if (n == MAX_JOBS) {
-            const dad_status rc = flush();
-            if (rc != DAD_OK) return rc;
         }
     }
-    return flush();
+    return DAD_OK;
 }
 
 dad_status gen_thin_tn(const void* X, const void* V, float* out_t, float* partials, SplitPlan sp, int64_t N,

@@ -753,10 +753,14 @@ dad_status launch_rebuild_group(int n, const void* const* L, const void* const* 
         }
         DAD_LAUNCH_CHECK();
     }
+    SumJob sums[MAX_JOBS];
+    int m = 0;
     for (int i = 0; i < n; ++i) {
-        if (sp[i].splits == 1) continue;
-        const dad_status rc = reduce_slabs(slabs[i], G[i], h_in[i] * h_out[i], sp[i].splits, s);
+        if (sp[i].splits > 1) sums[m++] = SumJob{slabs[i], G[i], nullptr, h_in[i] * h_out[i], sp[i].splits};
+        if (m < MAX_JOBS && i + 1 < n) continue;
+        const dad_status rc = reduce_slabs(sums, m, s);
         if (rc != DAD_OK) return rc;
+        m = 0;
     }
     return DAD_OK;
 }
