@@ -106,7 +106,8 @@ dad_status dad_stack_factors(int S, const void* const* A_sites, const void* cons
                              const int64_t* rows, int64_t h_in, int64_t h_out, dad_dtype dt,
                              void* A_out, void* D_out, void* stream);
 
-/* Bytes of device workspace dad_compress_rank needs for these sizes (0 on invalid sizes). */
+/* Bytes of device workspace dad_compress_rank needs for these sizes (0 on invalid sizes).  Where the reduction is done on M
+ * (below) that is M and its slabs, within DAD_STATIC_SCRATCH_BYTES wherever the reduction on the factors is. */
 size_t dad_compress_workspace_bytes(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt);
 
 /*
@@ -114,7 +115,9 @@ size_t dad_compress_workspace_bytes(int64_t N, int64_t h_in, int64_t h_out, int 
  * Eq. 5-6) applied to all r start vectors at once.  n_iter times the block
  * G (h_out x r) is replaced by an orthonormal basis of
  *     M^T M G = Delta^T ( A ( A^T ( Delta G ) ) ),
- * evaluated right to left so that neither M nor A A^T is formed; the
+ * evaluated right to left so that neither M nor A A^T is formed, or, for n_iter > 1 and where that takes less
+ * time (many rows, or many launches for little work), as M^T (M G) with M made in the workspace first
+ * (fp32; fp32 intermediates).  Which, depends on N, h_in, h_out, r, dt and n_iter > 1 alone; the
  * orthonormalisation (Cholesky QR in fp64: one round; for the last iterate a
  * second one unless the first factor shows cond(Y) <= 450 r through the upper
  * bound ||R||_F ||R^-1||_F, decided on the device) stands in for
@@ -127,9 +130,10 @@ size_t dad_compress_workspace_bytes(int64_t N, int64_t h_in, int64_t h_out, int 
  *   G0        device, r x h_out fp32: row j is the start vector g_0^j
  *   Pt        device out, r x h_in  fp32: row j is the left vector p_j = M g_j
  *   Gt        device out, r x h_out fp32: rows orthonormal
- *   workspace device, ws_bytes >= dad_compress_workspace_bytes(...)
+ *   workspace device, ws_bytes >= dad_compress_workspace_bytes(...).  A smaller one that holds the reduction on the
+ *             factors (the size this query returned before M was an alternative) is taken, and the reduction is then done on them
  * Outputs have the factor layout (one row per component), so S such pairs can
- * be stacked and compressed again (Algorithm 1).  For dt = DAD_BF16 on shapes of whole tiles (N a
+ * be stacked and compressed again (Algorithm 1).  On the factors, for dt = DAD_BF16 on shapes of whole tiles (N a
  * multiple of 256, widths multiples of 128, r in {16, 32, 64}) the two N x r intermediates travel as
  * bf16 between contractions: Delta G rounded once, A U as two bf16 terms (value and rounding remainder,
  * 16 significand bits: activations with a non-zero mean make one rounding of it too coarse), and the h x r
@@ -170,11 +174,11 @@ dad_status dad_compress_rank_noalloc(const void* A, const void* D, int64_t N, in
  * layer's pair in the same step).  Every layer's Pt, Gt are bit-identical to a single call's; up to
  * `lanes` layers (or batches, below) are in flight at once, each in its own region of the workspace, so
  * that the short, latency-bound launches of one layer run beside another's.  How, depends on the layer:
- *   - fp32 layers and bf16 layers outside the whole-tile sizes below share merged launches on `stream`, as
+ *   - layers that are reduced on M, fp32 layers and bf16 layers outside the whole-tile sizes below share merged launches on `stream`, as
  *     many at a time as they have regions (lanes = 1: one after the other);
  *   - a run of consecutive stacked layers of equal N that the bf16 direct-to-LDS kernels serve (N a
  *     multiple of 256, widths multiples of 128, r in {16, 32, 64}) is executed as a batch of up to 32: every
- *     launch does the same step of all its layers, so the run costs the launches of one layer.  Batched
+ *     launch does the same step of all its layers, so the run costs the launches of one layer (on M, of every eight).  Batched
  *     are layers of equal widths with at most 256 MiB of factors each (typically the S site reductions of
  *     one layer in Algorithm 1, each site's block passed as a layer), and layers of unequal widths, all
  *     multiples of 256, with at most 64 MiB each (the layers of a small block).  A batch takes one lane and

@@ -26,9 +26,11 @@ dad_status launch_panel_init(const float*, void*, void*, int64_t, int64_t, int, 
 dad_status dma_thin_nn(const void*, const RowBlocks*, const void*, void*, int64_t, int64_t, int, int, hipStream_t,
                        int jobs = 1, int64_t job_stride = 0);
 bool rebuild_fast_ok(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt);
-SplitPlan rebuild_fast_split(int64_t K, int64_t h_in, int64_t h_out, int* tile);
+SplitPlan rebuild_fast_split(int64_t K, int64_t h_in, int64_t h_out, int* tile, int most, bool fine);
+ProductTime rebuild_bf16_time(int64_t K, int64_t h_in, int64_t h_out, const RebuildPlan& p);
+ProductTime rebuild_f32_time(int64_t K, int64_t h_in, int64_t h_out);
 dad_status fast_rebuild(const void*, const void*, const RowBlocks*, const RowBlocks*, int64_t, int64_t, int64_t, float*,
-                        float*, SplitPlan, int, hipStream_t);
+                        float*, SplitPlan, int, hipStream_t, bool fine = false);
 bool rebuild_group_ok(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt);
 int rebuild_group_splits(int n, const int64_t* K, const int64_t* h_in, const int64_t* h_out);
 SplitPlan rebuild_group_plan(int64_t K, int splits);
@@ -48,7 +50,7 @@ static SplitPlan split_rows(int64_t rows, int64_t tiles, int64_t target_blocks, 
     return sp;
 }
 
-CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt, size_t part_floor) {
+CompressPlan plan_factors(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt, size_t part_floor) {
     CompressPlan p;
     p.dma = thin_dma_ok(N, h_in, h_out, r, dt);
     p.direct = !p.dma && direct_ok(h_in, h_out, dt);
@@ -108,12 +110,13 @@ CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dt
     return p;
 }
 
-RebuildPlan plan_rebuild(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt) {
+RebuildPlan plan_rebuild(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt, int most, bool fine) {
     RebuildPlan p;
+    p.fine = fine;
     p.fast = rebuild_fast_ok(K, h_in, h_out, dt);
     p.f32 = dt == DAD_F32 && rebuild_f32_ok(h_in, h_out);
     p.tile = 0;
-    p.split = p.fast  ? rebuild_fast_split(K, h_in, h_out, &p.tile)
+    p.split = p.fast  ? rebuild_fast_split(K, h_in, h_out, &p.tile, most, fine)
               : p.f32 ? rebuild_f32_split(K, h_in, h_out)
                       : split_rows(K, ceil_div(h_in, 64) * ceil_div(h_out, 64), 2048, 512, 16);
     p.total = p.split.splits > 1 ? (size_t)p.split.splits * h_in * h_out * 4 : 0;
@@ -122,7 +125,7 @@ RebuildPlan plan_rebuild(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt) {
 
 DensePlan plan_dense(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt) {
     DensePlan p;
-    p.m = plan_compress(h_in, h_out, h_out, r, DAD_F32);
+    p.m = plan_factors(h_in, h_out, h_out, r, DAD_F32);
     p.rb = plan_rebuild(N, h_in, h_out, dt);
     p.off_M = align_up(p.m.off_Yt + (size_t)r * h_out * 4, 256);  // nothing is orthonormalised: the layout ends with its Yt
     p.off_slabs = p.off_M + align_up((size_t)h_in * h_out * 4, 256);
@@ -142,6 +145,62 @@ bool dense_wins(int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt, int64_t pr
     const double thin = products * (2 * 4.0 + both / 5e6 + (N > 256 ? 2.5 : 0.0));
     const double dense = 10.0 + flops / rate + products * (5.0 + (double)h_in * h_out * 4.0 / 5e6);
     return dense < 0.9 * thin;
+}
+
+// One reduction on its own: on the factors, or on M = A^T Delta, made in the workspace first.
+struct RoutePlan {
+    CompressPlan f;      // on the factors
+    bool dense;          // on M, from two applications on; the workspace holds it
+    CompressPlan m;      // of the products with M: its N is h_in, both its widths h_out, its offsets behind M
+    RebuildPlan rb;      // how M is made; its first slab lies in M's own place
+    size_t off_M, total;
+    bool on_M(int n_iter) const { return dense && n_iter > 1; }
+    void to_factors() { dense = false, total = f.total; }  // a workspace without room for M
+};
+
+static bool dense_saves(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt, const RoutePlan& p);
+
+static RoutePlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt) {
+    RoutePlan p = {};
+    p.f = plan_factors(N, h_in, h_out, r, dt);
+    p.total = p.f.total;
+    if (!direct_ok(h_in, h_out, dt) || !direct_ok(h_in, h_out, DAD_F32)) return p;
+    const size_t bytes_M = align_up((size_t)h_in * h_out * 4, 256);
+    // dad_compress_rank_noalloc takes every size that it took on the factors, and gives the same bits
+    const size_t room = p.f.total <= DAD_STATIC_SCRATCH_BYTES ? (size_t)DAD_STATIC_SCRATCH_BYTES : SIZE_MAX;
+    if (256 + bytes_M > room) return p;
+    const int64_t most = (int64_t)((room - 256) / bytes_M);
+    p.rb = plan_rebuild(N, h_in, h_out, dt, most < 64 ? (int)most : 64, !p.f.dma);
+    p.m = plan_factors(h_in, h_out, h_out, r, DAD_F32);
+    p.off_M = 256;
+    for (size_t* o : {&p.m.off_V, &p.m.off_part, &p.m.off_Ut, &p.m.off_Yt, &p.m.off_gram, &p.m.off_rinv, &p.m.off_Gb, &p.m.off_Ub}) *o += bytes_M;
+    const size_t made = p.off_M + (size_t)p.rb.split.splits * bytes_M, used = p.m.total + bytes_M;
+    const size_t total = made > used ? made : used;
+    if (total > room) return p;
+    p.dense = dense_saves(N, h_in, h_out, r, dt, p);
+    if (p.dense && total > p.total) p.total = total;
+    return p;
+}
+
+// Whether two applications (five products with M) take less time on M, in microseconds fitted to 300 shapes timed both ways (64 to 65536 rows,
+// widths 64 to 4096, r 1 to 64, both types; 13399 x 768 x 3072, r = 16, 193 us on the factors and 154 on M, r = 32 272 and 186;
+// 8192 x 1024 x 1024, r = 64, 263 and 169; 17482 x 128 x 2432 175 and 87; 7900 x 2500 x 640 fp32 248 and 314).  By this rule 300 other shapes
+// take 1 / 1.30 of their time, and none of them 5 % more.  A product on the factors is two launches more and reads both
+// factors.  The second line is for a layer of a group: the launches are then shared, and what counts is whose work fills the chip; the third for
+// fp32, where making M is no less work than the products: a group with a layer on the factors has their launches all the same.
+// Not for whole-tile layers of up to 4096 rows: those share the launches of a batch, a region of which is a few hundred KB on the factors.
+static bool dense_saves(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt, const RoutePlan& p) {
+    if (p.f.dma && N <= 4096) return false;
+    const double tiles16 = (double)ceil_div(r, 16);
+    const double mb = (double)N * (h_in + h_out) * elem_size(dt) * 1e-6, mb_M = (double)h_in * h_out * 4e-6;
+    const double launches = 5.0 * (5.2 + (N > 256 ? 2.2 : 0.0));
+    const double per_mb = p.f.dma ? 0.083 + 0.031 * tiles16 : dt == DAD_BF16 ? 0.15 + 0.048 * tiles16 : 0.13 * tiles16;
+    const double full = p.f.dma && mb > 500.0 ? 500.0 : mb;  // the streaming kernels reach 6 TB/s beyond
+    const double bytes = 5.0 * (full * per_mb + (mb - full) * 0.165 - 0.26 * mb_M);
+    const ProductTime t = dt == DAD_F32 ? rebuild_f32_time(N, h_in, h_out) : rebuild_bf16_time(N, h_in, h_out, p.rb);
+    return launches + bytes > 6.0 + t.alone &&
+           (p.f.dma ? 1.0 : 0.33) * (launches - 6.0) + bytes > t.share &&
+           (dt == DAD_BF16 || t.alone - bytes < 12.0);
 }
 
 static bool dtype_ok(dad_dtype dt) { return dt == DAD_F32 || dt == DAD_BF16; }
@@ -196,6 +255,17 @@ dad_status device_ready(void** scratch_out) {
 // Copies the flag word of a workspace header to a caller-owned word.
 __global__ void k_copy_flag(const int* __restrict__ hdr, int* __restrict__ out) { *out = *hdr; }
 
+// r rows of n floats out of rows `pitch` long.
+__global__ void k_copy_rows(const float* __restrict__ from, int64_t pitch, float* __restrict__ to, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) to[blockIdx.y * n + i] = from[blockIdx.y * pitch + i];
+}
+static dad_status copy_rows(const float* from, int64_t pitch, float* to, int64_t n, int r, hipStream_t s) {
+    hipLaunchKernelGGL(k_copy_rows, dim3((unsigned)ceil_div(n, 256), (unsigned)r), dim3(256), 0, s, from, pitch, to, n);
+    DAD_LAUNCH_CHECK();
+    return DAD_OK;
+}
+
 // Grouped compress: the group's sticky flag is cleared at the start of the call; the orthonormalisations of all
 // layers set it.
 __global__ void k_clear_flag(int* __restrict__ flag) { *flag = 0; }
@@ -209,6 +279,7 @@ struct CompressJob {
     float *Pt, *Gt;
     char* ws;    // its workspace region
     int* flag;   // where a breakdown is latched
+    bool on_M = false;  // A is M (h_in x h_out, fp32) and p the plan of the products with it
     int* hdr() const { return reinterpret_cast<int*>(ws + p->off_flag); }
     template <typename T> T* at(size_t off) const { return reinterpret_cast<T*>(ws + off); }
 };
@@ -227,60 +298,87 @@ static QrJob qr_job(const CompressJob& j, const float* Y, float* Ysum, int split
                  splits};
 }
 
-// n <= MAX_DIRECT_JOBS reductions on the direct kernels: every launch does the same step of all of them, and a job's bits
-// are those of a call of its own.  clear (optional): one word the first launch sets to zero.
+// n <= MAX_DIRECT_JOBS reductions on the direct kernels, on their factors (of type dt) or on M: every launch does the same step of all
+// of them, and a job's bits are those of a call of its own.  An application on the factors is V = Delta G, U = A^T V, W = A U,
+// Y = Delta^T W; on M it is U = M G, Y = M^T U, beside the last two of the others.  clear (optional): one word the first
+// launch sets to zero.
 static dad_status direct_compress(const CompressJob* jobs, int n, dad_dtype dt, int r, int n_iter, hipStream_t s,
                                   int* clear = nullptr) {
     dad_status rc;
-    bool first = true;
-    // V <- X * panel: X = Delta with panel G (the start matrices at first), or X = A with panel U
-    auto nn = [&](bool delta) {
+    int factors = 0;
+    for (int i = 0; i < n; ++i) factors += !jobs[i].on_M;
+    const short f32 = dt == DAD_F32;
+    // V <- X * panel.  delta: X = Delta with panel G (the start matrices at first); else X = A with panel U, or M with panel G.
+    // last: P = M G beside the factors' last V = Delta G.
+    auto nn = [&](int it, bool delta, bool last) {
         NnJob t[MAX_DIRECT_JOBS];
+        int m = 0;
         for (int i = 0; i < n; ++i) {
             const CompressJob& j = jobs[i];
-            t[i] = NnJob{delta ? j.D : j.A, !delta ? j.at<float>(j.p->off_Ut) : first ? j.G0 : j.Gt, j.at<float>(j.p->off_V),
-                         j.at<float>(j.p->off_part), first ? j.hdr() : nullptr, j.N, (int)(delta ? j.h_out : j.h_in), (delta ? j.p->nn_out : j.p->nn_in).splits};
+            const CompressPlan& p = *j.p;
+            const float* const G = it == 0 ? j.G0 : j.Gt;
+            float *V = j.at<float>(p.off_V), *part = j.at<float>(p.off_part);
+            if (!j.on_M) {
+                const int cs = (delta ? p.nn_out : p.nn_in).splits;
+                if (delta || !last)
+                    t[m++] = NnJob{delta ? j.D : j.A, delta ? G : j.at<float>(p.off_Ut), V, part, it == 0 && delta ? j.hdr() : nullptr,
+                                   j.N, (int)(delta ? j.h_out : j.h_in), (short)cs, f32, 0, 0};
+            } else if (!delta || last) {
+                const int cs = p.nn_out.splits;
+                const bool straight = last && (cs == 1 || j.h_in % 32 == 0);  // rows of Pt, where slabs and the sum's rows fit them
+                t[m++] = NnJob{j.A, G, straight ? j.Pt : V, part, it == 0 ? j.hdr() : nullptr, j.h_in, (int)j.h_out, (short)cs, 1, 0,
+                               straight && cs == 1 ? (int)j.h_in : 0};
+            }
         }
-        int* const c = first ? clear : nullptr;
-        first = false;
-        return direct_nn(t, n, r, dt, s, nullptr, c);
+        return m == 0 ? DAD_OK : direct_nn(t, m, r, s, nullptr, it == 0 && (delta || factors == 0) ? clear : nullptr);
     };
-    // out <- V^T X, slabs in the partials region where the rows are split; the jobs with `sum` are summed
-    auto tn = [&](bool delta, auto out, auto sum) {
+    // out <- V^T A, slabs in the partials region where the rows are split
+    auto tn_A = [&](bool last) {
         TnJob t[MAX_DIRECT_JOBS];
         SumJob u[MAX_DIRECT_JOBS];
-        int nu = 0;
+        int m = 0, nu = 0;
         for (int i = 0; i < n; ++i) {
             const CompressJob& j = jobs[i];
-            const SplitPlan& sp = delta ? j.p->tn_out : j.p->tn_in;
-            const int h = (int)(delta ? j.h_out : j.h_in);
-            float* part = j.at<float>(j.p->off_part);
-            t[i] = TnJob{delta ? j.D : j.A, j.at<float>(j.p->off_V), sp.splits == 1 ? out(j) : part, j.N, sp.chunk, h, sp.splits};
-            if (sp.splits > 1 && sum(sp.splits)) u[nu++] = SumJob{part, out(j), nullptr, (int64_t)r * h, sp.splits};
+            if (j.on_M) continue;
+            const SplitPlan& sp = j.p->tn_in;
+            float* const out = last ? j.Pt : j.at<float>(j.p->off_Ut);
+            float* const part = j.at<float>(j.p->off_part);
+            t[m++] = TnJob{j.A, j.at<float>(j.p->off_V), sp.splits == 1 ? out : part, j.N, sp.chunk, (int)j.h_in, sp.splits, f32};
+            if (sp.splits > 1) u[nu++] = SumJob{part, out, nullptr, (int64_t)r * j.h_in, sp.splits};
         }
-        const dad_status rc1 = direct_tn(t, n, r, dt, s);
+        const dad_status rc1 = m == 0 ? DAD_OK : direct_tn(t, m, r, s);
         return rc1 == DAD_OK && nu ? reduce_slabs(u, nu, s) : rc1;
     };
-    auto to_U = [](const CompressJob& j) { return j.at<float>(j.p->off_Ut); };
-    auto to_Y = [](const CompressJob& j) { return j.at<float>(j.p->off_Yt); };
-    auto to_P = [](const CompressJob& j) { return j.Pt; };
-    auto all = [](int) { return true; };
     for (int it = 0; it < n_iter; ++it) {
-        DAD_TRY(nn(true));                                                         // V = Delta G
-        DAD_TRY(tn(false, to_U, all));                                             // U = A^T V
-        DAD_TRY(nn(false));                                                        // W = A U
-        DAD_TRY(tn(true, to_Y, [&](int sp) { return !few_slabs(r, sp); }));        // Y = Delta^T W
+        DAD_TRY(nn(it, true, false));   // V = Delta G
+        DAD_TRY(tn_A(false));           // U = A^T V
+        DAD_TRY(nn(it, false, false));  // W = A U;  U = M G
+        TnJob t[MAX_DIRECT_JOBS];
+        SumJob u[MAX_DIRECT_JOBS];
         QrJob q[MAX_DIRECT_JOBS];
-        for (int i = 0; i < n; ++i) {
-            const int sp = jobs[i].p->tn_out.splits;
-            const bool slabs = sp > 1 && few_slabs(r, sp);
-            q[i] = qr_job(jobs[i], slabs ? jobs[i].at<float>(jobs[i].p->off_part) : to_Y(jobs[i]), slabs ? to_Y(jobs[i]) : nullptr,
-                          slabs ? sp : 1, nullptr);
+        int nu = 0;
+        for (int i = 0; i < n; ++i) {  // Y = Delta^T W;  Y = M^T U
+            const CompressJob& j = jobs[i];
+            const SplitPlan& sp = j.p->tn_out;
+            float *part = j.at<float>(j.p->off_part), *Y = j.at<float>(j.p->off_Yt);
+            const bool slabs = sp.splits > 1, few = few_slabs(r, sp.splits);
+            t[i] = TnJob{j.on_M ? j.A : j.D, j.at<float>(j.p->off_V), slabs ? part : Y, j.on_M ? j.h_in : j.N, sp.chunk, (int)j.h_out, sp.splits,
+                         j.on_M ? (short)1 : f32};
+            if (slabs && !few) u[nu++] = SumJob{part, Y, nullptr, (int64_t)r * j.h_out, sp.splits};
+            q[i] = qr_job(j, slabs && few ? part : Y, slabs && few ? Y : nullptr, slabs && few ? sp.splits : 1, nullptr);
         }
-        DAD_TRY(launch_cholqr(q, n, r, it + 1 == n_iter, s));                      // G = orth(Y)
+        DAD_TRY(direct_tn(t, n, r, s));
+        if (nu) DAD_TRY(reduce_slabs(u, nu, s));
+        DAD_TRY(launch_cholqr(q, n, r, it + 1 == n_iter, s));  // G = orth(Y)
     }
-    DAD_TRY(nn(true));               // V = Delta G
-    return tn(false, to_P, all);     // P = A^T V
+    DAD_TRY(nn(n_iter, true, true));  // V = Delta G;  P = M G
+    DAD_TRY(tn_A(true));              // P = A^T V
+    for (int i = 0; i < n; ++i) {
+        const CompressJob& j = jobs[i];
+        if (j.on_M && j.p->nn_out.splits > 1 && j.h_in % 32)
+            DAD_TRY(copy_rows(j.at<float>(j.p->off_V), direct_npad(j.h_in), j.Pt, j.h_in, r, s));
+    }
+    return DAD_OK;
 }
 
 // The guarded kernels (widths below one 16-byte load).
@@ -384,11 +482,34 @@ static dad_status dma_compress(const CompressPlan& p, const CompressJob* jobs, i
     return reduce_slabs(u, n, s);
 }
 
+// A job on the route to M: the product that makes M in its place of the job's region, and the job of the products with it.
+static OwnProduct product_M(const CompressJob& j, const RoutePlan& p) {
+    return OwnProduct{j.A, j.D, j.at<float>(p.off_M), j.N, j.h_in, j.h_out, p.rb};
+}
+static CompressJob job_on_M(const CompressJob& j, const RoutePlan& p) {
+    CompressJob m = j;
+    m.p = &p.m;
+    m.A = j.at<float>(p.off_M);
+    m.D = nullptr;
+    m.on_M = true;
+    return m;
+}
+// From site blocks read in place.
+static dad_status make_M_sites(const OwnProduct& q, const RowBlocks& Ab, const RowBlocks& Db, hipStream_t s) {
+    return fast_rebuild(nullptr, nullptr, &Ab, &Db, q.K, q.h_in, q.h_out, q.G, q.G, q.rb.split, q.rb.tile, s);
+}
+
 // One reduction on its own.
-static dad_status compress_one(const CompressJob& j, dad_dtype dt, int r, int n_iter, hipStream_t s,
+static dad_status compress_one(const CompressJob& j, const RoutePlan& p, dad_dtype dt, int r, int n_iter, hipStream_t s,
                                const RowBlocks* Ab = nullptr, const RowBlocks* Db = nullptr) {
-    if (j.p->dma) return dma_compress(*j.p, &j, 1, 0, false, r, n_iter, s, Ab, Db);
-    if (j.p->direct) return direct_compress(&j, 1, dt, r, n_iter, s);
+    if (p.on_M(n_iter)) {
+        const OwnProduct q = product_M(j, p);
+        const CompressJob m = job_on_M(j, p);
+        const dad_status rc = Ab ? make_M_sites(q, *Ab, *Db, s) : launch_rebuild_own(&q, 1, dt, s);
+        return rc != DAD_OK ? rc : direct_compress(&m, 1, dt, r, n_iter, s);
+    }
+    if (p.f.dma) return dma_compress(p.f, &j, 1, 0, false, r, n_iter, s, Ab, Db);
+    if (p.f.direct) return direct_compress(&j, 1, dt, r, n_iter, s);
     return guarded_compress(j, dt, r, n_iter, s);
 }
 #undef DAD_TRY
@@ -506,17 +627,13 @@ static void fill_blocks(int S, const void* const* sites, const int64_t* rows, Ro
 // the call first stacks behind the layer's plan in its workspace.
 struct LayerPlan {
     int64_t N;
-    CompressPlan cp;
+    RoutePlan rp;
     bool sites, in_place;
     size_t off_A, off_D, total;
 };
 
-static bool compress_in_place(const CompressPlan& p, int S, const int64_t* rows) {
-    return p.dma && rows_allow_blocks(S, rows);
-}
-
-// Shapes only (d.S, d.rows, d.N, widths); DAD_ERR_* on sizes out of range.
-static dad_status plan_layer(const dad_compress_desc& d, dad_dtype dt, int r, LayerPlan* lp) {
+// Shapes only (d.S, d.rows, d.N, widths); DAD_ERR_* on sizes out of range.  factors: not on M.
+static dad_status plan_layer(const dad_compress_desc& d, dad_dtype dt, int r, LayerPlan* lp, bool factors = false) {
     lp->sites = d.S > 0;
     lp->N = d.N;
     if (d.S < 0) return DAD_ERR_SHAPE;
@@ -525,9 +642,10 @@ static dad_status plan_layer(const dad_compress_desc& d, dad_dtype dt, int r, La
         if (rc != DAD_OK) return rc;
     }
     if (!compress_shape_ok(lp->N, d.h_in, d.h_out, r)) return DAD_ERR_SHAPE;
-    lp->cp = plan_compress(lp->N, d.h_in, d.h_out, r, dt);
-    lp->in_place = lp->sites && compress_in_place(lp->cp, d.S, d.rows);
-    size_t o = align_up(lp->cp.total, 256);
+    lp->rp = plan_compress(lp->N, d.h_in, d.h_out, r, dt);
+    if (factors) lp->rp.to_factors();
+    lp->in_place = lp->sites && lp->rp.f.dma && rows_allow_blocks(d.S, d.rows);
+    size_t o = align_up(lp->rp.total, 256);
     lp->off_A = o;
     if (lp->sites && !lp->in_place) o += align_up((size_t)lp->N * d.h_in * elem_size(dt), 256);
     lp->off_D = o;
@@ -554,7 +672,7 @@ static dad_status layer_args_ok(const dad_compress_desc& d, const LayerPlan& lp,
 // behind the layer's plan first, on stream s.
 static dad_status layer_job(const dad_compress_desc& d, const LayerPlan& lp, dad_dtype dt, char* ws, int* flag, hipStream_t s,
                             CompressJob* job) {
-    *job = CompressJob{&lp.cp, d.A, d.D, lp.N, d.h_in, d.h_out, d.G0, d.Pt, d.Gt, ws, flag ? flag : reinterpret_cast<int*>(ws + lp.cp.off_flag)};
+    *job = CompressJob{&lp.rp.f, d.A, d.D, lp.N, d.h_in, d.h_out, d.G0, d.Pt, d.Gt, ws, flag ? flag : reinterpret_cast<int*>(ws)};
     if (!lp.sites || lp.in_place) return DAD_OK;
     job->A = ws + lp.off_A;
     job->D = ws + lp.off_D;
@@ -567,11 +685,11 @@ static dad_status launch_layer(const dad_compress_desc& d, const LayerPlan& lp, 
     CompressJob job;
     const dad_status rc = layer_job(d, lp, dt, static_cast<char*>(ws), flag, s, &job);
     if (rc != DAD_OK) return rc;
-    if (!lp.in_place) return compress_one(job, dt, r, n_iter, s);
+    if (!lp.in_place) return compress_one(job, lp.rp, dt, r, n_iter, s);
     RowBlocks a = {}, b = {};
     fill_blocks(d.S, d.A_sites, d.rows, &a);
     fill_blocks(d.S, d.D_sites, d.rows, &b);
-    return compress_one(job, dt, r, n_iter, s, &a, &b);
+    return compress_one(job, lp.rp, dt, r, n_iter, s, &a, &b);
 }
 
 dad_status dad_compress_rank(const void* A, const void* D, int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt,
@@ -581,11 +699,12 @@ dad_status dad_compress_rank(const void* A, const void* D, int64_t N, int64_t h_
     dad_status rc = compress_args_ok(A, D, N, h_in, h_out, dt, r, n_iter, G0, Pt, Gt);
     if (rc != DAD_OK) return rc;
     if (!aligned16(workspace)) return DAD_ERR_ALIGN;
-    const CompressPlan p = plan_compress(N, h_in, h_out, r, dt);
+    RoutePlan p = plan_compress(N, h_in, h_out, r, dt);
+    if (ws_bytes < p.total) p.to_factors();
     if (ws_bytes < p.total) return DAD_ERR_WORKSPACE;
     if ((rc = device_ready()) != DAD_OK) return rc;
     char* ws = static_cast<char*>(workspace);
-    return compress_one(CompressJob{&p, A, D, N, h_in, h_out, G0, Pt, Gt, ws, reinterpret_cast<int*>(ws + p.off_flag)}, dt, r, n_iter,
+    return compress_one(CompressJob{&p.f, A, D, N, h_in, h_out, G0, Pt, Gt, ws, reinterpret_cast<int*>(ws)}, p, dt, r, n_iter,
                         (hipStream_t)stream);
 }
 
@@ -595,12 +714,12 @@ dad_status dad_compress_rank_noalloc(const void* A, const void* D, int64_t N, in
     dad_status rc = compress_args_ok(A, D, N, h_in, h_out, dt, r, n_iter, G0, Pt, Gt);
     if (rc != DAD_OK) return rc;
     if (numeric_flag && (reinterpret_cast<uintptr_t>(numeric_flag) & 3u)) return DAD_ERR_ALIGN;
-    const CompressPlan p = plan_compress(N, h_in, h_out, r, dt);
+    const RoutePlan p = plan_compress(N, h_in, h_out, r, dt);
     if (p.total > (size_t)DAD_STATIC_SCRATCH_BYTES) return DAD_ERR_WORKSPACE;
     void* ws = nullptr;  // the current device's copy of `scratch`
     if ((rc = device_ready(&ws)) != DAD_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
-    rc = compress_one(CompressJob{&p, A, D, N, h_in, h_out, G0, Pt, Gt, static_cast<char*>(ws), static_cast<int*>(ws)}, dt, r, n_iter, s);
+    rc = compress_one(CompressJob{&p.f, A, D, N, h_in, h_out, G0, Pt, Gt, static_cast<char*>(ws), static_cast<int*>(ws)}, p, dt, r, n_iter, s);
     if (rc != DAD_OK || !numeric_flag) return rc;
     hipLaunchKernelGGL(k_copy_flag, dim3(1), dim3(1), 0, s, (const int*)ws, numeric_flag);
     DAD_LAUNCH_CHECK();
@@ -629,6 +748,7 @@ dad_status dad_compress_rank_sites(int S, const void* const* A_sites, const void
     if (rc != DAD_OK) return rc;
     if ((rc = layer_args_ok(d, lp, dt, r, n_iter)) != DAD_OK) return rc;
     if (!aligned16(workspace)) return DAD_ERR_ALIGN;
+    if (ws_bytes < lp.total && (rc = plan_layer(d, dt, r, &lp, true)) != DAD_OK) return rc;
     if (ws_bytes < lp.total) return DAD_ERR_WORKSPACE;
     if ((rc = device_ready()) != DAD_OK) return rc;
     return launch_layer(d, lp, dt, r, n_iter, workspace, nullptr, (hipStream_t)stream);
@@ -657,12 +777,14 @@ static double factor_bytes(const dad_compress_desc& d, int64_t N, dad_dtype dt) 
 struct Unit {
     int first, count;
     bool per_job;         // the jobs differ in their widths
-    CompressPlan layout;  // workspace layout of every job's region (sized for the largest job)
+    bool on_M;
+    CompressPlan layout;  // of a batch on the factors: workspace layout of every job's region (sized for the largest job)
+    size_t stride;        // of the jobs' regions
     size_t bytes;         // of its lane region
 };
 
 static bool batchable(const dad_compress_desc& d, const LayerPlan& lp, dad_dtype dt) {
-    return !lp.sites && lp.cp.dma && lp.N < ((int64_t)1 << 31) && factor_bytes(d, lp.N, dt) <= BATCH_MAX_BYTES;
+    return !lp.sites && lp.rp.f.dma && lp.N < ((int64_t)1 << 31) && factor_bytes(d, lp.N, dt) <= BATCH_MAX_BYTES;
 }
 
 // A layer that may share a batch with layers of other widths.
@@ -672,7 +794,7 @@ static bool mixable(const dad_compress_desc& d, int64_t N, dad_dtype dt) {
 
 // Layout of the grouped workspace: 256-byte group header (sticky numeric flag at +0), then one region
 // per lane, each large enough for any unit of the group.
-static dad_status grouped_plans(int n, const dad_compress_desc* descs, dad_dtype dt, int r, std::vector<LayerPlan>* plans,
+static dad_status grouped_plans(int n, const dad_compress_desc* descs, dad_dtype dt, int r, int n_iter, std::vector<LayerPlan>* plans,
                                 std::vector<Unit>* units, size_t* lane_bytes) {
     plans->resize((size_t)n);
     units->clear();
@@ -681,13 +803,13 @@ static dad_status grouped_plans(int n, const dad_compress_desc* descs, dad_dtype
         LayerPlan& lp = (*plans)[(size_t)i];
         const dad_status rc = plan_layer(descs[i], dt, r, &lp);
         if (rc != DAD_OK) return rc;
-        const bool can = batchable(descs[i], lp, dt);
+        const bool can = batchable(descs[i], lp, dt), on_M = lp.rp.on_M(n_iter);
         bool joined = false;
         if (open && can) {
             Unit& u = units->back();
             const dad_compress_desc& f = descs[u.first];
             const bool same = f.h_in == descs[i].h_in && f.h_out == descs[i].h_out;
-            if (u.count < MAX_ROW_BLOCKS && (*plans)[(size_t)u.first].N == lp.N &&
+            if (u.count < MAX_ROW_BLOCKS && (*plans)[(size_t)u.first].N == lp.N && u.on_M == on_M &&
                 ((uniform && same) || (all256 && mixable(descs[i], lp.N, dt)))) {
                 ++u.count;
                 uniform = uniform && same;
@@ -695,7 +817,7 @@ static dad_status grouped_plans(int n, const dad_compress_desc* descs, dad_dtype
             }
         }
         if (!joined) {
-            units->push_back(Unit{i, 1, false, lp.cp, lp.total});
+            units->push_back(Unit{i, 1, false, on_M, lp.rp.f, 0, lp.total});
             open = can;
             uniform = true;
             all256 = can && mixable(descs[i], lp.N, dt);
@@ -704,19 +826,26 @@ static dad_status grouped_plans(int n, const dad_compress_desc* descs, dad_dtype
     }
     size_t lane = 0;
     for (Unit& u : *units) {
-        if (u.count > 1) {  // one layout for all jobs of the batch
+        if (u.count > 1 && u.on_M) {
+            for (int j = u.first; j < u.first + u.count; ++j) {
+                const size_t b = align_up((*plans)[(size_t)j].total, 256);
+                if (b > u.stride) u.stride = b;
+            }
+            u.bytes = (size_t)u.count * u.stride;
+        } else if (u.count > 1) {  // one layout for all jobs of the batch
             int64_t hi = 0, ho = 0;
             size_t part = 0;
             for (int j = u.first; j < u.first + u.count; ++j) {
-                const CompressPlan& c = (*plans)[(size_t)j].cp;
+                const CompressPlan& c = (*plans)[(size_t)j].rp.f;
                 if (descs[j].h_in > hi) hi = descs[j].h_in;
                 if (descs[j].h_out > ho) ho = descs[j].h_out;
                 const size_t pi = (size_t)c.tn_in.splits * r * descs[j].h_in * 4, po = (size_t)c.tn_out.splits * r * descs[j].h_out * 4;
                 if (pi > part) part = pi;
                 if (po > part) part = po;
             }
-            u.layout = plan_compress((*plans)[(size_t)u.first].N, hi, ho, r, dt, part);
-            u.bytes = (size_t)u.count * align_up(u.layout.total, 256);
+            u.layout = plan_factors((*plans)[(size_t)u.first].N, hi, ho, r, dt, part);
+            u.stride = align_up(u.layout.total, 256);
+            u.bytes = (size_t)u.count * u.stride;
         }
         if (u.bytes > lane) lane = u.bytes;
     }
@@ -728,16 +857,20 @@ size_t dad_compress_grouped_workspace_bytes(int n, const dad_compress_desc* desc
     if (n < 1 || n > DAD_MAX_GROUP || !descs || !dtype_ok(dt) || lanes < 1 || lanes > DAD_MAX_LANES) return 0;
     std::vector<LayerPlan> plans;
     std::vector<Unit> units;
-    size_t lane_bytes = 0;
-    if (grouped_plans(n, descs, dt, r, &plans, &units, &lane_bytes) != DAD_OK) return 0;
-    const int used = lanes < (int)units.size() ? lanes : (int)units.size();
-    return 256 + (size_t)used * lane_bytes;
+    size_t most = 0;
+    for (int n_iter : {2, 1}) {  // layers that are on M with two applications may share a batch with one
+        size_t lane_bytes = 0;
+        if (grouped_plans(n, descs, dt, r, n_iter, &plans, &units, &lane_bytes) != DAD_OK) return 0;
+        const size_t bytes = 256 + (lanes < (int)units.size() ? lanes : units.size()) * lane_bytes;
+        if (bytes > most) most = bytes;
+    }
+    return most;
 }
 
 // The launches of one batch on stream s; ws holds u.count regions.
 static dad_status launch_batch(const dad_compress_desc* descs, const Unit& u, const std::vector<LayerPlan>& plans,
                                dad_dtype dt, int r, int n_iter, void* ws, int* flag, hipStream_t s) {
-    const int64_t N = plans[(size_t)u.first].N, stride = (int64_t)align_up(u.layout.total, 256);
+    const int64_t N = plans[(size_t)u.first].N, stride = (int64_t)u.stride;
     RowBlocks a = {}, b = {};
     CompressJob jobs[MAX_JOBS];
     for (int j = 0; j < MAX_ROW_BLOCKS; ++j) {
@@ -745,7 +878,7 @@ static dad_status launch_batch(const dad_compress_desc* descs, const Unit& u, co
         a.first[j] = b.first[j] = (in ? j : u.count) * N;
         if (!in) continue;
         const dad_compress_desc& d = descs[u.first + j];
-        const CompressPlan& c = plans[(size_t)(u.first + j)].cp;
+        const CompressPlan& c = plans[(size_t)(u.first + j)].rp.f;
         a.base[j] = static_cast<const char*>(d.A);
         b.base[j] = static_cast<const char*>(d.D);
         if (u.per_job) {
@@ -767,13 +900,12 @@ dad_status dad_compress_rank_grouped(int n, const dad_compress_desc* descs, dad_
     std::vector<LayerPlan> plans;
     std::vector<Unit> units;
     size_t lane_bytes = 0;
-    dad_status rc = grouped_plans(n, descs, dt, r, &plans, &units, &lane_bytes);
-    if (rc != DAD_OK) return rc;
+    dad_status rc;
+    if ((rc = grouped_plans(n, descs, dt, r, n_iter, &plans, &units, &lane_bytes)) != DAD_OK) return rc;
     for (int i = 0; i < n; ++i)
         if ((rc = layer_args_ok(descs[i], plans[(size_t)i], dt, r, n_iter)) != DAD_OK) return rc;
     if (!aligned16(workspace)) return DAD_ERR_ALIGN;
-    const int nu = (int)units.size();
-    const int used = lanes < nu ? lanes : nu;
+    const int nu = (int)units.size(), used = lanes < nu ? lanes : nu;
     if (ws_bytes < 256 + (size_t)used * lane_bytes) return DAD_ERR_WORKSPACE;
     if ((rc = device_ready()) != DAD_OK) return rc;
     int dev = 0;
@@ -785,14 +917,14 @@ dad_status dad_compress_rank_grouped(int n, const dad_compress_desc* descs, dad_
 
     std::lock_guard<std::mutex> lk(st.lanes_mu);
     auto region = [&](int l) { return ws + 256 + (size_t)l * lane_bytes; };
-    // Units on the direct kernels run as merged launches, a region each, on the caller's stream, the others beside them,
-    // a region and a stream each.  Where a group has both kinds they share the regions by their numbers of units
+    // Units on the direct kernels (on the factors or on M) run as merged launches, a region each, on the caller's stream, the others
+    // beside them, a region and a stream each.  Where a group has both kinds they share the regions by their numbers of units
     // (runs of one kind after the other lost the overlap: four of 16384 rows, 768 to 3072 wide, 504 us on four lanes, 713 us
     // in runs, 509 us so; eight of 4000 rows, 1000 wide, 791, 846, 469 us); with one region they follow each other on the caller's stream.
     std::vector<int> merged, apart;
     for (int k = 0; k < nu; ++k) {
         const Unit& u = units[(size_t)k];
-        (u.count == 1 && plans[(size_t)u.first].cp.direct ? merged : apart).push_back(k);
+        (u.on_M || (u.count == 1 && plans[(size_t)u.first].rp.f.direct) ? merged : apart).push_back(k);
     }
     const int nm = (int)merged.size(), na = (int)apart.size();
     const bool both = nm > 0 && na > 0 && used > 1;
@@ -814,6 +946,37 @@ dad_status dad_compress_rank_grouped(int n, const dad_compress_desc* descs, dad_
         DAD_HIP_TRY(hipEventRecord(st.fork, main));
         for (int l = 0; l < sides; ++l) DAD_HIP_TRY(hipStreamWaitEvent(st.side[l], st.fork, 0));
     }
+    // the merged launches take up to MAX_DIRECT_JOBS jobs at a time
+    CompressJob jobs[MAX_DIRECT_JOBS];
+    OwnProduct products[MAX_DIRECT_JOBS];
+    int c = 0, np = 0;
+    int* clear = na ? nullptr : group_flag;
+    auto flush = [&]() -> dad_status {
+        dad_status rc = np ? launch_rebuild_own(products, np, dt, main) : DAD_OK;
+        if (rc == DAD_OK && c) rc = direct_compress(jobs, c, dt, r, n_iter, main, clear);
+        c = np = 0;
+        clear = nullptr;
+        return rc;
+    };
+    auto add_merged = [&](const dad_compress_desc& d, const LayerPlan& lp, char* at) -> dad_status {
+        CompressJob job;
+        dad_status rc = layer_job(d, lp, dt, at, group_flag, main, &job);
+        if (rc != DAD_OK) return rc;
+        if (!lp.rp.on_M(n_iter)) {
+            jobs[c++] = job;
+        } else {
+            jobs[c++] = job_on_M(job, lp.rp);
+            if (lp.in_place) {
+                RowBlocks a = {}, b = {};
+                fill_blocks(d.S, d.A_sites, d.rows, &a);
+                fill_blocks(d.S, d.D_sites, d.rows, &b);
+                if ((rc = make_M_sites(product_M(job, lp.rp), a, b, main)) != DAD_OK) return rc;
+            } else {
+                products[np++] = product_M(job, lp.rp);
+            }
+        }
+        return c == MAX_DIRECT_JOBS ? flush() : DAD_OK;
+    };
     for (int m = 0, q = 0; rc == DAD_OK && (m < nm || q < na);) {
         for (int l = 0; l < lanes_used && q < na && rc == DAD_OK; ++l, ++q) {  // a lane's units follow each other on its stream
             const Unit& u = units[(size_t)apart[(size_t)q]];
@@ -821,15 +984,12 @@ dad_status dad_compress_rank_grouped(int n, const dad_compress_desc* descs, dad_
             rc = u.count > 1 ? launch_batch(descs, u, plans, dt, r, n_iter, at, group_flag, lane_stream(l))
                              : launch_layer(descs[u.first], plans[(size_t)u.first], dt, r, n_iter, at, group_flag, lane_stream(l));
         }
-        if (rc != DAD_OK || m == nm) continue;
-        CompressJob jobs[DAD_MAX_LANES];
-        int* const clear = na || m ? nullptr : group_flag;
-        int c = 0;
-        for (; c < together && m < nm && rc == DAD_OK; ++c, ++m) {
-            const int f = units[(size_t)merged[(size_t)m]].first;
-            rc = layer_job(descs[f], plans[(size_t)f], dt, region(c), group_flag, main, &jobs[c]);
+        for (int l = 0; l < together && m < nm && rc == DAD_OK; ++l, ++m) {
+            const Unit& u = units[(size_t)merged[(size_t)m]];
+            for (int i = 0; i < u.count && rc == DAD_OK; ++i)
+                rc = add_merged(descs[u.first + i], plans[(size_t)(u.first + i)], region(l) + (size_t)i * u.stride);
         }
-        if (rc == DAD_OK) rc = direct_compress(jobs, c, dt, r, n_iter, main, clear);
+        if (rc == DAD_OK) rc = flush();
     }
     // join, also after a failed enqueue: the caller's stream must not run ahead of the side streams
     for (int l = 0; l < sides; ++l) {
@@ -1064,7 +1224,7 @@ namespace dad {
 
 dad_status launch_rebuild(const void* L, const void* R, int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt,
                           float* G, float* partials, const RebuildPlan& plan, hipStream_t s) {
-    if (plan.fast) return fast_rebuild(L, R, nullptr, nullptr, K, h_in, h_out, G, partials, plan.split, plan.tile, s);
+    if (plan.fast) return fast_rebuild(L, R, nullptr, nullptr, K, h_in, h_out, G, partials, plan.split, plan.tile, s, plan.fine);
     if (plan.f32) return launch_rebuild_f32(1, &L, &R, &G, &K, &h_in, &h_out, &plan.split, &partials, s);
     return gen_rebuild(L, R, K, h_in, h_out, dt, G, partials, plan.split, s);
 }

@@ -248,8 +248,9 @@ struct CompressPlan {
     SplitPlan nn_out;     // column split of  Delta G
 };
 
+// Plan of a reduction on the factors.
 // part_floor: least size of the split-partials region (a batch of jobs of several widths).
-CompressPlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt, size_t part_floor = 0);
+CompressPlan plan_factors(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype dt, size_t part_floor = 0);
 
 struct RebuildPlan {
     SplitPlan split;
@@ -257,9 +258,11 @@ struct RebuildPlan {
     bool fast;     // bf16 MFMA kernels (all but operands shorter than one 16-byte load)
     bool f32;      // fp32 MFMA kernel (widths of at least 4; else the guarded kernel)
     int tile;      // output tile edge of the direct-to-LDS bf16 kernel (256 or 128); 0: the register-staged kernel
+    bool fine;     // long sums are added up from shorter ones on every kernel
 };
 
-RebuildPlan plan_rebuild(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt);
+// most: of chunks (bf16).
+RebuildPlan plan_rebuild(int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt, int most = 64, bool fine = false);
 
 // The iteration on the gradient itself: M = A^T Delta once, then every application reads M (h_in x h_out, fp32) instead
 // of the factors, with the direct kernels.
@@ -317,7 +320,7 @@ struct QrJob {
 size_t qr_part_bytes(int64_t h, int r);
 dad_status launch_cholqr(const QrJob* jobs, int count, int r, bool final, hipStream_t s);
 
-// The two thin contractions of the direct path (csrc/direct.hip), for jobs of one element type and rank.
+// The two thin contractions of the direct path (csrc/direct.hip), for jobs of one rank.
 constexpr int MAX_DIRECT_JOBS = DAD_MAX_LANES;
 struct alignas(64) NnJob {  // Vt (r x Npad) <- (X Pt^T)^T
     const void* X;
@@ -327,8 +330,10 @@ struct alignas(64) NnJob {  // Vt (r x Npad) <- (X Pt^T)^T
     int* zero_hdr;  // a 256-byte workspace header the launch clears on the side, or null
     int64_t N;
     int h;
-    int cs;      // workgroups that share a row (direct_nn_splits)
+    short cs;    // workgroups that share a row (direct_nn_splits)
+    short f32;   // type of X (else bf16)
     int wg;      // set by direct_nn: workgroups
+    int pitch;   // 0: Npad.  Else (cs = 1) of the rows of Vt, and nothing is written beyond row N of X
 };
 struct alignas(64) TnJob {  // out (r x h), or `splits` slabs of it, <- Vt X
     const void* X;
@@ -336,10 +341,10 @@ struct alignas(64) TnJob {  // out (r x h), or `splits` slabs of it, <- Vt X
     float* out;
     int64_t N, chunk;
     int h, splits;
+    int f32;  // type of X (else bf16)
 };
-dad_status direct_nn(const NnJob* jobs, int count, int r, dad_dtype dt, hipStream_t s, const int* skip = nullptr,
-                     int* clear = nullptr);
-dad_status direct_tn(const TnJob* jobs, int count, int r, dad_dtype dt, hipStream_t s, const int* skip = nullptr);
+dad_status direct_nn(const NnJob* jobs, int count, int r, hipStream_t s, const int* skip = nullptr, int* clear = nullptr);
+dad_status direct_tn(const TnJob* jobs, int count, int r, hipStream_t s, const int* skip = nullptr);
 int64_t direct_npad(int64_t N);
 // slab_bytes (here and below): most bytes of slabs; one chunk leaves none.
 int direct_nn_splits(int64_t N, int64_t h, int r, dad_dtype dt, size_t slab_bytes);
@@ -348,6 +353,19 @@ SplitPlan direct_tn_split(int64_t N, int64_t h, int r, dad_dtype dt, size_t slab
 
 dad_status launch_rebuild(const void* L, const void* R, int64_t K, int64_t h_in, int64_t h_out, dad_dtype dt,
                           float* G, float* partials, const RebuildPlan& plan, hipStream_t s);
+
+// Microseconds of a product, its slabs' sum included: by itself, and its part of a full chip beside others.
+struct ProductTime {
+    double alone, share;
+};
+
+struct OwnProduct {  // G <- L^T R; its slabs lie from G on
+    const void *L, *R;
+    float* G;
+    int64_t K, h_in, h_out;
+    RebuildPlan rb;
+};
+dad_status launch_rebuild_own(const OwnProduct* jobs, int n, dad_dtype dt, hipStream_t s);
 
 
 // G_i = L_i^T R_i for n fp32 jobs in as few launches as possible (csrc/rebuild_f32.hip); a job with
@@ -358,6 +376,6 @@ dad_status gen_rebuild(const void* L, const void* R, int64_t K, int64_t h_in, in
                        float* partials, SplitPlan sp, hipStream_t s);
 dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R, float* const* G, const int64_t* K,
                               const int64_t* h_in, const int64_t* h_out, const SplitPlan* sp, float* const* slabs,
-                              hipStream_t s);
+                              hipStream_t s, bool fine = false);
 
 }  // namespace dad

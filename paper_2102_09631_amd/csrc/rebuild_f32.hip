@@ -39,6 +39,7 @@ struct alignas(64) RebuildF32Job {
     int64_t K, chunk;  // chunk = K rows per slab, a multiple of 16 unless splits == 1
     int h_in, h_out, ks, splits;  // ks: waves that share a tile
     int wg;                       // workgroups
+    int fold;                     // rounds of three steps per wave that are summed before they are added to the rest
 };
 
 // The tiles of a workgroup (NW / ks of them) form a block, so that they share operand lines in the L1.
@@ -91,11 +92,10 @@ __global__ __launch_bounds__(64 * rf::NW, SHORT ? 3 : 1) void k_rebuild_f32_mfma
             y[set][s] = *reinterpret_cast<const f32x4_b4*>(r + (uint32_t)rc * (uint32_t)h_out + qc);
         }
     };
-    // The matrix instructions sum FOLD rounds of three steps (192 K rows), which are then added to the rest: one running
+    // The matrix instructions sum `fold` rounds of three steps (four: 192 K rows), which are then added to the rest: one running
     // sum over a wave's share of K rounds at full height with every instruction (2048 x 2304 x 756, error against fp64:
     // 5.7e-7 with one sum, 2.5e-7 so, the LDS-staged kernel before 4.7e-7; 4096 x 2048 x 2048: 274 -> 283 us, 384 rows 278 us
     // but 2560 x 403 x 977 then at 2.3e-7, before 2.1e-7).
-    constexpr int FOLD = 4;
     f32x4 acc[4][4], more[SHORT ? 1 : 4][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -104,6 +104,7 @@ __global__ __launch_bounds__(64 * rf::NW, SHORT ? 3 : 1) void k_rebuild_f32_mfma
             acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
             if constexpr (!SHORT) more[a][b] = acc[a][b];
         }
+    const int fold_at = jb.fold;
     auto fold = [&]() {
         if constexpr (!SHORT) {
 #pragma unroll
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(64 * rf::NW, SHORT ? 3 : 1) void k_rebuild_f32_mfma
         load(s1, at_most(kp + ks));
         int round = 0;
         for (int b = kp; b < nb; b += 3 * ks) {
-            if (++round > FOLD) {
+            if (++round > fold_at) {
                 fold();
                 round = 1;
             }
@@ -254,11 +255,22 @@ SplitPlan rebuild_f32_split(int64_t K, int64_t h_in, int64_t h_out) {
     return rf_plan(K, h_in, h_out, &ks);
 }
 
+// As fitted to 200 products on the way to a reduction.
+ProductTime rebuild_f32_time(int64_t K, int64_t h_in, int64_t h_out) {
+    int ks;
+    const SplitPlan sp = rf_plan(K, h_in, h_out, &ks);
+    const int64_t groups = rf_groups(h_in, h_out, ks), steps = ceil_div(K, rf::BK);
+    const double slabs = sp.splits == 1 ? 0.0 : (2.0 * sp.splits + 1.0) * h_in * h_out * 1e-6;
+    const double wg = 5.0 + (double)ceil_div(steps, (int64_t)ks * sp.splits);
+    return ProductTime{0.9 * ((sp.splits == 1 ? 0.0 : 5.0) + slabs + (double)rf_cost(groups, steps, ks, sp.splits)),
+                       0.9 * (slabs + wg * (double)(groups * sp.splits) / CU_COUNT)};
+}
+
 // Launches n jobs (G_i = L_i^T R_i, each with its own split plan; a job with splits > 1 writes slabs
 // at slabs[i] and is summed by reduce_slabs afterwards) in as few launches as the job table allows.
 dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R, float* const* G, const int64_t* K,
                               const int64_t* h_in, const int64_t* h_out, const SplitPlan* sp, float* const* slabs,
-                              hipStream_t s) {
+                              hipStream_t s, bool fine) {
     for (int first = 0; first < n; first += rf::MAX_JOBS) {
         const int cnt = n - first < rf::MAX_JOBS ? n - first : rf::MAX_JOBS;
         RebuildF32Job jobs[rf::MAX_JOBS];
@@ -285,6 +297,7 @@ dad_status launch_rebuild_f32(int n, const void* const* L, const void* const* R,
             const int64_t wg = rf_groups(h_in[i], h_out[i], jb.ks) * sp[i].splits;
             if (wg > (int64_t)1 << 30) return DAD_ERR_SHAPE;
             jb.wg = (int)wg;
+            jb.fold = fine && ceil_div(jb.chunk, rf::BK) >= 8 ? 1 : 4;  // shorter ones have the bits of the instance for them
             if (jb.wg > most) most = jb.wg;
             if (ceil_div(jb.chunk, rf::BK) > longest) longest = ceil_div(jb.chunk, rf::BK);
             bytes += 4.0 * h_in[i] * h_out[i];

@@ -83,9 +83,10 @@ constexpr int SETS = 4;                                  // stages in flight in 
 constexpr int LDS = 2 * SLOTB;
 }  // namespace ra
 
-__global__ __launch_bounds__(ra::THREADS, 2) void k_rebuild_bf16(const bf16_t* __restrict__ L, const bf16_t* __restrict__ R,
-                                                              float* __restrict__ out, int64_t K, int h_in, int h_out,
-                                                              int64_t chunk, int tiles_m, int tiles_n, int total) {
+// One workgroup's tile: `lid` is its logical index among the tiles_m * tiles_n * splits of this product.
+__device__ __forceinline__ void rebuild_tile_any(const bf16_t* __restrict__ L, const bf16_t* __restrict__ R,
+                                                 float* __restrict__ out, int64_t K, int h_in, int h_out,
+                                                 int64_t chunk, int tiles_m, int tiles_n, int lid) {
     constexpr int TILE = ra::TILE, ROWB = ra::ROWB, BK = rb::BK, SETS = ra::SETS, TILEB = ra::TILEB, SLOTB = ra::SLOTB;
     constexpr int CPR = TILE / 8, RPP = ra::THREADS / CPR;  // chunks per row, rows per pass of the workgroup (two passes per tile)
     static_assert(2 * RPP == BK, "two loads per thread and operand cover a stage");
@@ -96,7 +97,6 @@ __global__ __launch_bounds__(ra::THREADS, 2) void k_rebuild_bf16(const bf16_t* _
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int lid = rb_logical_id(total);
     const int tiles = tiles_m * tiles_n;
     const int split = lid / tiles, tile = lid - split * tiles;
     int pm, qn;
@@ -263,6 +263,12 @@ __global__ __launch_bounds__(ra::THREADS, 2) void k_rebuild_bf16(const bf16_t* _
                 if (p < h_in && q < h_out) o[(int64_t)p * h_out + q] = sum[a][b][v];
             }
         }
+}
+
+__global__ __launch_bounds__(ra::THREADS, 2) void k_rebuild_bf16(const bf16_t* __restrict__ L, const bf16_t* __restrict__ R,
+                                                              float* __restrict__ out, int64_t K, int h_in, int h_out,
+                                                              int64_t chunk, int tiles_m, int tiles_n, int total) {
+    rebuild_tile_any(L, R, out, K, h_in, h_out, chunk, tiles_m, tiles_n, rb_logical_id(total));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -520,6 +526,7 @@ struct RebuildJob {
     float* out;  // G, or the first of its slabs
     int64_t K, chunk;
     int h_in, h_out, tiles_m, tiles_n;
+    int total;  // workgroups
 };
 struct RebuildJobs {
     int first_block[rb::MAX_JOBS];  // first logical id of each job; entries beyond the last job hold INT_MAX
@@ -537,6 +544,39 @@ __global__ __launch_bounds__(64 * WM * WN) void k_rebuild_bf16_dma_jobs(RebuildJ
     const bf16_t* R = jb.R;
     rebuild_tile_dma<T, WM, WN, const bf16_t*, TAIL>(L, R, jb.out, jb.K, jb.h_in, jb.h_out, jb.chunk, jb.tiles_m, jb.tiles_n,
                                                      lid - tb.first_block[ji]);
+}
+
+
+// Products with plans of their own (the M of several reductions): their workgroups differ in length, so every product is dealt to all
+// eight XCDs in equal shares, the one with the longest workgroups first; an XCD's share of a product is a contiguous run of its logical
+// ids.  first_block counts the workgroups of one XCD.
+__device__ __forceinline__ int rb_own_id(const RebuildJobs& tb, int* job) {
+    const int at = (int)(blockIdx.x >> 3);
+    int ji = 0;
+#pragma unroll
+    for (int i = 1; i < rb::MAX_JOBS; ++i) ji += tb.first_block[i] <= at ? 1 : 0;
+    *job = ji;
+    const int total = tb.j[ji].total, lid = (int)(blockIdx.x & 7) * ((total + 7) >> 3) + at - tb.first_block[ji];
+    return lid < total ? lid : -1;
+}
+
+template <int T, int WM, int WN, bool TAIL>
+__global__ __launch_bounds__(64 * WM * WN) void k_rebuild_bf16_dma_own(RebuildJobs tb) {
+    int ji;
+    const int lid = rb_own_id(tb, &ji);
+    if (lid < 0) return;
+    const RebuildJob& jb = tb.j[ji];
+    const bf16_t* L = jb.L;
+    const bf16_t* R = jb.R;
+    rebuild_tile_dma<T, WM, WN, const bf16_t*, TAIL>(L, R, jb.out, jb.K, jb.h_in, jb.h_out, jb.chunk, jb.tiles_m, jb.tiles_n, lid);
+}
+
+__global__ __launch_bounds__(ra::THREADS, 2) void k_rebuild_bf16_own(RebuildJobs tb) {
+    int ji;
+    const int lid = rb_own_id(tb, &ji);
+    if (lid < 0) return;
+    const RebuildJob& jb = tb.j[ji];
+    rebuild_tile_any(jb.L, jb.R, jb.out, jb.K, jb.h_in, jb.h_out, jb.chunk, jb.tiles_m, jb.tiles_n, lid);
 }
 
 
@@ -570,8 +610,10 @@ static int64_t rebuild_any_slabs(int64_t K, int64_t tiles, int64_t h_in, int64_t
 
 // K chunks of the register-staged kernel, by a time in us.  A stage takes 0.32 us and up to 0.1 more as the units fill, 0.67 for
 // two workgroups of a unit; more than one chunk adds the slab traffic and the launch that sums it.
-static SplitPlan rebuild_any_split(int64_t K, int64_t h_in, int64_t h_out) {
-    const int64_t tiles = ceil_div(h_in, ra::TILE) * ceil_div(h_out, ra::TILE), most = rebuild_any_slabs(K, tiles, h_in, h_out);
+static SplitPlan rebuild_any_split(int64_t K, int64_t h_in, int64_t h_out, int limit) {
+    const int64_t tiles = ceil_div(h_in, ra::TILE) * ceil_div(h_out, ra::TILE);
+    int64_t most = rebuild_any_slabs(K, tiles, h_in, h_out);
+    if (most > limit) most = limit;
     double best_t = 0.0;
     int64_t best = 1;
     for (int64_t s = 1; s <= most; ++s) {
@@ -587,6 +629,18 @@ static SplitPlan rebuild_any_split(int64_t K, int64_t h_in, int64_t h_out) {
     return sp;
 }
 
+// A stage of 32 rows for a workgroup of its kernel, by how many of them share a unit, as fitted to 400 products on the way to a
+// reduction.
+ProductTime rebuild_bf16_time(int64_t K, int64_t h_in, int64_t h_out, const RebuildPlan& p) {
+    const int tile = p.tile ? p.tile : ra::TILE, s = p.split.splits;
+    const int64_t wg = ceil_div(h_in, tile) * ceil_div(h_out, tile) * s, slots = tile == 256 ? CU_COUNT : 2 * CU_COUNT;
+    const double full = p.tile == 0 ? 0.48 : p.tile == 128 ? 0.41 : 0.86;  // of a whole round
+    const double first = p.tile == 0 ? 0.23 + 0.07 * wg / CU_COUNT : p.tile == 128 ? 0.32 : full;  // one workgroup to a unit
+    const double stages = (double)ceil_div(p.split.chunk, rb::BK), slabs = s == 1 ? 0.0 : 0.24 * (2.0 * s + 1.0) * h_in * h_out * 4e-6;
+    return ProductTime{(p.tile == 0 ? 4.3 : 0.5) + slabs + (s == 1 ? 0.0 : 2.5) + stages * (wg <= CU_COUNT ? first : full * (double)ceil_div(wg, slots)),
+                       slabs + stages * full * (double)wg / (double)slots};
+}
+
 // Score of a tiling: share of the CU slots that whole rounds of workgroups fill, discounted by the
 // fp32 partial traffic (splits * h_in * h_out * 4 bytes written, read, and the result written) next
 // to the operand reads, and for 128-tiles by their doubled L2->LDS traffic per flop.
@@ -599,17 +653,17 @@ static double rebuild_score(int64_t K, int64_t h_in, int64_t h_out, int tile, in
     return eff / (1.0 + extra / ops) * (tile == 256 ? 1.0 : 0.8);
 }
 
-// Tile edge and number of K chunks; tile 0: the register-staged kernel.
-SplitPlan rebuild_fast_split(int64_t K, int64_t h_in, int64_t h_out, int* tile_out) {
+// Tile edge and number of K chunks, `most` at most; tile 0: the register-staged kernel.
+SplitPlan rebuild_fast_split(int64_t K, int64_t h_in, int64_t h_out, int* tile_out, int most, bool fine) {
     if (!rebuild_whole_tiles(K, h_in, h_out)) {
         *tile_out = 0;
-        return rebuild_any_split(K, h_in, h_out);
+        return rebuild_any_split(K, h_in, h_out, most);
     }
     int best = 1, best_tile = 0;
     double best_score = -1.0;
     for (int tile : {256, 128}) {
-        if (h_in % tile || h_out % tile) continue;
-        for (int s = 1; s <= 64; ++s) {
+        if (h_in % tile || h_out % tile || (fine && tile == 256)) continue;  // 256-tiles have no registers for a second sum
+        for (int s = 1; s <= most; ++s) {
             if (s > 1 && K / s < 1024) break;
             const double score = rebuild_score(K, h_in, h_out, tile, s);
             if (score > best_score * 1.02) {
@@ -628,7 +682,7 @@ SplitPlan rebuild_fast_split(int64_t K, int64_t h_in, int64_t h_out, int* tile_o
 
 template <int T, int WM, int WN>
 static dad_status launch_rebuild_dma(const void* L, const void* R, const RowBlocks* lb, const RowBlocks* rbk, float* dst,
-                                     int64_t K, int64_t h_in, int64_t h_out, SplitPlan sp, hipStream_t s) {
+                                     int64_t K, int64_t h_in, int64_t h_out, SplitPlan sp, bool fine, hipStream_t s) {
     const int lds = rb::DMA_STAGES * 2 * rb::BK * T * 2;
     const int tm = (int)(h_in / T), tn = (int)(h_out / T);
     const int total = tm * tn * sp.splits;
@@ -638,7 +692,7 @@ static dad_status launch_rebuild_dma(const void* L, const void* R, const RowBloc
     if (lb)
         hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, true>), grid, block, lds, s, *lb, *rbk, dst, K, (int)h_in,
                            (int)h_out, sp.chunk, tm, tn, total);
-    else if (K % rb::BK == 0)
+    else if (K % rb::BK == 0 && !fine)
         hipLaunchKernelGGL((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, false>), grid, block, lds, s, l, r, dst, K, (int)h_in,
                            (int)h_out, sp.chunk, tm, tn, total);
     else
@@ -651,13 +705,13 @@ static dad_status launch_rebuild_dma(const void* L, const void* R, const RowBloc
 // lb / rbk, when not null, give both operands as row blocks (L and R are then unused); only the
 // direct-to-LDS kernel reads blocks.
 dad_status fast_rebuild(const void* L, const void* R, const RowBlocks* lb, const RowBlocks* rbk, int64_t K, int64_t h_in,
-                        int64_t h_out, float* G, float* partials, SplitPlan sp, int tile, hipStream_t s) {
+                        int64_t h_out, float* G, float* partials, SplitPlan sp, int tile, hipStream_t s, bool fine) {
     float* dst = sp.splits == 1 ? G : partials;
     dad_status rc;
     if ((lb != nullptr) != (rbk != nullptr) || (lb && tile == 0)) return DAD_ERR_SHAPE;
     if (tile != 0) {
-        rc = tile == 128 ? launch_rebuild_dma<128, 2, 2>(L, R, lb, rbk, dst, K, h_in, h_out, sp, s)
-                         : launch_rebuild_dma<256, 2, 4>(L, R, lb, rbk, dst, K, h_in, h_out, sp, s);
+        rc = tile == 128 ? launch_rebuild_dma<128, 2, 2>(L, R, lb, rbk, dst, K, h_in, h_out, sp, fine, s)
+                         : launch_rebuild_dma<256, 2, 4>(L, R, lb, rbk, dst, K, h_in, h_out, sp, fine, s);
         if (rc != DAD_OK) return rc;
     } else {
         const int tm = (int)ceil_div(h_in, ra::TILE), tn = (int)ceil_div(h_out, ra::TILE);
@@ -765,12 +819,78 @@ dad_status launch_rebuild_group(int n, const void* const* L, const void* const* 
     return DAD_OK;
 }
 
+// n products, each by its own plan (the bits are those of a call of its own) and with its slabs from G on, in as few launches as their
+// kernels allow.
+dad_status launch_rebuild_own(const OwnProduct* jobs, int n, dad_dtype dt, hipStream_t s) {
+    if (n == 1 && dt == DAD_BF16) return launch_rebuild(jobs[0].L, jobs[0].R, jobs[0].K, jobs[0].h_in, jobs[0].h_out, dt, jobs[0].G, jobs[0].G, jobs[0].rb, s);
+    if (n > MAX_JOBS) return DAD_ERR_SHAPE;
+    if (dt == DAD_F32) {
+        const void *L[MAX_JOBS], *R[MAX_JOBS];
+        float* G[MAX_JOBS];
+        int64_t K[MAX_JOBS], hi[MAX_JOBS], ho[MAX_JOBS];
+        SplitPlan sp[MAX_JOBS];
+        for (int i = 0; i < n; ++i) L[i] = jobs[i].L, R[i] = jobs[i].R, G[i] = jobs[i].G, K[i] = jobs[i].K, hi[i] = jobs[i].h_in, ho[i] = jobs[i].h_out, sp[i] = jobs[i].rb.split;
+        return launch_rebuild_f32(n, L, R, G, K, hi, ho, sp, G, s, true);
+    }
+    constexpr int lds256 = rb::DMA_STAGES * 2 * rb::BK * 256 * 2, lds128 = rb::DMA_STAGES * 2 * rb::BK * 128 * 2;
+    // 256-tiles, 128-tiles, any shape; of the first two, K of whole stages in one sum, and others
+    auto kind = [&](const OwnProduct& j) { return j.rb.tile == 0 ? 4 : (j.rb.tile == 128 ? 2 : 0) + (j.rb.fine || j.K % rb::BK != 0); };
+    SumJob sums[MAX_JOBS];
+    int nsum = 0;
+    for (int i = 0; i < n; ++i)
+        if (jobs[i].rb.split.splits > 1) sums[nsum++] = SumJob{jobs[i].G, jobs[i].G, nullptr, jobs[i].h_in * jobs[i].h_out, jobs[i].rb.split.splits};
+    for (int which = 0; which < 5; ++which) {
+        int of[MAX_JOBS], c = 0;
+        for (int i = 0; i < n; ++i)
+            if (kind(jobs[i]) == which) {
+                int at = c++;  // longest workgroups first
+                for (; at > 0 && jobs[of[at - 1]].rb.split.chunk < jobs[i].rb.split.chunk; --at) of[at] = of[at - 1];
+                of[at] = i;
+            }
+        for (int first = 0; first < c; first += rb::MAX_JOBS) {
+            RebuildJobs tb;
+            int64_t per = 0;  // workgroups of an XCD
+            for (int i = 0; i < rb::MAX_JOBS; ++i) {
+                if (first + i >= c) {
+                    tb.first_block[i] = 0x7fffffff;
+                    tb.j[i] = RebuildJob{};
+                    continue;
+                }
+                const OwnProduct& j = jobs[of[first + i]];
+                const int tile = j.rb.tile ? j.rb.tile : ra::TILE;
+                const int64_t tm = ceil_div(j.h_in, tile), tn = ceil_div(j.h_out, tile), total = tm * tn * j.rb.split.splits;
+                tb.first_block[i] = (int)per;
+                per += ceil_div(total, 8);
+                if (per > (int64_t)1 << 27) return DAD_ERR_SHAPE;
+                tb.j[i] = RebuildJob{static_cast<const bf16_t*>(j.L), static_cast<const bf16_t*>(j.R), j.G, j.K, j.rb.split.chunk,
+                                     (int)j.h_in, (int)j.h_out, (int)tm, (int)tn, (int)total};
+            }
+            const dim3 grid((unsigned)(8 * per));
+            ProfScope prof(which == 4 ? KID_REBUILD_BF16 : KID_REBUILD_BF16_DMA, s);
+            if (which == 0)
+                hipLaunchKernelGGL((k_rebuild_bf16_dma_own<256, 2, 4, false>), grid, dim3(512), lds256, s, tb);
+            else if (which == 1)
+                hipLaunchKernelGGL((k_rebuild_bf16_dma_own<256, 2, 4, true>), grid, dim3(512), lds256, s, tb);
+            else if (which == 2)
+                hipLaunchKernelGGL((k_rebuild_bf16_dma_own<128, 2, 2, false>), grid, dim3(256), lds128, s, tb);
+            else if (which == 3)
+                hipLaunchKernelGGL((k_rebuild_bf16_dma_own<128, 2, 2, true>), grid, dim3(256), lds128, s, tb);
+            else
+                hipLaunchKernelGGL(k_rebuild_bf16_own, grid, dim3(ra::THREADS), ra::LDS, s, tb);
+            DAD_LAUNCH_CHECK();
+        }
+    }
+    return reduce_slabs(sums, nsum, s);
+}
+
 template <int T, int WM, int WN>
 static dad_status prepare_dma() {
     constexpr int lds = rb::DMA_STAGES * 2 * rb::BK * T * 2;
     DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, RowBlocks, true>), lds));
     DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, false>), lds));
     DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma<T, WM, WN, const bf16_t*, true>), lds));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma_own<T, WM, WN, false>), lds));
+    DAD_HIP_TRY(set_max_lds((k_rebuild_bf16_dma_own<T, WM, WN, true>), lds));
     return DAD_OK;
 }
 

@@ -580,7 +580,7 @@ constexpr int64_t SEQ_MANY_PRODUCTS = 64 * 5;
 static SeqPlan plan_sequential(int64_t N, int64_t h_in, int64_t h_out, dad_dtype dt) {
     SeqPlan p;
     const size_t vec = align_up((size_t)h_out * 4, 256);
-    p.c = plan_compress(N, h_in, h_out, 1, dt);
+    p.c = plan_factors(N, h_in, h_out, 1, dt);
     p.d = plan_dense(N, h_in, h_out, 1, dt);
     p.dense = dense_wins(N, h_in, h_out, dt, SEQ_MANY_PRODUCTS);
     const size_t factors = p.c.off_Yt + vec;  // nothing is orthonormalised: the layout ends with its Yt
@@ -654,13 +654,13 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
     const dad_dtype xt = dense ? DAD_F32 : dt;
     auto nn = [&](const void* X, const float* P, int64_t h, SplitPlan sp, const int* skip) {
         if (!c.direct) return gen_thin_nn(X, P, V, part, sp, rows, h, 1, xt, nullptr, s, skip);
-        const NnJob j = {X, P, static_cast<float*>(V), part, nullptr, rows, (int)h, sp.splits};
-        return direct_nn(&j, 1, 1, xt, s, skip);
+        const NnJob j = {X, P, static_cast<float*>(V), part, nullptr, rows, (int)h, (short)sp.splits, xt == DAD_F32, 0, 0};
+        return direct_nn(&j, 1, 1, s, skip);
     };
     auto tn = [&](const void* X, float* out, int64_t h, SplitPlan sp, const int* skip) {
         if (!c.direct) return gen_thin_tn(X, V, out, part, sp, rows, h, 1, xt, s, skip);
-        const TnJob j = {X, static_cast<const float*>(V), sp.splits == 1 ? out : part, rows, sp.chunk, (int)h, sp.splits};
-        const dad_status rc = direct_tn(&j, 1, 1, xt, s, skip);
+        const TnJob j = {X, static_cast<const float*>(V), sp.splits == 1 ? out : part, rows, sp.chunk, (int)h, sp.splits, xt == DAD_F32};
+        const dad_status rc = direct_tn(&j, 1, 1, s, skip);
         return rc == DAD_OK && sp.splits > 1 ? reduce_slabs(part, out, h, sp.splits, s, nullptr, skip) : rc;
     };
     // y = M^T M g, and p = M g (in V on the gradient, in Ut on the factors)
@@ -703,7 +703,7 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
             float* const vectors[2] = {panel, Ut};
             const int splits = c.tn_out.splits;
             a.slabs = splits == 1 ? Yt : part, a.nslabs = splits;
-            const TnJob product = {M, static_cast<const float*>(V), splits == 1 ? Yt : part, h_in, c.tn_out.chunk, (int)h_out, splits};
+            const TnJob product = {M, static_cast<const float*>(V), splits == 1 ? Yt : part, h_in, c.tn_out.chunk, (int)h_out, splits, 1};
             for (int j = 0; j < r; ++j)
                 for (int it = 0; it <= n_iter; ++it) {
                     const bool waits = it == n_iter && j + 1 < r;
@@ -713,7 +713,7 @@ static dad_status sequential_launch(const SeqPlan& p, const void* A, const void*
                     a.p_before = j > 0 ? Qt + (int64_t)(j - 1) * h_in : nullptr;
                     a.g = vectors[it & 1], a.g_before = vectors[(it == 0 ? n_iter : it - 1) & 1];
                     DAD_TRY(seq_product<true>(a, s));
-                    if (it < n_iter) DAD_TRY(direct_tn(&product, 1, 1, DAD_F32, s, nullptr));
+                    if (it < n_iter) DAD_TRY(direct_tn(&product, 1, 1, s, nullptr));
                 }
             return end(a.g);
         }

@@ -102,6 +102,14 @@ def test_static_scratch_holds_tall_reductions(lib, N, h_in, h_out, r, dt):
     assert 0 < lib.dad_compress_workspace_bytes(N, h_in, h_out, r, dt) <= dad.DAD_STATIC_SCRATCH_BYTES
 
 
+# M and its slabs stay within the static scratch wherever the reduction on the factors does; what they need is asked for
+@pytest.mark.parametrize("N,h_in,h_out,r,dt,least", [(64, 784, 128, 4, 0, 784 * 128), (16384, 768, 3072, 16, 1, 768 * 3072), (13399, 768, 3072, 16, 1, 2 * 768 * 3072),
+                                                     (3767, 1300, 2052, 33, 1, 1300 * 2052), (60000, 2000, 3000, 16, 1, 0), (16384, 768, 768, 16, 1, 2 * 768 * 768)])
+def test_workspace_of_reductions_on_m(lib, N, h_in, h_out, r, dt, least):
+    need = lib.dad_compress_workspace_bytes(N, h_in, h_out, r, dt)
+    assert 4 * least < need <= dad.DAD_STATIC_SCRATCH_BYTES
+
+
 def test_reconstruct_and_stack_reject_bad_arguments_on_host(lib):
     p = 0x1000
     assert lib.dad_reconstruct_grad(None, p, 4, 8, 8, 0, p, None, 0, None) == dad.DAD_ERR_NULL

@@ -1,0 +1,134 @@
+"""Reductions on M = A^T Delta (two applications or more, where that takes less time) and the ones on the factors beside them."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dad_oracle as O
+from paper_2102_09631_amd import binding as dad
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(N, h_in, h_out, r, seed, dev, dtype):
+    g = torch.Generator(device="cpu").manual_seed(seed)
+    A = torch.relu(torch.randn(N, h_in, generator=g)).to(dtype).to(dev)
+    D = (0.03 * torch.randn(N, h_out, generator=g)).to(dtype).to(dev)
+    return A, D, torch.randn(r, h_out, generator=g).to(dev)
+
+
+def _np(t):
+    return t.detach().float().cpu().numpy()
+
+
+def _kernels(call):
+    dad.profile_enable(True)
+    try:
+        dad.profile_reset()
+        call()
+        return dad.profile_read()
+    finally:
+        dad.profile_enable(False)
+
+
+def _bound(A, D, r):
+    # fp32 sums of 1.2e-7 each in M and in the products with it, and the fp32 resolution of the weakest kept direction
+    s = np.linalg.svd(_np(A).astype(np.float64).T @ _np(D), compute_uv=False)
+    return 1e-6 + 4 * np.finfo(np.float32).eps * s[0] / s[r - 1]
+
+
+# rows and widths that end inside a tile, a block and a 16-byte load; M in one slab and in several (its own place and behind it), by
+# the kernel for any shape, by 128-tiles of a whole and of a ragged K and by 256-tiles; few rows of M that several workgroups
+# share, in rows of 32 and others (their sum is copied into Pt); slabs of M^T U summed by the orthonormalisation and before it
+@pytest.mark.parametrize("dtype,N,h_in,h_out,r", [("f32", 65, 33, 47, 5), ("f32", 64, 784, 128, 4), ("f32", 1277, 897, 130, 33), ("bf16", 300, 130, 70, 16),
+                                                  ("bf16", 1161, 172, 80, 20), ("bf16", 2001, 70, 1900, 8), ("bf16", 2001, 64, 1900, 48),
+                                                  ("bf16", 5000, 2001, 71, 8), ("bf16", 6000, 384, 256, 7), ("bf16", 6001, 384, 256, 64),
+                                                  ("bf16", 8448, 256, 512, 64), ("bf16", 16640, 768, 256, 16), ("bf16", 9001, 700, 333, 33)])
+def test_reduction_on_m(gpu, dtype, N, h_in, h_out, r):
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    A, D, G0 = _layer(N, h_in, h_out, r, 11 + N, gpu, dt)
+    ran = _kernels(lambda: dad.compress_rank(A, D, r, 2, G0))
+    assert any(k.startswith("k_rebuild") for k in ran)
+    ws = torch.full((dad.compress_workspace_bytes(N, h_in, h_out, r, dt),), 255, dtype=torch.uint8, device=gpu)  # NaN all over
+    for n in (2, 3):
+        Pt, Gt = dad.compress_rank(A, D, r, n, G0, workspace=ws)
+        ref = O.rank_r_grad(*O.block_spi(_np(A), _np(D), _np(G0), n))
+        assert O.rel_fro(_np(Pt).astype(np.float64).T @ _np(Gt), ref) <= _bound(A, D, r)
+        assert np.abs(_np(Gt).astype(np.float64) @ _np(Gt).T - np.eye(r)).max() <= 1e-6
+        # the static scratch holds it too, with the same bits
+        P2, G2 = torch.empty_like(Pt), torch.empty_like(Gt)
+        dad.compress_rank_noalloc(A, D, r, n, G0, P2, G2)
+        assert torch.equal(Pt, P2) and torch.equal(Gt, G2)
+    # one application is done on the factors
+    assert not any(k.startswith("k_rebuild") for k in _kernels(lambda: dad.compress_rank(A, D, r, 1, G0, workspace=ws)))
+
+
+# the kernels on the factors with two applications, in a workspace without room for M
+@pytest.mark.parametrize("dtype,N,h_in,h_out,r,nbytes", [("bf16", 2001, 70, 1900, 8, 0.5), ("bf16", 8448, 256, 512, 32, 0.9), ("bf16", 20000, 512, 1000, 16, 0.6),
+                                                         ("f32", 64, 784, 128, 4, 0.5)])
+def test_workspace_without_room_for_m(gpu, dtype, N, h_in, h_out, r, nbytes):
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    A, D, G0 = _layer(N, h_in, h_out, r, 5, gpu, dt)
+    need = dad.compress_workspace_bytes(N, h_in, h_out, r, dt)
+    ws = torch.empty(int(need * nbytes) // 256 * 256, dtype=torch.uint8, device=gpu)
+    ran = _kernels(lambda: dad.compress_rank(A, D, r, 2, G0, workspace=ws))
+    assert not any(k.startswith("k_rebuild") for k in ran)
+    Pt, Gt = dad.compress_rank(A, D, r, 2, G0, workspace=ws, check=True)
+    ref = O.rank_r_grad(*O.block_spi(_np(A), _np(D), _np(G0), 2))
+    assert O.rel_fro(_np(Pt).astype(np.float64).T @ _np(Gt), ref) <= (2e-2 if N % 256 == 0 and dtype == "bf16" else _bound(A, D, r))
+
+
+# groups: runs that batch on M (more than the eight of a launch; other widths among them), layers on the factors of both kinds beside
+# them, sites in place
+@pytest.mark.parametrize("lanes", [1, 3, 8])
+@pytest.mark.parametrize("dtype,shapes,r", [("bf16", [(4608, 256, 384)] * 10, 16),
+                                            ("bf16", [(8192, 256, 512), (8192, 512, 256), (8192, 256, 256), (1024, 256, 256), (1000, 90, 60)], 32),
+                                            ("bf16", [(300, 2000, 2100), (300, 128, 90), (512, 256, 128), (300, 90, 128), (4608, 128, 256)], 16),
+                                            ("f32", [(600, 1500, 1700), (600, 128, 130), (600, 60, 200)], 5)])
+def test_groups_with_layers_on_m_equal_single_calls(gpu, dtype, shapes, r, lanes):
+    dad.init()
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    layers = [_layer(n, a, b, r, 40 + i, gpu, dt) for i, (n, a, b) in enumerate(shapes)]
+    for n_iter in (2, 1):
+        single = [dad.compress_rank(A, D, r, n_iter, G0, check=True) for A, D, G0 in layers]
+        grp = dad.CompressGroup(layers, r, n_iter, lanes=lanes)
+        grp.run(check=True)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            grp.run()
+        for rep in range(3):
+            for p, g in zip(grp.Pt, grp.Gt):
+                p.fill_(float("nan"))
+                g.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            for (p1, g1), p2, g2 in zip(single, grp.Pt, grp.Gt):
+                assert torch.equal(p1, p2) and torch.equal(g1, g2), (n_iter, rep)
+            _ = dad.reconstruct_grad(grp.Pt[0], grp.Gt[0])  # eager work between the replays
+            torch.cuda.synchronize()
+    broken = [(A, torch.zeros_like(D) if i == 1 else D, G0) for i, (A, D, G0) in enumerate(layers)]
+    bad = dad.CompressGroup(broken, r, 2, lanes=lanes)
+    bad.run()
+    assert dad.poll_numeric_status(bad.workspace) == dad.DAD_ERR_NUMERIC
+
+
+@pytest.mark.parametrize("rows", [[4096, 0, 512, 256], [4000, 37, 700]])
+def test_sites_on_m_equal_the_stacked_call(gpu, rows):
+    h_in, h_out, r = 256, 384, 16
+    A, D, G0 = _layer(sum(rows), h_in, h_out, r, 3, gpu, torch.bfloat16)
+    assert any(k.startswith("k_rebuild") for k in _kernels(lambda: dad.compress_rank(A, D, r, 2, G0)))
+    Pt, Gt = dad.compress_rank(A, D, r, 2, G0, check=True)
+    P2, G2 = dad.compress_rank_sites([x.clone() for x in A.split(rows)], [x.clone() for x in D.split(rows)], r, 2, G0)
+    torch.cuda.synchronize()
+    assert torch.equal(Pt, P2) and torch.equal(Gt, G2)
+
+
+# the kernels on the factors at the edges of their blocks and tiles, with the one application that is always done there
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,h_in,h_out,r", [(61, 65, 68, 15), (301, 130, 200, 32), (513, 300, 200, 49), (9000, 90, 131, 8), (6000, 1500, 1400, 20),
+                                            (8161, 40, 70, 17), (12000, 70, 140, 64), (16400, 129, 70, 20), (24545, 72, 130, 16), (50000, 48, 64, 48),
+                                            (9001, 2050, 1900, 40), (260, 4099, 2055, 20)])
+def test_one_application_on_the_factors(gpu, dtype, N, h_in, h_out, r):
+    A, D, G0 = _layer(N, h_in, h_out, r, 7 + N, gpu, torch.bfloat16 if dtype == "bf16" else torch.float32)
+    Pt, Gt = dad.compress_rank(A, D, r, 1, G0, check=True)
+    ref = O.rank_r_grad(*O.block_spi(_np(A), _np(D), _np(G0), 1))
+    assert O.rel_fro(_np(Pt).astype(np.float64).T @ _np(Gt), ref) <= 1e-5 + _bound(A, D, r)
