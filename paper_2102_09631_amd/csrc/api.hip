@@ -289,9 +289,11 @@ struct CompressJob {
         if ((rc = (expr)) != DAD_OK) return rc; \
     } while (0)
 
-// A few slabs of Y are summed by the orthonormalisation on the way; many before it (its few workgroups
-// would take longer to read them than a launch of their own: 8 against 5 us at r = 32 with 16 slabs).
-static bool few_slabs(int r, int splits) { return r * splits <= 192; }
+// A few slabs of Y are summed by the orthonormalisation on the way; more before it, as its few workgroups then take longer
+// to read them than a launch of their own.  Whole reductions at a line of 192 / 110 / none on the way, us: 777 x 768 x 3072
+// r = 48, four slabs 203 / 188 / 188, r = 33, five 185 / 174 / 174; 2048 x 512 x 512 r = 64, two 223 / 211 / 211;
+// 16-bit 512 x 1664 x 128 r = 8, six 51 / 51 / 53; 71 x 1304 x 404 r = 4 51 / 51 / 55.
+static bool few_slabs(int r, int splits) { return r * splits <= 110; }
 
 static QrJob qr_job(const CompressJob& j, const float* Y, float* Ysum, int splits, bf16_t* gb) {
     return QrJob{Y, Ysum, j.Gt, gb, j.at<double>(j.p->off_gram), j.at<double>(j.p->off_rinv), j.hdr(), j.flag, (int)j.h_out,
