@@ -184,8 +184,9 @@ static RoutePlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, da
 
 // Whether two applications (five products with M) take less time on M, in microseconds fitted to 300 shapes timed both ways (64 to 65536 rows,
 // widths 64 to 4096, r 1 to 64, both types; 13399 x 768 x 3072, r = 16, 193 us on the factors and 154 on M, r = 32 272 and 186;
-// 8192 x 1024 x 1024, r = 64, 263 and 169; 17482 x 128 x 2432 175 and 87; 7900 x 2500 x 640 fp32 248 and 314).  By this rule 300 other shapes
-// take 1 / 1.30 of their time, and none of them 5 % more.  A product on the factors is two launches more and reads both
+// 8192 x 1024 x 1024, r = 64, 263 and 169; 17482 x 128 x 2432 175 and 87; 7900 x 2500 x 640 fp32 248 and 314) and 100 of 60 to 840 MB of factors
+// (131072 x 1536 x 1536, r = 32, 763 and 1083; 65536 x 3072 x 768, r = 64, 570 and 429; 32768 x 1280 x 5120, r = 64, 542 and 810).  By this rule
+// 300 other shapes take 1 / 1.30 of their time, 60 large ones 1 / 1.46, and none of them 5 % more.  A product on the factors is two launches more and reads both
 // factors.  The second line is for a layer of a group: the launches are then shared, and what counts is whose work fills the chip; the third for
 // fp32, where making M is no less work than the products: a group with a layer on the factors has their launches all the same.
 // Not for whole-tile layers of up to 4096 rows: those share the launches of a batch, a region of which is a few hundred KB on the factors.
@@ -195,8 +196,9 @@ static bool dense_saves(int64_t N, int64_t h_in, int64_t h_out, int r, dad_dtype
     const double mb = (double)N * (h_in + h_out) * elem_size(dt) * 1e-6, mb_M = (double)h_in * h_out * 4e-6;
     const double launches = 5.0 * (5.2 + (N > 256 ? 2.2 : 0.0));
     const double per_mb = p.f.dma ? 0.083 + 0.031 * tiles16 : dt == DAD_BF16 ? 0.15 + 0.048 * tiles16 : 0.13 * tiles16;
-    const double full = p.f.dma && mb > 500.0 ? 500.0 : mb;  // the streaming kernels reach 6 TB/s beyond
-    const double bytes = 5.0 * (full * per_mb + (mb - full) * 0.165 - 0.26 * mb_M);
+    // Larger bf16 factors take less a megabyte beyond the first 100, with the streaming kernels the same at any rank.
+    const double near = dt == DAD_BF16 && mb > 100.0 ? 100.0 : mb, far = p.f.dma ? 0.12 : 0.8 * per_mb;
+    const double bytes = 5.0 * (near * per_mb + (mb - near) * far - 0.26 * mb_M);
     const ProductTime t = dt == DAD_F32 ? rebuild_f32_time(N, h_in, h_out) : rebuild_bf16_time(N, h_in, h_out, p.rb);
     return launches + bytes > 6.0 + t.alone &&
            (p.f.dma ? 1.0 : 0.33) * (launches - 6.0) + bytes > t.share &&

@@ -634,8 +634,11 @@ static SplitPlan rebuild_any_split(int64_t K, int64_t h_in, int64_t h_out, int l
 ProductTime rebuild_bf16_time(int64_t K, int64_t h_in, int64_t h_out, const RebuildPlan& p) {
     const int tile = p.tile ? p.tile : ra::TILE, s = p.split.splits;
     const int64_t wg = ceil_div(h_in, tile) * ceil_div(h_out, tile) * s, slots = tile == 256 ? CU_COUNT : 2 * CU_COUNT;
-    const double full = p.tile == 0 ? 0.48 : p.tile == 128 ? 0.41 : 0.86;  // of a whole round
-    const double first = p.tile == 0 ? 0.23 + 0.07 * wg / CU_COUNT : p.tile == 128 ? 0.32 : full;  // one workgroup to a unit
+    // Of a whole round.  128-tiles of a larger product drift apart in K and lose each other's lines: 0.41 us at 100 MB of operands, 0.49 at 250,
+    // 0.60 at 500, 0.72 at 800 (131072 x 1536 x 1536 in three chunks: 986 us).
+    const double mb = (double)K * (h_in + h_out) * 2e-6;
+    const double full = p.tile == 0 ? 0.48 : p.tile == 128 ? 0.41 + (mb > 100.0 ? 0.0005 * (mb - 100.0) : 0.0) : 0.89;
+    const double first = p.tile == 0 ? 0.23 + 0.07 * wg / CU_COUNT : p.tile == 128 ? (p.fine ? 0.34 : 0.32) : full;  // one workgroup to a unit
     const double stages = (double)ceil_div(p.split.chunk, rb::BK), slabs = s == 1 ? 0.0 : 0.24 * (2.0 * s + 1.0) * h_in * h_out * 4e-6;
     return ProductTime{(p.tile == 0 ? 4.3 : 0.5) + slabs + (s == 1 ? 0.0 : 2.5) + stages * (wg <= CU_COUNT ? first : full * (double)ceil_div(wg, slots)),
                        slabs + stages * full * (double)wg / (double)slots};
