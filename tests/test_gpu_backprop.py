@@ -102,6 +102,20 @@ def test_backprop_delta_rounds_correctly(gpu, N, h, act):
     assert off.double().mean().item() <= 6e-5
 
 
+# every bf16 number as a pre-activation, subnormals, infinities and NaN included; one term in each sum, so that the contraction is exact
+@pytest.mark.parametrize("N,h", [(16384, 1024), (300, 72)])
+def test_backprop_delta_relu_of_every_number(gpu, N, h):
+    hn = 64
+    W = torch.randn(h, hn, generator=torch.Generator().manual_seed(5)).bfloat16().to(gpu)
+    D = torch.zeros(N, hn, dtype=torch.bfloat16, device=gpu)
+    pick = torch.arange(N, device=gpu) % hn
+    D[torch.arange(N, device=gpu), pick] = 1
+    Z = (torch.arange(N * h, device=gpu) * 40503 % 65536 - 32768).to(torch.int16).view(torch.bfloat16).view(N, h)
+    out = dad.backprop_delta(D, W, Z, "relu")
+    want = W.t()[pick] * (Z.float() > 0).bfloat16()
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+
+
 def test_backprop_delta_writes_sites_in_place_in_the_stacked_buffer(gpu):
     """Three sites write their rows at their offsets of one stacked buffer; the result is the
     delta of the stacked batch (rows are independent), and rows outside a call stay untouched."""
