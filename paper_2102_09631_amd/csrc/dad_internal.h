@@ -56,6 +56,16 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// The barrier of a ring of tiles: behind it this tile is complete (at most N younger loads are in flight) and the slot of the one before is free.
+// For the latter a wave's own LDS reads have to be done.  __syncthreads() waits for them too, but in the gradient kernels the compiler left that
+// wait out at the head of the loop, where the reads come round the back edge only, and a product beside other kernels took
+// values of a later tile for its own now and then (8 blocks of 8192 x 1024 x 1024 beside three larger reductions: 14 of 60 calls).
+// The loops of the other kernels that use such rings have the wait in the compiled code.
+template <int N>
+__device__ __forceinline__ void tile_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+
 // Places NR LDS reads and NM matrix instructions of one scheduling region alternately in the
 // instruction stream (reads first or matrix instructions first), so that a wave's fragment reads are
 // issued in the shadow of its own MFMAs instead of in a block before them.

@@ -453,11 +453,11 @@ __device__ __forceinline__ void rebuild_tile_dma(const SRC& L, const SRC& R, flo
     auto step = [&](int kt, auto stage_c) {
         constexpr int STAGE = decltype(stage_c)::value;
         // tile kt has landed once at most DMA_STAGES-2 younger tiles are outstanding
+        // everyone's part of tile kt is in LDS, and tile kt-1's slot is free
         if (kt + rb::DMA_STAGES - 2 < nk)
-            wait_vmcnt<rb::DMA_LOADS * (rb::DMA_STAGES - 2)>();
+            tile_barrier<rb::DMA_LOADS * (rb::DMA_STAGES - 2)>();
         else
-            wait_vmcnt<0>();
-        __syncthreads();  // everyone's part of tile kt is in LDS, and tile kt-1's slot is free
+            tile_barrier<0>();
         if (kt + rb::DMA_STAGES - 1 < nk) issue((STAGE + rb::DMA_STAGES - 1) % rb::DMA_STAGES);
         const char* tl = smem + STAGE * STAGEB;
         if constexpr (TAIL) {

@@ -132,3 +132,24 @@ def test_one_application_on_the_factors(gpu, dtype, N, h_in, h_out, r):
     Pt, Gt = dad.compress_rank(A, D, r, 1, G0, check=True)
     ref = O.rank_r_grad(*O.block_spi(_np(A), _np(D), _np(G0), 1))
     assert O.rel_fro(_np(Pt).astype(np.float64).T @ _np(Gt), ref) <= 1e-5 + _bound(A, D, r)
+
+
+# M made on the caller's stream while other layers' passes keep the memory and the LDS of the same units busy: a tile's loads
+# then arrive as late, and its fragments are read as late, as they ever are
+@pytest.mark.parametrize("sites", [False, True])
+def test_m_beside_other_layers(gpu, sites):
+    S, b, r = 8, 8192, 32
+    gen = torch.Generator(device=gpu)
+    gen.manual_seed(1)
+    layers = []
+    for h_in, h_out in ((1024, 3072), (1024, 1024), (1024, 4096), (4096, 1024)):
+        A = [torch.randn(b, h_in, generator=gen, device=gpu).to(torch.bfloat16) for _ in range(S)]
+        D = [(1e-2 * torch.randn(b, h_out, generator=gen, device=gpu)).to(torch.bfloat16) for _ in range(S)]
+        layers.append((A, D, torch.randn(r, h_out, generator=gen, device=gpu)))
+    A, D = dad.stack_factors(layers[1][0], layers[1][1])
+    P1, G1 = dad.compress_rank(A, D, r, 2, layers[1][2])
+    group = dad.CompressGroup(layers if sites else [(*dad.stack_factors(a, d), g) for a, d, g in layers], r, 2, lanes=4)
+    for _ in range(40):
+        group.run()
+        torch.cuda.synchronize()
+        assert torch.equal(group.Pt[1], P1) and torch.equal(group.Gt[1], G1)
