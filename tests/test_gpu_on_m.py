@@ -39,7 +39,7 @@ def _bound(A, D, r):
 # rows and widths that end inside a tile, a block and a 16-byte load; M in one slab and in several (its own place and behind it), by
 # the kernel for any shape, by 128-tiles of a whole and of a ragged K and by 256-tiles; few rows of M that several workgroups
 # share, in rows of 32 and others (their sum is copied into Pt); slabs of M^T U summed by the orthonormalisation and before it
-@pytest.mark.parametrize("dtype,N,h_in,h_out,r", [("f32", 65, 33, 47, 5), ("f32", 64, 784, 128, 4), ("f32", 1277, 897, 130, 33), ("bf16", 300, 130, 70, 16),
+@pytest.mark.parametrize("dtype,N,h_in,h_out,r", [("f32", 63, 789, 131, 5), ("f32", 64, 784, 128, 4), ("f32", 1277, 897, 130, 33), ("bf16", 1030, 130, 70, 16),
                                                   ("bf16", 1161, 172, 80, 20), ("bf16", 2001, 70, 1900, 8), ("bf16", 2001, 64, 1900, 48),
                                                   ("bf16", 5000, 2001, 71, 8), ("bf16", 6000, 384, 256, 7), ("bf16", 6001, 384, 256, 64),
                                                   ("bf16", 8448, 256, 512, 64), ("bf16", 16640, 768, 256, 16), ("bf16", 9001, 700, 333, 33)])
