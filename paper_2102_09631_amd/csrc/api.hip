@@ -186,7 +186,7 @@ static RoutePlan plan_compress(int64_t N, int64_t h_in, int64_t h_out, int r, da
 // widths 64 to 4096, r 1 to 64, both types; 13399 x 768 x 3072, r = 16, 193 us on the factors and 154 on M, r = 32 272 and 186;
 // 8192 x 1024 x 1024, r = 64, 263 and 169; 17482 x 128 x 2432 175 and 87; 7900 x 2500 x 640 fp32 248 and 314) and 100 of 60 to 840 MB of factors
 // (131072 x 1536 x 1536, r = 32, 763 and 1083; 65536 x 3072 x 768, r = 64, 570 and 429; 32768 x 1280 x 5120, r = 64, 542 and 810).  By this rule
-// 42 drawn layers take 1 / 1.18 of their time, 60 large ones 1 / 1.46, and none of them 5 % more.  A product on the factors is two launches more and reads both
+// 42 drawn layers take 1 / 1.18 of their time, 60 large ones 1 / 1.45, and none of them 5 % more.  A product on the factors is two launches more and reads both
 // factors.  The second line is for a layer of a group: the launches are then shared, and what counts is whose work fills the chip (beyond r = 32 the
 // lanes hide a layer's orthonormalisation behind the others' passes: two of 11264 x 1408 x 2304, r = 64, 546 us on the factors, 645 on M).  The third
 // bounds what M costs a group that has the factors' launches all the same: few rows, where the widths of a block go either way (336 rows, 2082 x 256 to
